@@ -938,7 +938,7 @@ constexpr uint32_t enc_ring_bytes() {
 // (incompressible tiles: no overlap, as with one stage).
 template <typename T, int B, int BATCH>
 __device__ __forceinline__ void encode_pass(const CBatch& b, uint32_t* s_scan, uint32_t* s_tile, uint64_t* s_base,
-                                            uint64_t* s_end, uint32_t* s_stage) {
+                                            uint64_t* s_end, uint32_t* s_stage, ScanShared* s_sums) {
   using U = typename Traits<T>::U;
   using G = Geo<T, B>;
   constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB;
@@ -948,15 +948,13 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, uint32_t* s_scan, u
   constexpr int DT = sizeof(T) == 4 ? 0 : 1;
   const uint64_t ntiles = b.tiles_enc[DT];
   if (ntiles == 0) return;
-  // A single call's workgroup 0 is the scan wave of the tiles' mid-byte
+  // A single call's workgroup 0 is the scan workgroup of the tiles' mid-byte
   // offsets (the others wait on one status word each); a batch's tiles, of
   // many fields, resolve their offsets by look-back.
   if constexpr (BATCH == kSingle) {
     if (blockIdx.x == 0) {
-      if (threadIdx.x < kWave) {
-        const FieldC f = field_at<BATCH>(b, 0);
-        scan_wave<16>(f.enc_mid, ntiles, &f.ctr->err, 1u);
-      }
+      const FieldC f = field_at<BATCH>(b, 0);
+      scan_workgroup(f.enc_mid, ntiles, &f.ctr->err, 1u, *s_sums);
       return;
     }
   }
@@ -999,7 +997,7 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, uint32_t* s_scan, u
   uint32_t p_tile = 0, p_field = 0, p_bytes = 0, p_at = 0;
   uint32_t at = 0;  // ring byte of the current tile's start (16-byte aligned)
   // Resolve the pending tile's offset, copy it out and clear its ring bytes.
-  // A single call's tile waits on its own status word, which the scan wave
+  // A single call's tile waits on its own status word, which the scan workgroup
   // publishes; a batch's walks back by look-back, one status word per lane a
   // round (status loads go to the device's coherence point, and wider
   // windows measured slower).
@@ -1228,7 +1226,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Geo<T, B>::
   __shared__ uint32_t s_tile;
   __shared__ uint64_t s_base, s_end;
   __shared__ __align__(16) uint32_t s_stage[enc_ring_bytes<T, B>() / 4];
-  encode_pass<T, B, BATCH>(b, s_scan, &s_tile, &s_base, &s_end, s_stage);
+  __shared__ ScanShared s_sums;
+  encode_pass<T, B, BATCH>(b, s_scan, &s_tile, &s_base, &s_end, s_stage, &s_sums);
 }
 
 // --------------------------------------------------------------- finalize ---
@@ -1275,7 +1274,7 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
       const uint64_t want = std::max<uint64_t>(g.encode_wgs[dt], kTicketClasses);
       const uint32_t genc = (uint32_t)std::min<uint64_t>(b.tiles_enc[dt], want);
       const bool batch = b.fields != nullptr;
-      // a single call adds workgroup 0, its scan wave
+      // a single call adds workgroup 0, its scan workgroup
       if (dt == 0 && !batch)
         run("k_encode", [&] { k_encode<float, B, kSingle><<<genc + 1, 256, 0, stream>>>(b); });
       else if (dt == 0)

@@ -403,7 +403,10 @@ __device__ __forceinline__ void wg_excl_scan_multi(const uint32_t (&v)[S], uint3
 // ------------------------------------------------------ decoupled look-back -
 
 // A tile's status word: flag in the top two bits (0 = not yet published,
-// 1 = aggregate of the tile alone, 2 = inclusive prefix), value below.
+// 1 = aggregate of the tile alone, 2 = inclusive prefix), value below. An
+// aggregate takes at most 23 bits (the values of 1024 blocks of 1024 doubles),
+// so a window of them adds up in 32 bits, with DPP and no LDS (sums of 64-bit
+// words by lane shuffles cost 12 LDS permutes a window, one after another).
 constexpr uint64_t kFlagAgg = 1ull << 62;
 constexpr uint64_t kFlagIncl = 2ull << 62;
 constexpr uint64_t kValueMask = (1ull << 62) - 1;
@@ -436,6 +439,15 @@ __device__ __forceinline__ void lookback_publish(uint64_t* status, uint32_t t, u
   status_store(status + t, (t == 0 ? kFlagIncl : kFlagAgg) | (agg & kValueMask));
 }
 
+// The 64-bit word of lane i (i wave-uniform).
+__device__ __forceinline__ uint64_t lane_word(uint64_t w, int i) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(w >> 32), i) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)w, i);
+}
+__device__ __forceinline__ uint32_t wave_total_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum_u32(v), 63);
+}
+
 // Called by all 64 lanes of one wave after lookback_publish; returns the same
 // exclusive prefix in every lane.
 template <int R = 4>  // status words per lane per round: a window of 64 R tiles
@@ -450,9 +462,13 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
     uint64_t w[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
+      // every lane loads (word 0 before the first tile, replaced below): a load
+      // in a branch would wait for the one before it
       const int64_t j = base - (k * kWave + lane);
-      w[k] = j >= 0 ? status_load(status + j) : (kFlagIncl | 0ull);
+      w[k] = status_load(status + (j >= 0 ? j : 0));
     }
+#pragma unroll
+    for (int k = 0; k < R; ++k) w[k] = base - (k * kWave + lane) >= 0 ? w[k] : kFlagIncl;
     bool done = false, retry = false;
     int consumed = 0;
 #pragma unroll
@@ -467,12 +483,14 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
         retry = true;
         continue;
       }
-      uint64_t v = lane <= first ? (w[k] & kValueMask) : 0ull;
-      excl += group_sum<kWave, uint64_t>(v);
-      if (first < 64)
+      // the aggregates ahead of the inclusive word, then that word itself
+      excl += wave_total_u32(lane < first ? (uint32_t)w[k] : 0u);
+      if (first < 64) {
+        excl += lane_word(w[k], first) & kValueMask;
         done = true;
-      else
+      } else {
         ++consumed;
+      }
     }
     if (done) break;
     base -= (int64_t)consumed * kWave;
@@ -488,46 +506,85 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
   return excl;
 }
 
-// Prefix sums over tiles kept by one scan wave, for a pass whose tiles are
-// many and in flight all at once: the tiles only publish their aggregates;
-// the scan wave reads them in tile order, 64 R words a round, and publishes
-// every tile's inclusive prefix as soon as all earlier tiles have published,
-// so a tile's own wait is one status word. (A decoupled look-back walks back
-// through every tile still in flight, one window per round and per tile.)
-// The scan wave waits only on tiles that running workgroups hold, and its
-// waits are bounded like the others: on exhaustion err is raised and it
-// stops, and the tiles still waiting give up on their own bounds.
-template <int R>
-__device__ __noinline__ void scan_wave(uint64_t* status, uint64_t ntiles, uint32_t* err, uint32_t err_code) {
+// Prefix sums over tiles kept by one scan workgroup, for a pass whose tiles
+// are many and in flight all at once: the tiles only publish their
+// aggregates; the scan workgroup reads them in tile order, 1024 words a round
+// (256 a wave), and publishes every tile's inclusive prefix as soon as all
+// earlier tiles have published, so a tile's own wait is one status word. (A
+// decoupled look-back walks back through every tile still in flight, one
+// window per round and per tile.) It waits only on tiles that running
+// workgroups hold, and its waits are bounded like the others: on exhaustion
+// err is raised and it stops, and the tiles still waiting give up on their own
+// bounds. A round is one trip to the device's coherence point: the loads go
+// out together (none in a branch, where it would wait for the one before it;
+// past the last tile they read the word behind it, which stays unpublished)
+// and the sums take 32-bit DPP steps. (One wave that read 16 words a lane, each
+// load behind a branch and spilled, and summed 64-bit words by lane shuffles
+// took 6.5 us a round of 1024: the encoder of a 2 GiB float64 field, 65536
+// tiles, ran 421 us and waited on it; with this 331 us.)
+struct ScanShared {
+  uint32_t count[2][kWavesPerWG], sum[2][kWavesPerWG];
+};
+__device__ __forceinline__ void scan_workgroup(uint64_t* status, uint64_t ntiles, uint32_t* err, uint32_t err_code,
+                                               ScanShared& sh) {
+  constexpr int R = 4;
   const int lane = lane_id();
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   uint64_t first = 0, run = 0;
   uint32_t spins = 0;
-  while (first < ntiles) {
+  for (uint32_t par = 0; first < ntiles; par ^= 1) {
+    uint64_t* const base = status + first;
+    const uint32_t left = (uint32_t)(ntiles - first < 4096u ? ntiles - first : 4096u);
+    const uint32_t j0 = wave * (R * kWave) + (uint32_t)lane;
     uint64_t w[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const uint64_t j = first + (uint64_t)(k * kWave + lane);
-      w[k] = j < ntiles ? status_load(status + j) : 0ull;
+      const uint32_t j = j0 + (uint32_t)(k * kWave);
+      w[k] = status_load(base + (j < left ? j : left));
     }
-    uint64_t adv = 0;
-    bool stop = false;
+    // the wave's published words from its window's start, consecutively, and
+    // their prefix sums
+    uint32_t count = 0, sum = 0, incl[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      if (stop) continue;
-      // the published words from the window's start, consecutively
       const uint64_t pub = __ballot((w[k] >> 62) != 0);
-      const int c = pub == ~0ull ? 64 : (int)__ffsll((long long)~pub) - 1;
-      const uint64_t v = lane < c ? (w[k] & kValueMask) : 0ull;
-      const uint64_t incl = run + group_incl_sum<kWave, uint64_t>(v);
-      if (lane < c) status_store(status + first + adv + lane, kFlagIncl | (incl & kValueMask));
-      run = __shfl(incl, 63);
-      adv += (uint64_t)c;
-      stop = c < 64;
+      const uint32_t c = pub == ~0ull ? 64u : (uint32_t)__ffsll((long long)~pub) - 1u;
+      incl[k] = sum + wave_incl_sum_u32((uint32_t)w[k]);
+      if (count == (uint32_t)(k * kWave) && c > 0) {
+        sum = (uint32_t)__builtin_amdgcn_readlane((int)incl[k], (int)c - 1);
+        count += c;
+      }
     }
+    if (lane == 0) {
+      sh.count[par][wave] = count;
+      sh.sum[par][wave] = sum;
+    }
+    __syncthreads();  // one a round: the next round writes the other half
+    uint32_t adv = 0, before = 0, total = 0;
+    bool open = true, mine = true;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kWavesPerWG; ++i) {
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.count[par][i]);
+      const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.sum[par][i]);
+      if (i == wave) {
+        mine = open;
+        before = total;
+      }
+      adv += open ? c : 0u;
+      total += open ? v : 0u;
+      open = open && c == R * kWave;
+    }
+    if (mine) {
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+        if ((uint32_t)(k * kWave + lane) < count)
+          status_store(base + (j0 + (uint32_t)(k * kWave)), kFlagIncl | ((run + before + incl[k]) & kValueMask));
+    }
+    run += total;
     first += adv;
     if (adv == 0) {
       if (++spins > kSpinLimit) {
-        if (lane == 0) atomicMax(err, err_code);
+        if (threadIdx.x == 0) atomicMax(err, err_code);
         return;
       }
       __builtin_amdgcn_s_sleep(2);
@@ -537,7 +594,7 @@ __device__ __noinline__ void scan_wave(uint64_t* status, uint64_t ntiles, uint32
   }
 }
 
-// A tile's exclusive prefix once the scan wave has published its inclusive
+// A tile's exclusive prefix once the scan workgroup has published its inclusive
 // one (one lane polls; the value is the inclusive prefix less the tile's own
 // aggregate). Bounded: on exhaustion err is raised and 0 is returned.
 __device__ __forceinline__ uint64_t scan_wait(const uint64_t* status, uint32_t t, uint64_t agg, uint32_t* err,
