@@ -141,7 +141,8 @@ szx::FieldC single_field_c(const szx::Job& j, const void* in, void* out, uint64_
   f.parts = (uint64_t*)(ws + W.parts);
   f.stats = ws + W.stats;
   f.plan = ws + W.plan;
-  f.enc_r0 = (uint64_t*)(ws + W.enc_r0);
+  f.enc_r0 = (uint32_t*)(ws + W.enc_r0);
+  f.enc_list = f.enc_r0 + ft.enc + 1;
   f.cls_status = (uint64_t*)(ws + W.cls_status);
   f.enc_mid = (uint64_t*)(ws + W.enc_mid);
   return f;
@@ -252,15 +253,20 @@ sz_status plan_compress(const sz_cfield* fs, uint32_t n, uint8_t* ws, std::vecto
   }
   P.zero_off = off;
   off = a256(off + 2ull * szx::kTicketClasses * 256);  // tickets
-  std::vector<uint64_t> ctr_off(n), cls_off(n), mid_off(n);
+  std::vector<uint64_t> ctr_off(n), cls_off(n);
+  uint64_t mid_off[2];
   for (uint32_t i = 0; i < n; ++i) {
     const szx::FieldTiles ft = szx::field_tiles(jobs[i].n, jobs[i].nblk, jobs[i].w, block);
     ctr_off[i] = off;
     off = a256(off + 256);
     cls_off[i] = off;
     off = a256(off + (ft.cls + 1) * 8);
-    mid_off[i] = off;
-    off = a256(off + (ft.enc + 1) * 8);
+  }
+  // the encode tiles' status words: one array per element type, the fields'
+  // one after another (and the word behind the last, which stays zero)
+  for (int dt = 0; dt < 2; ++dt) {
+    mid_off[dt] = off;
+    off = a256(off + (P.tiles[4 + dt] + 1) * 8);
   }
   P.zero_end = off;
   std::vector<uint64_t> parts_off(n), stats_off(n), plan_off(n), r0_off(n);
@@ -313,10 +319,10 @@ sz_status plan_compress(const sz_cfield* fs, uint32_t n, uint8_t* ws, std::vecto
     *(uint64_t*)(host->data() + slot_off[i]) = szx::kCleanWord;
     f.stats = ws + stats_off[i];
     f.plan = ws + plan_off[i];
-    f.enc_r0 = (uint64_t*)(ws + r0_off[i]);
+    f.enc_r0 = (uint32_t*)(ws + r0_off[i]);
     f.cls_status = (uint64_t*)(ws + cls_off[i]);
-    f.enc_mid = (uint64_t*)(ws + mid_off[i]);
     const uint32_t dt = j.dtype;
+    f.enc_mid = (uint64_t*)(ws + mid_off[dt]) + be[dt];
     f.base_stats = bc[dt];
     f.base_cls = bl[dt];
     f.base_enc = be[dt];

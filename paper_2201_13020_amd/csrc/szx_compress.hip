@@ -12,7 +12,8 @@
 //               the range slots itself), then mid-range mu and constant test
 //               of every block (Alg. 1), the state bits and the mu section; a
 //               light single-pass prefix count of non-constant blocks gives
-//               each encode tile its first rank. The field's last tile writes
+//               each encode tile its first rank and a single call its list of
+//               tiles to encode. The field's last tile writes
 //               the header (all but the mid-byte total) and the section
 //               padding, and leaves the range slots zero for the next call.
 //   k_encode    per non-constant block: normalise, keep K bits (eq. (4)), shift
@@ -20,11 +21,11 @@
 //               2-bit leading-byte codes and mid bytes. Persistent workgroups
 //               take tiles from interleaved ticket counters (float32 tiles of
 //               all fields, then float64 tiles); each tile's output offset comes
-//               from a single-pass prefix sum over its field's tiles (Sec. V-B),
-//               and while a tile waits for it the next tile's data is loaded.
-//               Bytes are packed in LDS and leave in aligned 16-byte stores.
-//               A single call's last tile, once its offset is known, writes
-//               the mid-byte total and the stream size.
+//               from a single-pass prefix sum over the tiles (Sec. V-B) by
+//               workgroup 0, and while a tile waits for it the next tile is
+//               encoded. Bytes are packed in LDS and leave in aligned 16-byte
+//               stores. In a single call workgroup 0 ends the stream: the
+//               mid-byte total and the stream size.
 //   k_finalize  batches: every field's mid-byte total and stream size, and
 //               the header of fields without values (a single call only
 //               runs it when its field has no values)
@@ -36,7 +37,7 @@
 namespace szx {
 
 // The stream size while a compression runs (the classification pass sets
-// it, the field's last encode tile replaces it).
+// it, the end of the encode pass replaces it).
 constexpr uint64_t kSizePending = ~0ull;
 
 // Field of a call, or of a batch entry, as the kernels see it (a copy with
@@ -46,7 +47,15 @@ constexpr uint64_t kSizePending = ~0ull;
 enum : int { kAnyCall = -1, kSingle = 0, kBatch = 1 };
 template <int BATCH = kAnyCall>
 __device__ __forceinline__ FieldC field_at(const CBatch& b, uint32_t fi) {
-  FieldC f = BATCH == kSingle ? b.one : BATCH == kBatch ? b.fields[fi] : (b.fields ? b.fields[fi] : b.one);
+  // (the table is only read while a batch runs: read as constant memory, it
+  // comes with scalar loads also where the kernel stores in between)
+  FieldC f;
+  if constexpr (BATCH == kSingle)
+    f = b.one;
+  else if (BATCH == kBatch || b.fields)
+    f = *as_constant(b.fields + fi);
+  else
+    f = b.one;
   f.in = as_global(f.in);
   f.out = as_global(f.out);
   f.out_size = as_global(f.out_size);
@@ -58,13 +67,15 @@ __device__ __forceinline__ FieldC field_at(const CBatch& b, uint32_t fi) {
   f.stats = as_global(f.stats);
   f.plan = as_global(f.plan);
   f.enc_r0 = as_global(f.enc_r0);
+  f.enc_list = as_global(f.enc_list);
   f.cls_status = as_global(f.cls_status);
   f.enc_mid = as_global(f.enc_mid);
   return f;
 }
 template <int BATCH = kAnyCall>
 __device__ __forceinline__ uint32_t field_of(const uint32_t* map, uint64_t t) {
-  return BATCH == kSingle ? 0u : BATCH == kBatch ? map[t] : (map ? map[t] : 0u);
+  if (BATCH == kSingle || (BATCH == kAnyCall && !map)) return 0u;
+  return *as_constant(map + t);
 }
 
 // Load EPL consecutive values starting at element i0 (aligned to EPL); values
@@ -137,6 +148,31 @@ __device__ __forceinline__ U group_scan_last(U v) {
     return MAX ? group_max<G, U>(v) : group_min<G, U>(v);
   }
 }
+
+// Geometry of the encode pass: a workgroup's tile is about 32 KiB of values,
+// each of its four waves a contiguous quarter of it, in SUB rows of EPL
+// consecutive values a lane (whole blocks a row). Sixteen float32 values a
+// lane share the per-row work (ranks, prefix sums, K and code writes) among
+// twice the values of eight; sixteen doubles would not fit the registers.
+template <typename T, int B>
+struct EncGeo {
+  static constexpr int EPL = (int)enc_epl(B, sizeof(T));
+  static constexpr int LPB = B / EPL;       // lanes per block
+  static constexpr int GPW = kWave / LPB;   // blocks per row
+  static constexpr int ROW = kWave * EPL;   // values per row
+  static constexpr int TBLK = (int)enc_blocks(B, sizeof(T));
+  static constexpr int WBLK = TBLK / kWavesPerWG;  // blocks per wave
+  static constexpr int SUB = WBLK / GPW;    // rows per wave
+  // the wave's LDS ring holds its worst case (every value stored whole); the
+  // slack behind it, the run of the lane that crosses the ring's end
+  static constexpr uint32_t RING = (uint32_t)(ROW * SUB * (int)sizeof(T));
+  static constexpr uint32_t SLACK = (uint32_t)(EPL * (int)sizeof(T)) + 16u;
+  static_assert(LPB >= 1 && LPB <= 64 && GPW * LPB == kWave && SUB * GPW * kWavesPerWG == TBLK, "whole rows");
+  static_assert((RING & (RING - 1)) == 0, "the ring wraps by masking");
+  // waves per SIMD, as the rings fit the 160 KiB of LDS: four workgroups of 32
+  // KiB, or two of the 64 KiB of 1024-double blocks
+  static constexpr int WAVES = RING > 8192u ? 2 : 4;
+};
 
 // ----------------------------------------------------------------- stats ---
 
@@ -458,15 +494,22 @@ __device__ __forceinline__ uint64_t write_stream_header(const FieldC& f, uint64_
   return s.total;
 }
 
-// The end of a field's stream, by its last encode tile once that tile's
-// offset is known: the mid-byte total (the header's last field) and the
-// stream size, or 0 there if a bounded wait of this compression gave up.
-// (Every tile's wait ends once all tiles before it have published, which the
-// last tile's own wait has seen, so no wait can give up after this.)
-__device__ __forceinline__ void finish_stream(const FieldC& f, uint64_t mid_off, uint64_t mid_total) {
+// The end of a field's stream, once every tile of it has published its size:
+// the mid-byte total (the header's last field) and the stream size, or 0
+// there if a bounded wait of this compression gave up. (A wait that gives up
+// meanwhile raises the error first and then clears the size itself; the error
+// is read once more after the size is stored, so one of the two sees the
+// other.)
+__device__ __forceinline__ void finish_stream(const FieldC& f, uint64_t mid_total) {
+  const uint64_t mid_off = sections(f.nblk, f.ctr->n_nc, f.dtype == 0 ? 4 : 8, f.b, 0).mid;
   reinterpret_cast<uint64_t*>(f.out)[11] = mid_total;
-  const uint32_t err = __hip_atomic_load(&f.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  *f.out_size = err ? 0 : mid_off + mid_total;
+  const uint64_t size = mid_off + mid_total;
+  if (__hip_atomic_load(&f.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+    __hip_atomic_store(f.out_size, size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
+    if (__hip_atomic_load(&f.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+  }
+  __hip_atomic_store(f.out_size, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // -------------------------------------------------------------- classify ---
@@ -478,14 +521,13 @@ template <typename T, int B>
 __device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint32_t* s_scan, uint32_t* s_state,
                                               uint64_t* s_base, uint64_t* s_red) {
   using U = typename Traits<T>::U;
-  using G = Geo<T, B>;
-  constexpr int TBLK = G::TBLK;
-  constexpr int CLS = TBLK > (int)kClsMin ? TBLK : (int)kClsMin;
+  constexpr int TBLK = EncGeo<T, B>::TBLK;
+  constexpr int CLS = (int)kClsBlocks;
   constexpr int BPT = CLS / kWG;  // blocks per thread
   const U* stats = reinterpret_cast<const U*>(f.stats);
   const uint64_t nblk = f.nblk;
   const uint64_t k0 = (uint64_t)t * CLS + (uint64_t)threadIdx.x * BPT;
-  static_assert(BPT == 4, "four blocks per thread");
+  static_assert(BPT == 4 && TBLK % BPT == 0 && CLS % TBLK == 0, "a thread's four blocks lie in one encode tile");
   // a thread's blocks are consecutive and start 16-byte aligned in the
   // extrema, mu and plan arrays, so a full group moves as 16-byte words. The
   // extrema come through a buffer resource over the tile's blocks (reads
@@ -556,11 +598,29 @@ __device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint3
     }
   }
   if (bits) atomicOr(&s_state[(threadIdx.x * BPT) / 32], bits << ((threadIdx.x * BPT) % 32));
-  uint32_t total;
-  const uint32_t ex = wg_excl_sum<uint32_t>(cnt, s_scan, total);  // has barriers
+  __syncthreads();
+  // whether an encode tile that starts in this thread's blocks has a
+  // non-constant one
+  const bool starts = (k0 % TBLK) == 0 && k0 < nblk;
+  uint32_t used = 0;
+  if (starts) {
+    const uint32_t b0 = threadIdx.x * BPT;
+    if constexpr (TBLK >= 32) {
+#pragma unroll
+      for (int i = 0; i < TBLK / 32; ++i) used |= s_state[b0 / 32 + i];
+    } else {
+      used = (s_state[b0 / 32] >> (b0 % 32)) & ((1u << (TBLK % 32)) - 1u);
+    }
+    used = used ? 1u : 0u;
+  }
+  const uint32_t v2[2] = {cnt, used};
+  uint32_t ex2[2], tot2[2];
+  wg_excl_scan_multi<2>(v2, ex2, tot2, s_scan);  // has barriers
+  const uint32_t total = tot2[0], ex = ex2[0];
   if (threadIdx.x < kWave) {
-    if (threadIdx.x == 0) lookback_publish(f.cls_status, t, total);
-    const uint64_t p = lookback_resolve_n(f.cls_status, t, total, &f.ctr->err, 1u, ntiles);
+    const uint64_t agg = pair_aggregate(total, tot2[1]);
+    if (threadIdx.x == 0) lookback_publish<true>(f.cls_status, t, agg);
+    const uint64_t p = lookback_resolve_n<true>(f.cls_status, t, agg, &f.ctr->err, 1u, ntiles);
     if (threadIdx.x == 0) *s_base = p;
   }
   // state bytes of this tile, never past the state section
@@ -570,16 +630,29 @@ __device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint3
     if (byte < state_bytes) f.out[96 + byte] = (uint8_t)(s_state[i / 4] >> (8 * (i % 4)));
   }
   __syncthreads();
-  const uint64_t base = *s_base;
-  // first rank of every encode tile that starts in this thread's blocks
-  if ((k0 % TBLK) == 0 && k0 < nblk) f.enc_r0[k0 / TBLK] = base + ex;
+  const uint32_t base = (uint32_t)*s_base, tbase = (uint32_t)(*s_base >> 32);
+  // first rank of every encode tile that starts in this thread's blocks, and
+  // (a single call) its place in the list of tiles to encode, or its size, 0
+  if (starts) {
+    const uint32_t et = (uint32_t)(k0 / TBLK);
+    f.enc_r0[et] = base + ex;
+    if (f.enc_list) {
+      if (used)
+        f.enc_list[tbase + (ex2[1] - total)] = et;
+      else
+        status_store(f.enc_mid + et, et == 0 ? kFlagIncl : kFlagAgg);
+    }
+  }
   if (t == ntiles - 1) {
     // Every tile has published, so every tile has read the range slots: the
     // last one clears them for the next call and marks them clean; it also
     // writes the header (the encode pass adds the mid-byte total) and the
     // padding between the sections.
-    const uint64_t n_nc = base + total;
-    if (threadIdx.x == 0) f.ctr->n_nc = n_nc;
+    const uint64_t n_nc = (uint64_t)base + total;
+    if (threadIdx.x == 0) {
+      f.ctr->n_nc = n_nc;
+      f.ctr->n_tiles = tbase + tot2[1];
+    }
     if (threadIdx.x < kRangeSlots)
       *reinterpret_cast<ulonglong2*>(f.range + threadIdx.x * (kRangeStride / 8)) = make_ulonglong2(0, 0);
     if (threadIdx.x == 0) *f.clean = kCleanWord;
@@ -589,9 +662,8 @@ __device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint3
 
 template <typename T, int B>
 __global__ __launch_bounds__(256) void k_classify(CBatch b) {
-  constexpr int CLS = Geo<T, B>::TBLK > (int)kClsMin ? Geo<T, B>::TBLK : (int)kClsMin;
-  __shared__ uint32_t s_scan[kWavesPerWG];
-  __shared__ uint32_t s_state[CLS / 32 > 32 ? CLS / 32 : 32];
+  __shared__ uint32_t s_scan[2 * kWavesPerWG];
+  __shared__ uint32_t s_state[kClsBlocks / 32];
   __shared__ uint64_t s_base;
   __shared__ uint64_t s_red[2 * kWavesPerWG];
   const uint64_t g = blockIdx.x;
@@ -601,633 +673,661 @@ __global__ __launch_bounds__(256) void k_classify(CBatch b) {
 
 // ---------------------------------------------------------------- encode ---
 
-// Truncate v = x - mu to K leading bits, shifted right by s into nb whole
-// bytes; when verify is set, check that every valid value reconstructs within
-// e exactly. Returns false if some value fails.
+// A wave-uniform value held in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
+
+// Whether every valid value of a lane's run reconstructs within e exactly
+// when K leading bits of x - mu are kept.
 template <typename T, int EPL>
-__device__ __forceinline__ bool encode_try(const T (&x)[EPL], int cnt, T mu, T e, int K, bool verify,
-                                           typename Traits<T>::U (&q)[EPL]) {
+__device__ __forceinline__ bool run_within(const T (&x)[EPL], int cnt, T mu, T e, int K) {
   using U = typename Traits<T>::U;
   const int s = shift_of(K);
-  const U keep = top_bytes_mask<U>(bytes_of(K));
-#pragma unroll
-  for (int i = 0; i < EPL; ++i) q[i] = (U)(bits_of(x[i] - mu) >> s) & keep;
+  const U keep = (U)(top_bytes_mask<U>(bytes_of(K)) << s);
   bool ok = true;
-  if (verify) {  // one branch per row, none per value
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const T xr = mu + from_bits<T>((U)(q[i] << s));
-      // bitwise on purpose: both checks, no short-circuit branch
-      const bool good = (bool)((int)exact_le<T>(x[i], xr, e) & (int)exact_le<T>(xr, x[i], e));
-      ok = (bool)((int)ok & ((int)good | (int)(i >= cnt)));
-      // one value at a time: interleaving all of them costs registers, and
-      // this path is rare
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  for (int i = 0; i < EPL; ++i) {
+    const T xr = mu + from_bits<T>((U)(bits_of(x[i] - mu) & keep));
+    // bitwise on purpose: both checks, no short-circuit branch
+    const bool good = (bool)((int)exact_le<T>(x[i], xr, e) & (int)exact_le<T>(xr, x[i], e));
+    ok = (bool)((int)ok & ((int)good | (int)(i >= cnt)));
+    // one value at a time: interleaving all of them costs registers, and
+    // this path is rare
+    __builtin_amdgcn_sched_barrier(0);
   }
   return ok;
 }
 
-// Appends byte strings to a lane's run of the LDS byte stream, a ring of
-// bmask + 1 bytes. The ring is zeroed beforehand and every full dword is
-// OR-ed in (the first and last may be shared with the neighbouring lanes), so
-// the only per-value branch is the predicated store itself.
-struct LanePacker {
-  uint8_t* stage;
-  uint32_t da;     // ring byte of the dword being filled (a multiple of 4)
-  uint32_t lo, hi; // pending bytes, the next byte of the stream in the low byte of lo
-  uint32_t fill;   // pending bits (< 32)
-  uint32_t bmask;  // ring bytes - 1 (a power of two less one)
-  __device__ __forceinline__ LanePacker(uint32_t* st, uint32_t off, uint32_t bm)
-      : stage(reinterpret_cast<uint8_t*>(st)), da(off & ~3u & bm), lo(0), hi(0), fill((off & 3u) * 8u), bmask(bm) {}
-  // L <= 4 bytes of sv, first byte in the low byte, bytes above L zero
-  __device__ __forceinline__ void put4(uint32_t sv, int L) {
-    const uint64_t sh = (uint64_t)sv << fill;
-    lo |= (uint32_t)sh;
-    hi |= (uint32_t)(sh >> 32);
-    const uint32_t nf = fill + 8u * (uint32_t)L;  // < 64
-    fill = nf & 31u;
-    if (nf > 31u) {
-      atomicOr(reinterpret_cast<uint32_t*>(stage + da), lo);
-      da = (da + 4u) & bmask;
-      lo = hi;
-      hi = 0;
-    }
+// The high 32 bits of a value's shifted word (the bytes that leading-byte
+// codes look at), and its low 32 bits (float64 only).
+__device__ __forceinline__ uint32_t high_word(uint32_t q) { return q; }
+__device__ __forceinline__ uint32_t high_word(uint64_t q) { return (uint32_t)(q >> 32); }
+__device__ __forceinline__ uint32_t low_word(uint32_t) { return 0; }
+__device__ __forceinline__ uint32_t low_word(uint64_t q) { return (uint32_t)q; }
+
+// Byte selectors of the packer for words of which the top nb bytes (nb <= 4)
+// may be stored. Shifted right by c bytes (a value that drops its c leading
+// bytes, c <= min(3, nb)) they give
+//   w: the word's stored bytes, most significant first (v_perm_b32 indices
+//      0-3 of the word), then the bytes of the string behind it (indices 4-7);
+//   x: the bytes 4 - L and on of the eight bytes behind it (L = nb - c).
+// Byte j of both is 4 + j - nb, but for the first nb bytes of w.
+struct PackSel {
+  uint32_t w, x, hi;
+  __device__ __forceinline__ explicit PackSel(uint32_t nb) {
+    const uint32_t nb4 = __builtin_amdgcn_perm(0u, nb, 0u);  // nb in every byte
+    x = 0x07060504u - nb4;
+    hi = 0x0B0A0908u - nb4;
+    const uint32_t rest = (uint32_t)(~0ull << (8u * nb));  // 64-bit: nb = 4 leaves none
+    w = (x & rest) | (0x00010203u & ~rest);
   }
-  __device__ __forceinline__ void put(uint32_t sv, int L) { put4(sv, L); }
-  // L <= 8 bytes of sv at once: the 96-bit window lo, hi, x takes them at
-  // bit `fill`, and up to two full dwords leave
-  __device__ __forceinline__ void put(uint64_t sv, int L) {
-    const uint64_t a = (uint64_t)(uint32_t)sv << fill;
-    const uint64_t b = (sv >> 32) << fill;
-    lo |= (uint32_t)a;
-    hi |= (uint32_t)(a >> 32) | (uint32_t)b;
-    const uint32_t x = (uint32_t)(b >> 32);
-    const uint32_t nf = fill + 8u * (uint32_t)L;  // < 96
-    fill = nf & 31u;
-    if (nf > 31u) {
-      atomicOr(reinterpret_cast<uint32_t*>(stage + da), lo);
-      da = (da + 4u) & bmask;
-      lo = hi;
-      hi = x;
-      if (nf > 63u) {
-        atomicOr(reinterpret_cast<uint32_t*>(stage + da), lo);
-        da = (da + 4u) & bmask;
-        lo = hi;
-        hi = 0;
-      }
-    }
+  __device__ __forceinline__ uint32_t w_at(uint32_t c) const { return __builtin_amdgcn_alignbyte(hi, w, c); }
+  __device__ __forceinline__ uint32_t x_at(uint32_t c) const { return __builtin_amdgcn_alignbyte(hi, x, c); }
+};
+
+// The dword at LDS address a (positions in the packer are LDS addresses, so
+// that no base is added per string).
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ lds_u32* lds_at(uint32_t a) { return (lds_u32*)a; }
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+
+// Packs a lane's byte strings, last one first, into its run of an LDS byte
+// stream. w holds the four stream bytes from the current string's start on
+// and x the four after them (zero past the run's end). Putting a string in
+// front is two byte permutes, and the aligned dword at or after its start
+// (its bytes all lie in w and x) is stored as it is then: every dword that
+// starts inside the run is written with its run bytes, most of them more
+// than once and always the same. A dword that starts at or past the run's
+// end may be overwritten with zeros, but only before the last of the run's
+// strings is put (put_first, which does not write there): it is the first
+// aligned dword of a later lane, which that lane's own put_first, the same
+// instruction, restores. What remains are the bytes before the run's first
+// aligned dword, OR-ed into the dword that the lanes before left zero there
+// (or_head). No per-string branch, no dword to clear beforehand, one LDS
+// store a string.
+struct RunPacker {
+  uint32_t m;  // ~(position + 3): its low two bits are the bytes up to the next aligned dword
+  uint32_t w, x;
+  __device__ __forceinline__ explicit RunPacker(uint32_t end) : m(~(end + 3u)), w(0), x(0) {}
+  // L = nb - c <= 4 bytes of the word v
+  __device__ __forceinline__ void prepend(uint32_t v, uint32_t nb, uint32_t c, const PackSel& sel) {
+    m = __builtin_amdgcn_sad_u8(nb, c, m);  // m + nb - c
+    const uint32_t nx = __builtin_amdgcn_perm(x, w, sel.x_at(c));
+    w = __builtin_amdgcn_perm(w, v, sel.w_at(c));
+    x = nx;
   }
-  __device__ __forceinline__ void flush() {
-    if (fill > 0) atomicOr(reinterpret_cast<uint32_t*>(stage + da), lo);
+  __device__ __forceinline__ uint32_t dword_at() const { return ~(m | 3u); }
+  __device__ __forceinline__ void store() { *lds_at(dword_at()) = __builtin_amdgcn_alignbyte(x, w, m); }
+  __device__ __forceinline__ void store_first(uint32_t end) {
+    if (dword_at() < end) store();
+  }
+  __device__ __forceinline__ void or_head(uint32_t start) {
+    __hip_atomic_fetch_or(lds_at(start & ~3u), w << (8u * (start & 3u)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 };
 
-// The bytes of v after its c lowest ones (c in [0, 3]; v's string after
-// dropping c leading bytes when the first byte is the low one).
-__device__ __forceinline__ uint32_t drop_low_bytes(uint32_t v, uint32_t c) {
-  return __builtin_amdgcn_alignbyte(0u, v, c);
-}
-__device__ __forceinline__ uint64_t drop_low_bytes(uint64_t v, uint32_t c) {
-  const uint32_t l = (uint32_t)v, h = (uint32_t)(v >> 32);
-  return ((uint64_t)__builtin_amdgcn_alignbyte(0u, h, c) << 32) | __builtin_amdgcn_alignbyte(h, l, c);
-}
-
-// Copy total staged bytes to out + [dst, dst + total). They start at the
-// 16-byte word at16 of the LDS ring of mask16 + 1 such words (a power of two)
-// and may wrap around its end. Whole aligned 16-byte chunks of the
-// destination go out as single stores, the shared first and last chunks byte
-// by byte. Chunk c of the destination starts at staged byte 16 c - a (a = dst
-// mod 16, the same for every chunk), so its bytes lie in the two staged
-// 16-byte words c - 1 and c (c when a = 0): every lane reads two consecutive
-// 16-byte words (a wave reads a contiguous range: no LDS bank conflicts; five
-// strided dword reads per chunk put 64 lanes on 8 banks) and realigns them
-// with byte funnel shifts by the same amount.
-__device__ __forceinline__ void copy_out(uint8_t* __restrict__ out, uint64_t dst, const uint32_t* stage,
-                                         uint32_t at16, uint32_t mask16, uint32_t total) {
+// Copy the wave's total staged bytes to out + [dst, dst + total). They start
+// at the 16-byte word at16 of its LDS ring of mask16 + 1 such words (a power
+// of two) and may wrap around its end. Whole aligned 16-byte chunks of the
+// destination go out as single stores: a chunk starts h bytes into a staged
+// word (h the bytes before the first whole chunk, the same for every chunk),
+// so every lane reads two consecutive 16-byte words (a wave reads a
+// contiguous range: no LDS bank conflicts) and realigns them with byte funnel
+// shifts by the same amount. The bytes before the first whole chunk and after
+// the last go out one a lane.
+__device__ __forceinline__ void copy_out(uint8_t* __restrict__ out, uint64_t dst, const uint8_t* stage, uint32_t at16,
+                                         uint32_t mask16, uint32_t total) {
   const uint4* ring = reinterpret_cast<const uint4*>(stage);
-  const uint32_t st = (uint32_t)(dst & 15u);
-  uint8_t* base = out + (dst - st);
-  const uint32_t end = st + total;
-  const uint32_t nchunk = (end + 15) / 16;
-  const uint32_t b = (16u - st) & 15u;  // byte of the chunk's start in the first stage word read
-  const uint32_t k = b >> 2, sh = b & 3u;
-  const uint32_t back = st ? 1u : 0u;
   const uint32_t bmask = mask16 * 16u + 15u;
-  for (uint32_t c = threadIdx.x; c < nchunk; c += kWG) {
-    const uint32_t lo = c * 16 < st ? st : c * 16;
-    const uint32_t hi = c * 16 + 16 > end ? end : c * 16 + 16;
-    if (lo == c * 16 && hi == c * 16 + 16) {
-      // c >= 1 here whenever st > 0 (chunk 0 is then partial)
-      const uint4 q0 = ring[(at16 + c - back) & mask16];
-      const uint4 q1 = ring[(at16 + c - back + 1) & mask16];
-      const uint32_t w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-      uint4 u;
-      // k is the same for every lane: a uniform branch picks the words
-      switch (k) {
-        case 0:
-          u = make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], sh), __builtin_amdgcn_alignbyte(w[2], w[1], sh),
-                         __builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh));
-          break;
-        case 1:
-          u = make_uint4(__builtin_amdgcn_alignbyte(w[2], w[1], sh), __builtin_amdgcn_alignbyte(w[3], w[2], sh),
-                         __builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh));
-          break;
-        case 2:
-          u = make_uint4(__builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh),
-                         __builtin_amdgcn_alignbyte(w[5], w[4], sh), __builtin_amdgcn_alignbyte(w[6], w[5], sh));
-          break;
-        default:
-          u = make_uint4(__builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh),
-                         __builtin_amdgcn_alignbyte(w[6], w[5], sh), __builtin_amdgcn_alignbyte(w[7], w[6], sh));
-          break;
-      }
-      *reinterpret_cast<uint4*>(base + c * 16) = u;
-    } else {
-      for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t bi = (at16 * 16u + i - st) & bmask;
-        base[i] = (uint8_t)(stage[bi >> 2] >> ((bi & 3u) * 8u));
-      }
+  const uint32_t l = (uint32_t)lane_id();
+  uint8_t* base = out + dst;
+  uint32_t h = (16u - (uint32_t)(dst & 15u)) & 15u;
+  h = h < total ? h : total;
+  const uint32_t nfull = (total - h) / 16u;
+  {
+    const uint32_t tail0 = h + nfull * 16u;
+    const uint32_t i = l < 16u ? l : tail0 + (l - 16u);
+    const bool on = l < 16u ? l < h : (l < 32u && i < total);
+    if (on) base[i] = stage[(at16 * 16u + i) & bmask];
+  }
+  const uint32_t k = h >> 2, sh = h & 3u;
+  for (uint32_t c = l; c < nfull; c += kWave) {
+    const uint4 q0 = ring[(at16 + c) & mask16];
+    const uint4 q1 = ring[(at16 + c + 1) & mask16];
+    const uint32_t w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+    uint4 u;
+    // k is the same for every lane: a uniform branch picks the words
+    switch (k) {
+      case 0:
+        u = make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], sh), __builtin_amdgcn_alignbyte(w[2], w[1], sh),
+                       __builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh));
+        break;
+      case 1:
+        u = make_uint4(__builtin_amdgcn_alignbyte(w[2], w[1], sh), __builtin_amdgcn_alignbyte(w[3], w[2], sh),
+                       __builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh));
+        break;
+      case 2:
+        u = make_uint4(__builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh),
+                       __builtin_amdgcn_alignbyte(w[5], w[4], sh), __builtin_amdgcn_alignbyte(w[6], w[5], sh));
+        break;
+      default:
+        u = make_uint4(__builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh),
+                       __builtin_amdgcn_alignbyte(w[6], w[5], sh), __builtin_amdgcn_alignbyte(w[7], w[6], sh));
+        break;
     }
+    *reinterpret_cast<uint4*>(base + h + c * 16u) = u;
   }
 }
 
-// Clear the ring's 16-byte words that hold total bytes from word at16 on.
-__device__ __forceinline__ void ring_clear(uint32_t* stage, uint32_t at16, uint32_t mask16, uint32_t total) {
-  uint4* ring = reinterpret_cast<uint4*>(stage);
-  const uint32_t nw = (total + 15) / 16;
-  for (uint32_t i = threadIdx.x; i < nw; i += kWG) ring[(at16 + i) & mask16] = make_uint4(0, 0, 0, 0);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t rs, uint32_t off);
+template <>
+__device__ __forceinline__ float buffer_value<float>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+}
+template <>
+__device__ __forceinline__ double buffer_value<double>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  using v2u = unsigned int __attribute__((ext_vector_type(2)));
+  const v2u u = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+  return __longlong_as_double((long long)(((uint64_t)u.y << 32) | u.x));
 }
 
-// Per-row plan of a tile's blocks as one lane sees them: K (-1 raw, 0
-// constant or no block, else kept bits), whether the values need verifying,
-// how many values the lane holds, and the rank of the row's block among the
-// tile's non-constant ones. For float64 the four are packed into one word
-// per row (K + 1 in bits 0-6, verify in bit 7, the count in bits 8-12, the
-// rank from bit 13): that encoder is at its register cap and spills
-// otherwise; for float32 plain fields measured faster.
-template <typename T, int B, bool PACK = (sizeof(T) == 8)>
-struct RowPlan;
+// The previous lane's value over the whole wave (wave_shr:1; lane 0 gets 0).
+__device__ __forceinline__ uint32_t wave_before(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, false);
+}
 
+// Lanes that begin a group of LPB.
+template <int LPB>
+__device__ __forceinline__ constexpr uint64_t first_lanes() {
+  return LPB == 64   ? 1ull
+         : LPB == 32 ? 0x0000000100000001ull
+         : LPB == 16 ? 0x0001000100010001ull
+         : LPB == 8  ? 0x0101010101010101ull
+         : LPB == 4  ? 0x1111111111111111ull
+         : LPB == 2  ? 0x5555555555555555ull
+                     : ~0ull;
+}
+
+// Plan of a wave's blocks: each row's mu and plan byte (both left by the
+// classification pass), what the rank of the wave's first block is counted
+// from (the tile's plan bytes, or its state bits where the tile has more
+// blocks than a wave lanes), and the rank of the tile's first block.
 template <typename T, int B>
-struct RowPlan<T, B, false> {
-  static constexpr int SUB = Geo<T, B>::SUB;
-  int K_[SUB], cnt_[SUB];
-  bool verify_[SUB];
-  uint32_t rank_[SUB];
-  __device__ __forceinline__ void set(int s, int K, bool verify, int cnt) {
-    K_[s] = K;
-    verify_[s] = verify;
-    cnt_[s] = cnt;
-  }
-  __device__ __forceinline__ void set_rank(int s, uint32_t r) { rank_[s] = r; }
-  __device__ __forceinline__ int K(int s) const { return K_[s]; }
-  __device__ __forceinline__ bool verify(int s) const { return verify_[s]; }
-  __device__ __forceinline__ int cnt(int s) const { return cnt_[s]; }
-  __device__ __forceinline__ uint32_t rank(int s) const { return rank_[s]; }
+struct WavePlan {
+  T mu[EncGeo<T, B>::SUB];
+  uint32_t pb[EncGeo<T, B>::SUB];
+  uint32_t ahead;
+  uint32_t r0;
 };
 
+// Through buffer resources over the tile's entries: reads past the field's
+// last block return zeros (a constant block, which stores nothing), so no
+// load sits in a branch and the compiler can count the loads in flight.
+// on = false loads nothing (every plan byte 0).
 template <typename T, int B>
-struct RowPlan<T, B, true> {
-  static constexpr int SUB = Geo<T, B>::SUB;
-  static_assert(Geo<T, B>::EPL <= 31 && Geo<T, B>::TBLK <= (1 << 19), "packed row fields overflow");
-  uint32_t meta[SUB];
-  __device__ __forceinline__ void set(int s, int K, bool verify, int cnt) {
-    meta[s] = (uint32_t)(K + 1) | (verify ? 0x80u : 0u) | ((uint32_t)cnt << 8);
-  }
-  __device__ __forceinline__ void set_rank(int s, uint32_t r) { meta[s] |= r << 13; }
-  __device__ __forceinline__ int K(int s) const { return (int)(meta[s] & 0x7Fu) - 1; }
-  __device__ __forceinline__ bool verify(int s) const { return (meta[s] >> 7) & 1u; }
-  __device__ __forceinline__ int cnt(int s) const { return (int)((meta[s] >> 8) & 31u); }
-  __device__ __forceinline__ uint32_t rank(int s) const { return meta[s] >> 13; }
-};
-
-// What a workgroup holds of one tile between its loads and its encoding.
-template <typename T, int B>
-struct TileIn {
-  T x[Geo<T, B>::SUB][Geo<T, B>::EPL];
-  T mu[Geo<T, B>::SUB];
-  RowPlan<T, B> row;
-  uint64_t r0;                    // rank of the tile's first non-constant block
-  uint32_t field;                 // batch entry
-  uint32_t tile;                  // tile within the field
-  T e;                            // the field's bound and non-constant block count,
-  uint64_t n_nc;                  // read with the tile so their latency hides too
-};
-
-// Loads tile t: each block's mu (from the stream) and plan byte (both left
-// by the classification pass), ranks within the tile (barriers), and the
-// values of its non-constant blocks (left in flight).
-template <typename T, int B>
-__device__ __forceinline__ void tile_load(TileIn<T, B>& in, uint32_t t, const T* __restrict__ x,
-                                          const T* __restrict__ mus, const uint8_t* __restrict__ plan,
-                                          const uint64_t* __restrict__ enc_r0, uint64_t n, uint64_t nblk,
-                                          uint32_t* s_scan) {
-  using G = Geo<T, B>;
-  constexpr int EPL = G::EPL, LPB = G::LPB, TB = G::TB, SUB = G::SUB, TBLK = G::TBLK;
-  const int g = threadIdx.x / LPB, lig = threadIdx.x % LPB;
-  in.r0 = enc_r0[t];
-  uint32_t first[SUB];
-  if constexpr (sizeof(T) == 4) {
-    // the tile's first block and value (wave-uniform), its block and value
-    // counts; lanes index from them with 32-bit offsets. (For float64 the
-    // same form measured slower: it left the encoder spilling registers.)
-    const uint64_t kb = (uint64_t)t * TBLK;
-    const uint32_t nblk_t = (uint32_t)std::min<uint64_t>(nblk - kb, (uint64_t)TBLK);
-    const uint32_t nval_t = (uint32_t)std::min<uint64_t>(n - kb * B, (uint64_t)TBLK * B);
-    const T* x_t = x + kb * B;
-    const T* mus_t = mus + kb;
-    const uint8_t* plan_t = plan + kb;
-    // every row's mu and plan byte first, then the values: vector loads
-    // return in order, so a row's plan byte read after the previous row's
-    // values would wait for them (one memory latency per row)
-    uint32_t pbs[SUB];
+__device__ __forceinline__ void plan_load(WavePlan<T, B>& p, const FieldC* f, uint32_t t, uint32_t wave, bool on) {
+  using G = EncGeo<T, B>;
+  constexpr int SUB = G::SUB, TBLK = G::TBLK;
+  const uint32_t lane = (uint32_t)lane_id(), g = lane / G::LPB;
+  // the tile's first block (wave-uniform) and its block count
+  const uint64_t kb = on ? (uint64_t)t * TBLK : 0;
+  const uint32_t nblk_t = on ? (uint32_t)std::min<uint64_t>(f->nblk - kb, (uint64_t)TBLK) : 0u;
+  const __amdgpu_buffer_rsrc_t rm =
+      buffer_of(reinterpret_cast<const T*>(f->out + f->mu_off) + kb, nblk_t * (uint32_t)sizeof(T));
+  const __amdgpu_buffer_rsrc_t rp = buffer_of(f->plan + kb, nblk_t);
 #pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      const uint32_t lk = (uint32_t)(s * TB + g);
-      in.mu[s] = (T)0;
-      pbs[s] = 0;
-      if (lk < nblk_t) {
-        in.mu[s] = mus_t[lk];
-        pbs[s] = plan_t[lk];
-      }
-    }
-    // The values through a buffer resource over the tile's values (to the
-    // field's end): reads past its range return zeros without touching
-    // memory, so lanes of constant blocks (sent far past it) and a short
-    // block's run past the field's end need no branch. With one load form
-    // for every lane no lane's loads wait on another's (two forms writing
-    // the same registers made every row wait for all loads before it).
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x_t), (short)0, (int)(nval_t * sizeof(T)), 0x00020000);
-    using v4u = unsigned int __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      const uint32_t lk = (uint32_t)(s * TB + g);
-      const bool inb = lk < nblk_t;
-      const uint32_t pb = pbs[s];
-      const int K = pb == 0xFFu ? -1 : (int)(pb & 0x7Fu);
-      // values from this lane's first one to the tile's end (constant blocks load none)
-      const int rem = (int)nval_t - (int)(lk * B) - lig * EPL;
-      const int cnt = (inb && K != 0) ? (rem < 0 ? 0 : (rem > EPL ? EPL : rem)) : 0;
-      in.row.set(s, K, (pb & 0x80u) != 0 && pb != 0xFFu, cnt);
-      const uint32_t off = cnt > 0 ? (lk * B + (uint32_t)(lig * EPL)) * 4u : 0x40000000u;
-#pragma unroll
-      for (int c = 0; c < EPL / 4; ++c) {
-        const v4u u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 16u * (uint32_t)c), 0, 0);
-        in.x[s][4 * c + 0] = __uint_as_float(u.x);
-        in.x[s][4 * c + 1] = __uint_as_float(u.y);
-        in.x[s][4 * c + 2] = __uint_as_float(u.z);
-        in.x[s][4 * c + 3] = __uint_as_float(u.w);
-      }
-      first[s] = (lig == 0 && K != 0) ? 1u : 0u;
-    }
+  for (int s = 0; s < SUB; ++s)
+    p.pb[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rp, (int)(wave * G::WBLK + (uint32_t)(s * G::GPW) + g), 0, 0);
+  if constexpr (TBLK <= kWave) {
+    p.ahead = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rp, (int)lane, 0, 0);
   } else {
-    uint32_t pbs[SUB];  // as above: every row's plan byte before any value
-#pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      const uint64_t k = (uint64_t)t * TBLK + (uint64_t)s * TB + g;
-      in.mu[s] = (T)0;
-      pbs[s] = 0;
-      if (k < nblk) {
-        in.mu[s] = mus[k];
-        pbs[s] = plan[k];
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      const uint64_t k = (uint64_t)t * TBLK + (uint64_t)s * TB + g;
-      const uint32_t pb = pbs[s];
-      const int K = pb == 0xFFu ? -1 : (int)(pb & 0x7Fu);
-      const uint64_t nk = (k < nblk && K != 0) ? std::min<uint64_t>((uint64_t)B, n - k * B) : 0;
-      const int cnt = (int)((uint64_t)lig * EPL >= nk ? 0 : std::min<uint64_t>(EPL, nk - (uint64_t)lig * EPL));
-      in.row.set(s, K, (pb & 0x80u) != 0 && pb != 0xFFu, cnt);
-      load_run<T, EPL>(x, k * B + (uint64_t)lig * EPL, k * B + nk, in.x[s]);
-      first[s] = (lig == 0 && K != 0) ? 1u : 0u;
-    }
+    // whole words of state bits: bits past the field's last block are never
+    // counted (a word past the section's end reads its padding or mu)
+    static_assert(TBLK <= 32 * kWave && TBLK % 32 == 0, "a wave covers the tile's state words");
+    const __amdgpu_buffer_rsrc_t rb = buffer_of(f->out + 96 + kb / 8, (nblk_t + 31) / 32 * 4);
+    p.ahead = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(lane * 4u), 0, 0);
   }
-  uint32_t tot[SUB], rank[SUB];
-  wg_excl_scan_multi<SUB>(first, rank, tot, s_scan);
-  // the group's first lane counted its block; the others see it counted
 #pragma unroll
-  for (int s = 0; s < SUB; ++s) in.row.set_rank(s, rank[s] - ((lig != 0 && in.row.K(s) != 0) ? 1u : 0u));
+  for (int s = 0; s < SUB; ++s)
+    p.mu[s] = buffer_value<T>(rm, (wave * G::WBLK + (uint32_t)(s * G::GPW) + g) * (uint32_t)sizeof(T));
+  p.r0 = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(buffer_of(f->enc_r0 + (on ? t : 0u), 4u), 0, 0, 0);
 }
 
-// Bytes of the encoder's LDS ring: the least power of two that holds a
-// tile's worst case (every value stored whole).
+// Non-constant blocks of the tile before the wave's first one.
 template <typename T, int B>
-constexpr uint32_t enc_ring_bytes() {
-  constexpr uint32_t worst = (uint32_t)(Geo<T, B>::TILE * Geo<T, B>::SUB * (int)sizeof(T));
-  uint32_t r = 16;
-  while (r < worst) r *= 2;
-  return r;
+__device__ __forceinline__ uint32_t rank_ahead(uint32_t ahead, uint32_t wave) {
+  using G = EncGeo<T, B>;
+  if constexpr (G::TBLK <= kWave) {
+    return (uint32_t)__popcll(__ballot(ahead != 0) & ((1ull << (wave * G::WBLK)) - 1ull));
+  } else {
+    const int left = (int)(wave * G::WBLK) - lane_id() * 32;
+    const uint32_t mask = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
+    return wave_total_u32((uint32_t)__popc(ahead & mask));
+  }
 }
+
+// The descriptor of a field as constant memory behind an address that the
+// compiler cannot see through, so that each use reads the members it needs
+// again with scalar loads: kept in scalar registers over the tile loop they
+// spill to vector lanes, a vector instruction each way.
+template <int BATCH>
+__device__ __forceinline__ const FieldC* field_ref(const CBatch& b, uint32_t fi) {
+  uint64_t p = BATCH == kSingle
+                   ? (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + __builtin_offsetof(CBatch, one)
+                   : (uint64_t)(uintptr_t)(b.fields + fi);
+  p = uniform(p);
+  asm volatile("" : "+s"(p));
+  return as_constant(reinterpret_cast<const FieldC*>((uintptr_t)p));
+}
+
+// Row s of the wave's values (left in flight), through a buffer resource over
+// the tile's values (to the field's end): reads past its range return zeros
+// without touching memory, so lanes of constant blocks (sent far past it) and
+// a short block's run past the field's end need no branch.
+template <typename T, int B, int EPL>
+__device__ __forceinline__ void row_load(T (&x)[EPL], __amdgpu_buffer_rsrc_t rs, uint32_t wave, int s, uint32_t pb) {
+  using G = EncGeo<T, B>;
+  constexpr int PER16 = 16 / (int)sizeof(T);
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t lk = wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / G::LPB;
+  const uint32_t off = pb != 0 ? (lk * B + (lane % G::LPB) * EPL) * (uint32_t)sizeof(T) : 0x40000000u;
+  using v4u = unsigned int __attribute__((ext_vector_type(4)));
+#pragma unroll
+  for (int c = 0; c < EPL / PER16; ++c) {
+    const v4u u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 16u * (uint32_t)c), 0, 0);
+    if constexpr (sizeof(T) == 4) {
+      x[4 * c + 0] = __uint_as_float(u.x);
+      x[4 * c + 1] = __uint_as_float(u.y);
+      x[4 * c + 2] = __uint_as_float(u.z);
+      x[4 * c + 3] = __uint_as_float(u.w);
+    } else {
+      x[2 * c + 0] = __longlong_as_double((long long)(((uint64_t)u.y << 32) | u.x));
+      x[2 * c + 1] = __longlong_as_double((long long)(((uint64_t)u.w << 32) | u.z));
+    }
+  }
+}
+
+// Buffer resource over the values of tile t of a field.
+template <typename T, int B>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t values_of(const FieldC* f, uint32_t t) {
+  const uint64_t i0 = (uint64_t)t * EncGeo<T, B>::TBLK * B;
+  return buffer_of(reinterpret_cast<const T*>(f->in) + i0,
+                   (uint32_t)std::min<uint64_t>(f->n - i0, (uint64_t)EncGeo<T, B>::TBLK * B) * (uint32_t)sizeof(T));
+}
+
+// What the workgroup's waves share.
+struct EncShared {
+  uint32_t tot[2][kWavesPerWG];  // a tile's bytes by wave, by the tile's parity
+  uint32_t next[2];              // the tile after the next one
+};
 
 // The encode pass for the tiles of element type T: persistent workgroups take
 // tickets from the kTicketClasses counters of this type; ticket i of class c
 // is global tile kTicketClasses * i + c, global tiles running over the fields
-// of this type in order.
+// of this type in order. A single call's tickets run over the list of tiles
+// with a non-constant block that the classification pass made (it published
+// the other tiles' sizes, zero). A launch with a workgroup for every tile
+// takes no tickets: workgroups are dispatched in order, so a tile waits only
+// on running or finished ones all the same.
 //
-// A workgroup stages each tile's mid bytes in an LDS ring (a power of two of
-// at least one tile's worst case) and leaves it there, pending, while it
-// encodes its next tile behind it; only then does it resolve the pending
-// tile's offset in the mid section and copy it out. By then the tiles before
-// it have long published their sizes, so the look-back finds them without
-// waiting, and its latency overlaps the next tile's loads. When a tile's
-// bytes would reach the pending tile's, the pending one is written out first
-// (incompressible tiles: no overlap, as with one stage).
+// Each wave encodes a contiguous quarter of its workgroup's tile by itself:
+// its rows' prefix sums, ranks and packing stay in the wave, and its mid bytes
+// go to an LDS ring of its own. The waves meet at one barrier a tile, where
+// their byte counts add up and the next ticket is handed out; then thread 0
+// publishes the tile's count. A wave leaves a tile's bytes in its ring,
+// pending, while it encodes its quarter of the next tile behind them; only
+// then does it take the pending tile's offset in the mid section, which the
+// scan workgroup has published by then, and copy its bytes out. When a row
+// would reach the pending bytes, they are written out first (incompressible
+// tiles: no overlap).
+//
+// Bound: the values' reads and the stream's writes (100x500x500 float32 at
+// REL 1e-3, 100 MB in and 41 MB out, take 27 us at the copy rate of 5.2 TB/s)
+// and, about as long, 18 vector instructions a value plus 250 a tile. Measured
+// there 36 us a launch, and 233 us on 2^28 float64 values at REL 1e-3 (43 and
+// 421 us with a barrier for every row's sums, LDS atomics for every packed
+// dword and tickets for constant tiles); a batch of 256 float32 fields, 175 us
+// (239). Smaller workgroups without the pending tile, eight a compute unit,
+// took 51 us: every tile then waits 4-5 us for its offset.
 template <typename T, int B, int BATCH>
-__device__ __forceinline__ void encode_pass(const CBatch& b, uint32_t* s_scan, uint32_t* s_tile, uint64_t* s_base,
-                                            uint64_t* s_end, uint32_t* s_stage, ScanShared* s_sums) {
+__device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint8_t* s_ring) {
   using U = typename Traits<T>::U;
-  using G = Geo<T, B>;
+  using G = EncGeo<T, B>;
   constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB;
   constexpr int BYTES = Traits<T>::BYTES;
-  constexpr uint32_t RING = enc_ring_bytes<T, B>();
+  constexpr uint32_t RING = G::RING;
   constexpr uint32_t MASK16 = RING / 16 - 1;
   constexpr int DT = sizeof(T) == 4 ? 0 : 1;
-  const uint64_t ntiles = b.tiles_enc[DT];
-  if (ntiles == 0) return;
-  // A single call's workgroup 0 is the scan workgroup of the tiles' mid-byte
-  // offsets (the others wait on one status word each); a batch's tiles, of
-  // many fields, resolve their offsets by look-back.
-  if constexpr (BATCH == kSingle) {
-    if (blockIdx.x == 0) {
-      const FieldC f = field_at<BATCH>(b, 0);
-      scan_workgroup(f.enc_mid, ntiles, &f.ctr->err, 1u, *s_sums);
-      return;
-    }
-  }
-  const uint32_t wid = BATCH == kSingle ? blockIdx.x - 1 : blockIdx.x;
+  const uint32_t wid = blockIdx.x - 1;
   const uint32_t cls = wid % kTicketClasses;
+  const bool direct = gridDim.x > b.tiles_enc[DT];  // a workgroup for every tile
+  const FieldC* const one = BATCH == kSingle ? field_ref<BATCH>(b, 0) : nullptr;
+  const uint64_t ntiles = BATCH == kSingle ? as_constant(one->ctr)->n_tiles : b.tiles_enc[DT];
+  const uint32_t* const list = BATCH == kSingle ? as_global(one->enc_list) : nullptr;
   uint32_t* ticket = b.tickets + (DT * kTicketClasses + cls) * 64;
-  const int lig = threadIdx.x % LPB;
+  const uint32_t wave = uniform(threadIdx.x / kWave);
+  const uint32_t lane = (uint32_t)lane_id(), lig = lane % LPB;
+  uint8_t* const stage = s_ring + wave * (RING + G::SLACK);
+  const uint32_t ring0 = uniform(lds_address(stage));
 
-  auto claim = [&]() -> uint64_t {
-    if (threadIdx.x == 0) *s_tile = atomicAdd(ticket, 1u);
-    __syncthreads();
-    const uint64_t v = (uint64_t)*s_tile * kTicketClasses + cls;
-    __syncthreads();
-    return v;
+  // A claimed tile travels as its global number (a single call's, as the list
+  // has it), or ntiles (past every tile) when there is none left.
+  auto number = [&](uint32_t tk) -> uint64_t { return (uint64_t)tk * kTicketClasses + cls; };
+  auto listed = [&](uint64_t g) -> uint32_t {
+    if (g >= ntiles) return ~0u;
+    return BATCH == kSingle ? list[g] : (uint32_t)g;
   };
-  auto load = [&](TileIn<T, B>& in, uint64_t gt) {
-    const uint32_t fi = field_of<BATCH>(b.field_enc[DT], gt);
-    const FieldC f = field_at<BATCH>(b, fi);
-    in.field = fi;
-    in.tile = (uint32_t)(gt - f.base_enc);
-    in.e = from_bits<T>((U)f.ctr->e_bits);
-    in.n_nc = f.ctr->n_nc;
-    tile_load<T, B>(in, in.tile, reinterpret_cast<const T*>(f.in), reinterpret_cast<const T*>(f.out + f.mu_off),
-                    f.plan, f.enc_r0, f.n, f.nblk, s_scan);
+  auto tile_in = [&](uint32_t gt, uint32_t& fi) -> uint32_t {
+    fi = field_of<BATCH>(b.field_enc[DT], gt);
+    return BATCH == kSingle ? gt : gt - (uint32_t)field_ref<BATCH>(b, fi)->base_enc;
   };
 
-  for (uint32_t i = threadIdx.x; i <= MASK16; i += kWG) reinterpret_cast<uint4*>(s_stage)[i] = make_uint4(0, 0, 0, 0);
-  uint64_t gt = claim();
-  if (gt >= ntiles) return;
-  TileIn<T, B> cur;
-  load(cur, gt);
-  // a single call's last tile leaves its stream end to after the loop, where
-  // nothing else is live (written in the loop, it made the loop spill); the
-  // mid-byte total waits in LDS
-  if (threadIdx.x == 0) *s_end = ~0ull;
+  // The first tile and its plan; then the ticket of the second, taken only
+  // now, so that the workgroups' first tiles come before all second ones.
+  uint32_t gt;
+  if (direct) {
+    if (wid >= ntiles) return;
+    gt = uniform(listed(wid));
+  } else {
+    if (threadIdx.x == 0) sh.next[0] = listed(number(atomicAdd(ticket, 1u)));
+    __syncthreads();
+    gt = uniform(sh.next[0]);
+    if (gt == ~0u) return;
+  }
+  T x[SUB][EPL];
+  WavePlan<T, B> cur, nxt;
+  uint32_t fi;
+  uint32_t t = tile_in(gt, fi);
+  uint32_t fi_n = fi, t_n = t;
+  uint32_t tk = 0, tn = ~0u;
+  bool more = false;
+  {
+    const FieldC* f = field_ref<BATCH>(b, fi);
+    const __amdgpu_buffer_rsrc_t rs = values_of<T, B>(f, t);
+    plan_load<T, B>(cur, f, t, wave, true);
+    if (!direct && threadIdx.x == 0) tk = atomicAdd(ticket, 1u);
+    // the first tile's values without regard to its plan, a memory latency
+    // earlier (constant blocks' are not used)
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) row_load<T, B, EPL>(x[s], rs, wave, s, 1u);
+  }
+  // the next tile (from slot `slot`) and its plan's loads, and the ticket of
+  // the tile after it
+  auto next = [&](uint32_t slot) {
+    if (!direct) {
+      const uint32_t g = uniform(sh.next[slot]);
+      more = g != ~0u;
+      if (more) t_n = tile_in(g, fi_n);
+    }
+    plan_load<T, B>(nxt, field_ref<BATCH>(b, fi_n), t_n, wave, more);
+    if (more && threadIdx.x == 0) tk = atomicAdd(ticket, 1u);
+  };
+  if (!direct) {
+    if (threadIdx.x == 0) sh.next[1] = listed(number(tk));
+    __syncthreads();
+  }
+  next(1);
 
-  // the pending tile (same in every lane): encoded into the ring from byte
-  // p_at (16-byte aligned), its offset not yet resolved
+  // the pending tile (wave-uniform): its bytes in the wave's ring from byte
+  // p_at (16-byte aligned) on, its offset not yet taken
   bool pend = false;
-  uint32_t p_tile = 0, p_field = 0, p_bytes = 0, p_at = 0;
+  uint32_t p_tile = 0, p_field = 0, p_bytes = 0, p_at = 0, p_total = 0, p_before = 0;
   uint32_t at = 0;  // ring byte of the current tile's start (16-byte aligned)
-  // Resolve the pending tile's offset, copy it out and clear its ring bytes.
-  // A single call's tile waits on its own status word, which the scan workgroup
-  // publishes; a batch's walks back by look-back, one status word per lane a
-  // round (status loads go to the device's coherence point, and wider
-  // windows measured slower).
+  // Take the pending tile's offset and copy the wave's share of it out. The
+  // scan workgroup's sums run over all fields of the type: a batch's tile
+  // takes off the sum up to its field's first tile.
   auto flush = [&](uint64_t first_poll) {
-    const FieldC fp = field_at<BATCH>(b, p_field);
-    if constexpr (BATCH == kSingle) {
-      if (threadIdx.x == 0) *s_base = scan_wait(fp.enc_mid, p_tile, p_bytes, &fp.ctr->err, 1u, first_poll);
-    } else if (threadIdx.x < kWave) {
-      // the predecessor's word was read before the next tile's loads: when
-      // it already holds its inclusive prefix (the common case by now), that
-      // is this tile's offset, published as the look-back would
-      const uint64_t w0 = __shfl(first_poll, 0);
-      uint64_t p;
-      if (p_tile > 0 && (w0 >> 62) == 2) {
-        p = w0 & kValueMask;
-        if (threadIdx.x == 0) status_store(fp.enc_mid + p_tile, kFlagIncl | ((p + p_bytes) & kValueMask));
-      } else {
-        p = lookback_resolve<1>(fp.enc_mid, p_tile, p_bytes, &fp.ctr->err, 1u);
-      }
-      if (threadIdx.x == 0) *s_base = p;
+    const FieldC* fp = field_ref<BATCH>(b, p_field);
+    Counters* const ctr = as_global(fp->ctr);
+    uint64_t* const st = as_global(fp->enc_mid);
+    bool ok = true;
+    uint64_t base = uniform(scan_wait(st, p_tile, p_total, ok, first_poll));
+    if constexpr (BATCH == kBatch) {
+      if (fp->base_enc > 0) base -= uniform(scan_wait(st - 1, 0, 0, ok));
     }
-    __syncthreads();
-    const uint64_t base = *s_base;
-    const uint64_t mid = sections(fp.nblk, fp.ctr->n_nc, BYTES, B, 0).mid;
+    if (!ok) {  // a bounded wait gave up: the field has no stream (finish_stream)
+      atomicMax(&ctr->err, 1u);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
+      __hip_atomic_store(as_global(fp->out_size), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const uint64_t nblk = fp->nblk;
+    const uint64_t mid = sections(nblk, *as_constant(&ctr->n_nc), BYTES, B, 0).mid;
     // the output holds the worst case (every block raw; the caller's capacity
-    // is checked against it): an offset past it can only come from a failed
-    // wait, which has raised the error already
-    if (mid + base + p_bytes <= sections(fp.nblk, fp.nblk, BYTES, B, fp.n * BYTES).total)
-      copy_out(fp.out, mid + base, s_stage, p_at / 16, MASK16, p_bytes);
-    if (p_tile == cdiv(fp.nblk, G::TBLK) - 1) {
-      // the field's last tile ends the mid section: its total (the last
-      // header field) and the stream size
-      if (threadIdx.x == 0) {
-        if constexpr (BATCH == kSingle)
-          *s_end = base + p_bytes;
-        else
-          fp.ctr->mid_total = base + p_bytes;  // for the finishing pass
-      }
-    }
-    __syncthreads();
-    ring_clear(s_stage, p_at / 16, MASK16, p_bytes);
+    // is checked against it)
+    if (ok && mid + base + p_total <= sections(nblk, nblk, BYTES, B, fp->n * BYTES).total)
+      copy_out(as_global(fp->out), mid + base + p_before, stage, p_at / 16, MASK16, p_bytes);
     pend = false;
   };
 
-  for (;;) {
-    const FieldC f = field_at<BATCH>(b, cur.field);
-    const uint32_t t = cur.tile;
-    const T e = cur.e;
-    const Sections sec = sections(f.nblk, cur.n_nc, BYTES, B, 0);
-    uint8_t* out = f.out;
-    uint64_t* mid_status = f.enc_mid;
-    // the tile's K bytes, codes and mu values from their first (the same in
-    // every lane); rows index them with 32-bit offsets
-    uint8_t* const kb_t = out + sec.kbytes + cur.r0;
-    uint8_t* const cd_t = out + sec.codes + cur.r0 * (B / 4);
-    T* const mus_t = reinterpret_cast<T*>(out + f.mu_off) + (uint64_t)t * G::TBLK;
-    // Row by row: encode with error control (K0, then one more mantissa bit,
-    // then raw; every lane votes, lanes without a coded block vote yes), codes
-    // and byte counts, the row's offsets, K bytes and codes, and the staged
-    // mid bytes, so that only one row's words are live at a time.
-    uint32_t tile_bytes = 0;
+  for (uint32_t par = 0;; par ^= 1) {
+    const FieldC* f = field_ref<BATCH>(b, fi);
+    uint8_t* const out = as_global(f->out);
+    const uint64_t kb = (uint64_t)t * G::TBLK;
+    const uint32_t nval_t = (uint32_t)std::min<uint64_t>(f->n - kb * B, (uint64_t)G::TBLK * B);
+    const bool tail = nval_t != (uint32_t)(G::TBLK * B);  // the field's last tile may hold a short block
+    const __amdgpu_buffer_rsrc_t rx = values_of<T, B>(field_ref<BATCH>(b, fi_n), t_n);
+    // the wave's K bytes and codes from their first; rows index them with
+    // 32-bit offsets (lanes without one store far past the range: nothing)
+    const uint64_t r0 = uniform(cur.r0) + rank_ahead<T, B>(cur.ahead, wave);
+    const Sections sec = sections(f->nblk, as_constant(f->ctr)->n_nc, BYTES, B, 0);
+    const __amdgpu_buffer_rsrc_t rk = buffer_of(out + sec.kbytes + r0, G::WBLK);
+    const __amdgpu_buffer_rsrc_t rc = buffer_of(out + sec.codes + r0 * (B / 4), G::WBLK * (B / 4));
+    uint32_t wbytes = 0, wrank = 0;
 #pragma unroll
     for (int s = 0; s < SUB; ++s) {
-      if constexpr (sizeof(T) == 4) {
-        // the flush's barrier orders the cleared words before this row's
-        // stores
-        if (pend && tile_bytes + (uint32_t)(G::TILE * BYTES) > RING - ((p_bytes + 15u) & ~15u)) flush(0);
-      }
-      U q[EPL];
-      int K = cur.row.K(s);
-      // a wave whose blocks of this row are all constant (or past the end)
-      // stores nothing: it skips to the row's offset scan, which every wave
-      // joins (the vote is wave-uniform, so the branch is too). Only the
-      // 64-bit words pay enough per row for the skip to win; for float32 it
-      // measured no faster and the branch is left out.
-      const bool live = sizeof(T) == 4 || __ballot(K != 0) != 0;
-      const int cnt_s = cur.row.cnt(s);
-      bool raw = false;
-      int nb = 0;
-      uint32_t codes = 0, lb = 0;
-      const bool coded = K > 0;
-      // Without a short block (the last of a field) in the wave, no value
-      // needs a validity test: constant and absent blocks encode as zero
-      // words that keep nothing (K = 0: no kept bytes, no codes), raw blocks
-      // keep every byte with code 0.
-      const bool whole = __ballot(K != 0 && cnt_s != EPL) == 0;
-      if (live) {
-        bool ok = encode_try<T, EPL>(cur.x[s], coded ? cnt_s : 0, cur.mu[s], e, K, coded && cur.row.verify(s), q);
-        if (!group_all<LPB>(ok)) {  // only coded blocks can fail
-          const int K1 = kept_bits<T>(K - Traits<T>::KMIN + 1);
-          bool ok1 = false;
-          if (K1 != K) ok1 = encode_try<T, EPL>(cur.x[s], cnt_s, cur.mu[s], e, K1, true, q);
-          K = group_all<LPB>(ok1) ? K1 : -1;
+      const uint32_t pb = cur.pb[s];
+      const uint64_t has = __ballot(pb != 0);
+      if (has != 0) {  // a row of constant blocks stores nothing (wave-uniform)
+        int K = pb == 0xFFu ? -1 : (int)(pb & 0x7Fu);
+        const T mu = cur.mu[s];
+        const uint32_t lk = wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / LPB;  // block of the tile
+        int cnt = EPL;
+        if (tail) {
+          const int rem = (int)nval_t - (int)(lk * B + lig * EPL);
+          cnt = rem < 0 ? 0 : (rem > EPL ? EPL : rem);
         }
-        raw = K < 0;
-        if (raw) {  // byte-swapped here, so that every string below is byte_swap(q) less its ci low bytes
-#pragma unroll
-          for (int i = 0; i < EPL; ++i) q[i] = byte_swap(bits_of(cur.x[s][i]));
-        }
-        nb = raw ? BYTES : (K > 0 ? bytes_of(K) : 0);
-        U prev = lane_before<LPB, U>(q[EPL - 1]);
-        prev = lig == 0 ? (U)0 : prev;
-        // leading identical bytes capped at min(3, nb) (0 for raw blocks); a
-        // zero difference counts all bytes, which the cap turns into the cap
-        // as well. The cap is at most 24 bits, so a 64-bit word's high half
-        // decides it.
-        const uint32_t cap8 = raw ? 0u : 8u * (uint32_t)(nb < 3 ? nb : 3);
-        auto code_of = [&](U z) -> uint32_t {
-          const uint32_t lz = sizeof(U) == 8 ? lead_zero_bits((uint32_t)((uint64_t)z >> 32)) : lead_zero_bits(z);
-          return (lz < cap8 ? lz : cap8) >> 3;
-        };
-        uint32_t csum = 0;
-        if (whole) {
-#pragma unroll
-          for (int i = 0; i < EPL; ++i) {
-            const uint32_t ci = code_of(q[i] ^ prev);
-            codes |= ci << (2 * (EPL - 1 - i));
-            csum += ci;
-            prev = q[i];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < EPL; ++i) {
-            const uint32_t ci = i < cnt_s ? code_of(q[i] ^ prev) : 0u;
-            codes |= ci << (2 * (EPL - 1 - i));
-            csum += ci;
-            prev = q[i];
+        // Error control where the classification pass could not prove the
+        // bound: K0, then one more mantissa bit, then raw. Every lane of a
+        // block votes.
+        const bool special = __ballot((pb & 0x80u) != 0) != 0;
+        if (special) {
+          const T e = from_bits<T>((U)as_constant(f->ctr)->e_bits);
+          const bool ok = !(K > 0 && (pb & 0x80u)) || run_within<T, EPL>(x[s], cnt, mu, e, K);
+          if (!group_all<LPB>(ok)) {
+            const int K1 = kept_bits<T>(K - Traits<T>::KMIN + 1);
+            const bool ok1 = K1 != K && run_within<T, EPL>(x[s], cnt, mu, e, K1);
+            K = group_all<LPB>(ok1) ? K1 : -1;
+            if (K < 0 && lig == 0) reinterpret_cast<T*>(out + f->mu_off)[kb + lk] = (T)0;
           }
         }
+        const bool raw = K < 0;
+        uint32_t nb = ((uint32_t)K + 7u) >> 3;
+        const uint32_t sft = 8u * nb - (uint32_t)K;
+        uint32_t cap = 0x80000000u >> (8u * (nb < 3u ? nb : 3u));
+        // a value's word: its top nb bytes are stored (less the leading ones
+        // its code names); a raw value's bytes in storage order
+        U q[EPL];
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) q[i] = (U)(bits_of(x[s][i] - mu) >> sft);
+        if (special) {
+          if (raw) {
+            nb = (uint32_t)BYTES;
+            cap = 0x80000000u;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) q[i] = byte_swap(bits_of(x[s][i]));
+          }
+        }
+        // Codes: leading identical bytes capped at min(3, nb) (0 for raw
+        // blocks), at most 24 bits, so a 64-bit word's high half decides: a
+        // bit set at the cap ends the count there. Lanes of constant and
+        // absent blocks (nb = 0) get code 0 and store nothing.
+        uint32_t prev = wave_before(high_word(q[EPL - 1]));
+        prev = lig == 0 ? 0u : prev;
+        uint32_t c[EPL], codes = 0;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          const uint32_t hw = high_word(q[i]);
+          c[i] = lead_zero_bits((hw ^ prev) | cap) >> 3;
+          prev = hw;
+        }
+        uint32_t live = nb * EPL;
+        if (tail) {
+          int cv = cnt;
+          asm volatile("" : "+v"(cv));  // keeps this branch's tests inside it
+#pragma unroll
+          for (int i = 0; i < EPL; ++i) c[i] = i < cv ? c[i] : 0u;
+          live = nb * (uint32_t)cnt;
+        }
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) codes = (codes << 2) | c[i];
         // stored bytes of the lane: nb per valid value less the identical ones
-        lb = (uint32_t)(nb * cnt_s) - csum;
-      }
-      uint32_t rtot;
-      const uint32_t ex = wg_excl_sum<uint32_t>(lb, s_scan, rtot);
-      // the ring from this tile's start up to the pending tile's must hold
-      // the row (the condition is the same in every lane). For float64 rows
-      // (16 KiB) the check takes the row's own size; float32 rows check
-      // their largest size before the row, where the flush's code does not
-      // meet the row's live registers (checked here, the float32 encoder
-      // spilled).
-      if constexpr (sizeof(T) == 8) {
-        if (pend && tile_bytes + rtot > RING - ((p_bytes + 15u) & ~15u)) {
-          flush(0);
-          __syncthreads();  // the cleared words before this row's stores
-        }
-      }
-      if (K != 0) {
-        const uint32_t r = cur.row.rank(s);  // within the tile
-        if (lig == 0) {
-          kb_t[r] = raw ? kRawK : (uint8_t)K;
-          if (coded && raw) mus_t[(uint32_t)(s * G::TB) + threadIdx.x / LPB] = (T)0;
-        }
-        uint8_t* cdst = cd_t + (r * (uint32_t)(B / 4) + (uint32_t)lig * (EPL / 4));
+        const uint32_t lb = live - ((uint32_t)__popc(codes) + (uint32_t)__popc(codes & 0xAAAAAAAAu));
+        const uint32_t inc = wave_incl_sum_u32(lb);
+        const uint32_t rtot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        // K bytes and codes. The group's first lane does not count its own
+        // block; the others see it counted.
+        const uint64_t firsts = has & first_lanes<LPB>();
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, wrank - (lig != 0 ? 1u : 0u)));
+        wrank += (uint32_t)__popcll(firsts);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(raw ? kRawK : (uint8_t)K), rk,
+                                             (int)(pb != 0 && lig == 0 ? rank : 0x40000000u), 0, 0);
+        const uint32_t coff = pb != 0 ? rank * (uint32_t)(B / 4) + lig * (EPL / 4) : 0x40000000u;
         if constexpr (EPL == 8) {
-          const uint16_t wv = (uint16_t)(((codes >> 8) & 0xFFu) | ((codes & 0xFFu) << 8));
-          *reinterpret_cast<uint16_t*>(cdst) = wv;
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(((codes >> 8) & 0xFFu) | ((codes & 0xFFu) << 8)), rc,
+                                                (int)coff, 0, 0);
         } else {
-#pragma unroll
-          for (int j = 0; j < EPL / 4; ++j) cdst[j] = (uint8_t)(codes >> (8 * (EPL / 4 - 1 - j)));
+          static_assert(EPL == 16, "a lane's codes are one or two half words");
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bswap32(codes), rc, (int)coff, 0, 0);
         }
-      }
-      // stage the kept bytes of each value, most significant first: q holds
-      // only its top nb bytes, so after the byte swap the value's string is
-      // byte_swap(q) without its ci low bytes, zero bytes above it
-      if (live) {
-        LanePacker pk(s_stage, at + tile_bytes + ex, RING - 1);
-        if (whole) {
+        // the ring from this tile's start up to the pending tile's must hold
+        // the row and the dword that may be zeroed behind it
+        if (pend && wbytes + rtot + 8u > RING - ((p_bytes + 15u) & ~15u)) flush(0);
+        if (!pend && wbytes == 0) at = 0;
+        // a tile that fills the ring: the dword zeroed behind the row may be
+        // the tile's first one (never where the tile starts at 0: behind it
+        // is the slack)
+        const bool tight = wbytes + rtot + 8u > RING;
+        uint32_t kept = 0;
+        if (tight) kept = *lds_at(ring0 + at);
+        // stage the kept bytes. A lane's run starts inside the ring and may
+        // end in the slack behind it.
+        const uint32_t start = ring0 + ((at + wbytes + inc - lb) & (RING - 1u));
+        const uint32_t end = start + lb;
+        RunPacker pk(end);
+        const uint32_t nbh = nb < 4u ? nb : 4u, nbl = nb - nbh;
+        const PackSel sel(nbh);
+        if (tail) {
+          int cv = cnt;
+          asm volatile("" : "+v"(cv));
+          const PackSel sell(nbl);
 #pragma unroll
-          for (int i = 0; i < EPL; ++i) {
-            const int ci = (int)((codes >> (2 * (EPL - 1 - i))) & 3u);
-            pk.put(drop_low_bytes(byte_swap(q[i]), (uint32_t)ci), nb - ci);
+          for (int i = EPL - 1; i >= 0; --i) {
+            if (sizeof(T) == 8) {
+              if (i < cv) pk.prepend(low_word(q[i]), nbl, 0u, sell);
+              pk.store();
+            }
+            if (i < cv) pk.prepend(high_word(q[i]), nbh, c[i], sel);
+            if (i > 0) pk.store();
+          }
+        } else if (sizeof(T) == 8 && __ballot(nb > 4u) != 0) {
+          const PackSel sell(nbl);
+#pragma unroll
+          for (int i = EPL - 1; i >= 0; --i) {
+            pk.prepend(low_word(q[i]), nbl, 0u, sell);
+            pk.store();
+            pk.prepend(high_word(q[i]), nbh, c[i], sel);
+            if (i > 0) pk.store();
           }
         } else {
 #pragma unroll
-          for (int i = 0; i < EPL; ++i) {
-            const int ci = (int)((codes >> (2 * (EPL - 1 - i))) & 3u);
-            const bool valid = i < cnt_s;
-            const U sv = valid ? drop_low_bytes(byte_swap(q[i]), (uint32_t)ci) : (U)0;
-            pk.put(sv, valid ? nb - ci : 0);
+          for (int i = EPL - 1; i >= 0; --i) {
+            pk.prepend(high_word(q[i]), nbh, c[i], sel);
+            if (i > 0) pk.store();
           }
         }
-        pk.flush();
+        pk.store_first(end);
+        // the run of the lane that crosses the ring's end: its dwords behind
+        // the end move to the ring's start
+        const uint64_t over = __ballot(end > ring0 + RING);
+        if (over != 0) {
+          const uint32_t ov =
+              (uint32_t)__builtin_amdgcn_readlane((int)end, (int)__ffsll((long long)over) - 1) - ring0 - RING;
+          if (lane * 4u < ov) *lds_at(ring0 + lane * 4u) = *lds_at(ring0 + RING + lane * 4u);
+        }
+        pk.or_head(start);
+        if (tight && wbytes > 0) *lds_at(ring0 + at) = kept;
+        wbytes += rtot;
       }
-      tile_bytes += rtot;
+      // the row's registers are free: the next tile's row goes out
+      row_load<T, B, EPL>(x[s], rx, wave, s, nxt.pb[s]);
+      // the ticket has arrived: its tile's number, needed at the barrier
+      if (s == 0 && more && threadIdx.x == 0) tn = listed(number(tk));
     }
-    if (threadIdx.x == 0) lookback_publish(mid_status, t, tile_bytes);
-    const uint32_t f_cur = cur.field;
-
-    // the next tile's loads go out while the pending tile's offset is
-    // resolved. A single call reads the pending tile's offset word before
-    // them: vector loads return in order, so a read issued after the tile's
-    // loads would wait for all of them
-    gt = claim();  // its barriers also order the staging before the copy-out
-    const bool more = gt < ntiles;
+    if (lane == 0) sh.tot[par][wave] = wbytes;
+    if (threadIdx.x == 0) sh.next[par] = tn;
+    __syncthreads();
+    uint32_t total = 0, before = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kWavesPerWG; ++i) {
+      const uint32_t v = uniform(sh.tot[par][i]);
+      before += i < wave ? v : 0u;
+      total += v;
+    }
+    // (the first tile's sum is its own)
+    if (threadIdx.x == 0)
+      status_store(as_global(f->enc_mid) + t, (t == 0 && (BATCH == kSingle || f->base_enc == 0) ? kFlagIncl : kFlagAgg) | total);
     uint64_t first_poll = 0;
-    if constexpr (BATCH == kSingle) {
-      if (pend && threadIdx.x == 0) first_poll = status_load(field_at<BATCH>(b, p_field).enc_mid + p_tile);
-    } else {  // a batch: the predecessor's word, for the look-back's shortcut
-      if (pend && threadIdx.x == 0 && p_tile > 0)
-        first_poll = status_load(field_at<BATCH>(b, p_field).enc_mid + p_tile - 1);
-    }
-    if (more) load(cur, gt);
+    if (pend) first_poll = status_load(as_global(field_ref<BATCH>(b, p_field)->enc_mid) + p_tile);
+    const bool last = !more;
+    const uint32_t t_c = t, fi_c = fi;
+    t = t_n;
+    fi = fi_n;
+    cur = nxt;
+    if (!last) next(par);
     if (pend) flush(first_poll);
     pend = true;
-    p_tile = t;
-    p_field = f_cur;
-    p_bytes = tile_bytes;
+    p_tile = t_c;
+    p_field = fi_c;
+    p_bytes = wbytes;
+    p_total = total;
+    p_before = before;
     p_at = at;
-    at = (at + ((tile_bytes + 15u) & ~15u)) & (RING - 1);
-    if (!more) break;
+    at = (at + ((wbytes + 15u) & ~15u)) & (RING - 1u);
+    if (last) break;
   }
   flush(0);
-  if constexpr (BATCH == kSingle) {
-    if (threadIdx.x == 0 && *s_end != ~0ull) {
-      const FieldC f = field_at<BATCH>(b, 0);
-      finish_stream(f, sections(f.nblk, f.ctr->n_nc, BYTES, B, 0).mid, *s_end);
-    }
-  }
 }
 
+// Workgroup 0 is the scan workgroup of the tiles' mid-byte offsets (every
+// other waits on one status word a tile).
 template <typename T, int B, int BATCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Geo<T, B>::ENC_WAVES))) void k_encode(
-    CBatch b) {
-  using G = Geo<T, B>;
-  __shared__ uint32_t s_scan[G::SUB * kWavesPerWG];
-  __shared__ uint32_t s_tile;
-  __shared__ uint64_t s_base, s_end;
-  __shared__ __align__(16) uint32_t s_stage[enc_ring_bytes<T, B>() / 4];
-  __shared__ ScanShared s_sums;
-  encode_pass<T, B, BATCH>(b, s_scan, &s_tile, &s_base, &s_end, s_stage, &s_sums);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<T, B>::WAVES))) void k_encode(CBatch b) {
+  using G = EncGeo<T, B>;
+  constexpr int DT = sizeof(T) == 4 ? 0 : 1;
+  __shared__ union {
+    EncShared enc;
+    ScanShared scan;
+  } s_sh;
+  __shared__ __align__(16) uint8_t s_ring[kWavesPerWG * (G::RING + G::SLACK)];
+  if (blockIdx.x == 0) {
+    // the type's status words lie in one array, its first field's first
+    const FieldC* f = field_ref<BATCH>(b, BATCH == kSingle ? 0u : *as_constant(b.field_enc[DT]));
+    const uint64_t total = scan_workgroup(as_global(f->enc_mid), b.tiles_enc[DT], &as_global(f->ctr)->err, 1u, s_sh.scan);
+    if constexpr (BATCH == kSingle) {
+      if (threadIdx.x == 0) finish_stream(field_at<BATCH>(b, 0), total);
+    }
+    return;
+  }
+  encode_pass<T, B, BATCH>(b, s_sh.enc, s_ring);
 }
 
 // --------------------------------------------------------------- finalize ---
@@ -1241,8 +1341,10 @@ __global__ void k_finalize(CBatch b) {
   const FieldC f = field_at(b, blockIdx.x);
   if (f.nblk != 0) {
     if (threadIdx.x == 0) {
-      const uint32_t w = f.dtype == 0 ? 4 : 8;
-      finish_stream(f, sections(f.nblk, f.ctr->n_nc, w, f.b, 0).mid, f.ctr->mid_total);
+      // the scan over the type's tiles: the sum up to the field's last one
+      // less the sum before its first
+      const uint64_t last = f.enc_mid[cdiv(f.nblk, enc_blocks(f.b, f.dtype == 0 ? 4 : 8)) - 1] & kValueMask;
+      finish_stream(f, last - (f.base_enc > 0 ? f.enc_mid[-1] & kValueMask : 0));
     }
     return;
   }
@@ -1274,15 +1376,15 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
       const uint64_t want = std::max<uint64_t>(g.encode_wgs[dt], kTicketClasses);
       const uint32_t genc = (uint32_t)std::min<uint64_t>(b.tiles_enc[dt], want);
       const bool batch = b.fields != nullptr;
-      // a single call adds workgroup 0, its scan workgroup
+      // workgroup 0 is the scan workgroup
       if (dt == 0 && !batch)
         run("k_encode", [&] { k_encode<float, B, kSingle><<<genc + 1, 256, 0, stream>>>(b); });
       else if (dt == 0)
-        run("k_encode", [&] { k_encode<float, B, kBatch><<<genc, 256, 0, stream>>>(b); });
+        run("k_encode", [&] { k_encode<float, B, kBatch><<<genc + 1, 256, 0, stream>>>(b); });
       else if (!batch)
         run("k_encode", [&] { k_encode<double, B, kSingle><<<genc + 1, 256, 0, stream>>>(b); });
       else
-        run("k_encode", [&] { k_encode<double, B, kBatch><<<genc, 256, 0, stream>>>(b); });
+        run("k_encode", [&] { k_encode<double, B, kBatch><<<genc + 1, 256, 0, stream>>>(b); });
     }
   }
   // batches finish their streams here; a single call only without values

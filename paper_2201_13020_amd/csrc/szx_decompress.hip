@@ -327,10 +327,8 @@ __device__ __forceinline__ uint32_t block_mid_bytes(const BlockCodes<B>& c, uint
 template <typename T, int B>
 __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, uint32_t t, uint32_t* s_scan,
                                             uint64_t* s_r0p, uint64_t* s_m0p, int* s_flag) {
-  using G = Geo<T, B>;  // classification tiles follow the encode geometry
   constexpr int BYTES = Traits<T>::BYTES;
-  constexpr int TBLK = G::TBLK;
-  constexpr int CLS = TBLK > (int)kClsMin ? TBLK : (int)kClsMin;
+  constexpr int CLS = (int)kClsBlocks;
   constexpr int BPT = CLS / kWG;
   static_assert(GeoD<T, B>::TBLK % BPT == 0, "every decode tile starts at some thread's first block");
   uint64_t& s_r0 = *s_r0p;

@@ -25,6 +25,15 @@ __device__ __forceinline__ P as_global(const P& member) {
   return (P)(__attribute__((address_space(1))) char*)raw;
 }
 
+// A pointer to memory that nothing writes while the kernel runs, re-read as a
+// constant-memory pointer: a read at a wave-uniform address through it is a
+// scalar load (no vector register, no wait on vector loads), also in a kernel
+// that stores.
+template <typename V>
+__device__ __forceinline__ const V* as_constant(const V* p) {
+  return (const V*)(__attribute__((address_space(4))) const char*)(uintptr_t)p;
+}
+
 constexpr int kWave = 64;
 constexpr int kWG = 256;
 constexpr int kWavesPerWG = kWG / kWave;
@@ -79,10 +88,6 @@ struct Geo {
   static constexpr int TILE = TB * B;  // values per row
   static constexpr int SUB = geo_sub(TILE * (int)sizeof(T), TB, TARGET);
   static constexpr int TBLK = TB * SUB;  // blocks per tile
-  // waves per SIMD the encoder is held to (its LDS stage holds a tile's
-  // output: 4 workgroups of a 32 KiB stage fit the 160 KiB of LDS, one of a
-  // 64 KiB stage leaves room for 2)
-  static constexpr int ENC_WAVES = TILE * SUB * (int)sizeof(T) > 40000 ? 2 : 4;
   static_assert(LPB >= 1 && LPB <= 64 && (64 % LPB) == 0, "group must fit a wave");
   static_assert(TBLK % 8 == 0, "a tile owns whole state bytes");
 };
@@ -141,12 +146,12 @@ template <typename T>
 __device__ __forceinline__ bool exact_le(T a, T c, T e) {
   const T nb = -c;
   const T s = a + nb;
-  if (s < e) return true;
-  if (s > e) return false;
   const T bv = s - a;
   const T av = s - bv;
   const T t = (a - av) + (nb - bv);
-  return t <= (T)0;
+  // bitwise on purpose: no branch (branches here nest in every value of the
+  // encoder's verification and cost it its scalar registers)
+  return (bool)((int)(s < e) | ((int)(s == e) & (int)(t <= (T)0)));
 }
 
 // p(y) of eq. (4): unbiased exponent of |y|, with zero and subnormals at the
@@ -427,6 +432,13 @@ __device__ __forceinline__ uint64_t status_load(const uint64_t* p) {
   return __hip_atomic_load((global_u64*)const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Two counts in one word, summed together: an aggregate holds the first in
+// its low 17 bits (at most 1024 a tile, 64 tiles a window) and the second
+// above (at most 256 a tile), an inclusive prefix the first in its low 32
+// bits and the second above.
+__device__ __forceinline__ uint64_t pair_aggregate(uint32_t a, uint32_t c) { return a | (c << 17); }
+__device__ __forceinline__ uint64_t pair_sum(uint32_t s) { return (uint64_t)(s & 0x1FFFFu) | ((uint64_t)(s >> 17) << 32); }
+
 // Device-wide exclusive prefix sums over tiles (decoupled look-back). A tile
 // first publishes its own aggregate, then resolves its exclusive prefix from
 // its predecessors' words and publishes its inclusive prefix. A tile waits
@@ -435,8 +447,12 @@ __device__ __forceinline__ uint64_t status_load(const uint64_t* p) {
 // before it waits on anything, so every wait ends. Waits are bounded all the
 // same: on exhaustion err is raised to err_code and the partial prefix is
 // returned.
+template <bool PAIR = false>
 __device__ __forceinline__ void lookback_publish(uint64_t* status, uint32_t t, uint64_t agg) {
-  status_store(status + t, (t == 0 ? kFlagIncl : kFlagAgg) | (agg & kValueMask));
+  if (PAIR && t == 0)
+    status_store(status, kFlagIncl | pair_sum((uint32_t)agg));
+  else
+    status_store(status + t, (t == 0 ? kFlagIncl : kFlagAgg) | (agg & kValueMask));
 }
 
 // The 64-bit word of lane i (i wave-uniform).
@@ -450,7 +466,7 @@ __device__ __forceinline__ uint32_t wave_total_u32(uint32_t v) {
 
 // Called by all 64 lanes of one wave after lookback_publish; returns the same
 // exclusive prefix in every lane.
-template <int R = 4>  // status words per lane per round: a window of 64 R tiles
+template <int R = 4, bool PAIR = false>  // R: status words per lane per round (a window of 64 R tiles)
 __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, uint64_t agg,
                                                   uint32_t* err, uint32_t err_code) {
   const int lane = lane_id();
@@ -484,7 +500,8 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
         continue;
       }
       // the aggregates ahead of the inclusive word, then that word itself
-      excl += wave_total_u32(lane < first ? (uint32_t)w[k] : 0u);
+      const uint32_t sum = wave_total_u32(lane < first ? (uint32_t)w[k] : 0u);
+      excl += PAIR ? pair_sum(sum) : sum;
       if (first < 64) {
         excl += lane_word(w[k], first) & kValueMask;
         done = true;
@@ -502,7 +519,7 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
       __builtin_amdgcn_s_sleep(1);
     }
   }
-  if (lane == 0) status_store(status + t, kFlagIncl | ((excl + agg) & kValueMask));
+  if (lane == 0) status_store(status + t, kFlagIncl | ((excl + (PAIR ? pair_sum((uint32_t)agg) : agg)) & kValueMask));
   return excl;
 }
 
@@ -515,7 +532,7 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
 // window per round and per tile.) It waits only on tiles that running
 // workgroups hold, and its waits are bounded like the others: on exhaustion
 // err is raised and it stops, and the tiles still waiting give up on their own
-// bounds. A round is one trip to the device's coherence point: the loads go
+// bounds. Returns the sum over all tiles. A round is one trip to the device's coherence point: the loads go
 // out together (none in a branch, where it would wait for the one before it;
 // past the last tile they read the word behind it, which stays unpublished)
 // and the sums take 32-bit DPP steps. (One wave that read 16 words a lane, each
@@ -525,7 +542,7 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
 struct ScanShared {
   uint32_t count[2][kWavesPerWG], sum[2][kWavesPerWG];
 };
-__device__ __forceinline__ void scan_workgroup(uint64_t* status, uint64_t ntiles, uint32_t* err, uint32_t err_code,
+__device__ __forceinline__ uint64_t scan_workgroup(uint64_t* status, uint64_t ntiles, uint32_t* err, uint32_t err_code,
                                                ScanShared& sh) {
   constexpr int R = 4;
   const int lane = lane_id();
@@ -585,20 +602,21 @@ __device__ __forceinline__ void scan_workgroup(uint64_t* status, uint64_t ntiles
     if (adv == 0) {
       if (++spins > kSpinLimit) {
         if (threadIdx.x == 0) atomicMax(err, err_code);
-        return;
+        break;
       }
       __builtin_amdgcn_s_sleep(2);
     } else {
       spins = 0;
     }
   }
+  return run;
 }
 
 // A tile's exclusive prefix once the scan workgroup has published its inclusive
-// one (one lane polls; the value is the inclusive prefix less the tile's own
-// aggregate). Bounded: on exhaustion err is raised and 0 is returned.
-__device__ __forceinline__ uint64_t scan_wait(const uint64_t* status, uint32_t t, uint64_t agg, uint32_t* err,
-                                              uint32_t err_code, uint64_t first = 0) {
+// one (the inclusive prefix less the tile's own aggregate). Bounded: on
+// exhaustion ok becomes false and 0 is returned.
+__device__ __forceinline__ uint64_t scan_wait(const uint64_t* status, uint32_t t, uint64_t agg, bool& ok,
+                                              uint64_t first = 0) {
   // `first`: the word as read earlier by the caller (0: not read)
   if ((first >> 62) == 2) return ((first & kValueMask) - agg) & kValueMask;
   uint32_t spins = 0;
@@ -606,7 +624,7 @@ __device__ __forceinline__ uint64_t scan_wait(const uint64_t* status, uint32_t t
     const uint64_t w = status_load(status + t);
     if ((w >> 62) == 2) return ((w & kValueMask) - agg) & kValueMask;
     if (++spins > kSpinLimit) {
-      atomicMax(err, err_code);
+      ok = false;
       return 0;
     }
     __builtin_amdgcn_s_sleep(1);
@@ -617,10 +635,11 @@ __device__ __forceinline__ uint64_t scan_wait(const uint64_t* status, uint32_t t
 // load is a transaction at the device's coherence point, so where many tiles
 // are in flight a window of 64 (one word per lane) costs less than fewer,
 // wider rounds; where few are, a window of 256 covers them in one round.
+template <bool PAIR = false>
 __device__ __forceinline__ uint64_t lookback_resolve_n(uint64_t* status, uint32_t t, uint64_t agg, uint32_t* err,
                                                        uint32_t err_code, uint64_t ntiles) {
-  return ntiles > 512 ? lookback_resolve<1>(status, t, agg, err, err_code)
-                      : lookback_resolve<4>(status, t, agg, err, err_code);
+  return ntiles > 512 ? lookback_resolve<1, PAIR>(status, t, agg, err, err_code)
+                      : lookback_resolve<4, PAIR>(status, t, agg, err, err_code);
 }
 
 }  // namespace szx

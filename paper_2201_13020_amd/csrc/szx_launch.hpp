@@ -29,7 +29,8 @@ struct FieldC {
   uint64_t* parts;      // first use only: per chunk, lowest and highest totalOrder key of its finite values
   void* stats;          // two totalOrder keys per block
   uint8_t* plan;        // one plan byte per block (classification -> encode)
-  uint64_t* enc_r0;     // first rank of every encode tile
+  uint32_t* enc_r0;     // first rank of every encode tile
+  uint32_t* enc_list;   // single calls: the encode tiles with a non-constant block
   uint64_t* cls_status; // scan status words, classification tiles
   uint64_t* enc_mid;    // scan status words, encode tiles
   uint64_t base_stats, base_cls, base_enc;  // first chunk / tile of the field in its type's numbering

@@ -34,9 +34,9 @@ struct Counters {
   uint32_t err;        // nonzero: a bounded wait of the compression gave up
   uint32_t e_ready;    // first-use path: the bound is published in e_bits
   uint32_t reserved[2];
+  uint64_t n_tiles;    // encode tiles with a non-constant block (single calls)
   uint64_t reserved2[2];
   uint64_t n_nc;       // non-constant blocks (raw included)
-  uint64_t mid_total;  // mid-byte section size (batches: for the finishing pass)
   uint64_t e_bits;     // bit pattern of the bound e in the element type
 };
 
@@ -69,15 +69,14 @@ struct Job {
   uint32_t w;
 };
 
-// Input bytes per tile of the encode and of the decode pass (targets; a tile
-// is a whole number of rows and at least 8 blocks). A decode tile divides an
-// encode tile.
+// Input bytes per tile of the encode and of the decode pass (targets; a decode
+// tile is a whole number of rows and at least 8 blocks).
 constexpr uint32_t kEncodeTileBytes = 32768;
 constexpr uint32_t kDecodeTileBytes = 16384;
 
-// Blocks per tile of the encode (or, with kDecodeTileBytes, the decode) pass
-// for block size b and element size w (mirrors Geo in szx_device.hpp).
-__host__ __device__ inline uint32_t tile_blocks(uint32_t b, uint32_t w, uint32_t target = kEncodeTileBytes) {
+// Blocks per tile of about `target` input bytes (the decode pass) for block
+// size b and element size w (mirrors Geo in szx_device.hpp).
+__host__ __device__ inline uint32_t tile_blocks(uint32_t b, uint32_t w, uint32_t target) {
   const uint32_t epl = b >= 512 ? b / 64 : 8;
   const uint32_t lpb = b / epl;
   const uint32_t tb = 256 / lpb;
@@ -87,14 +86,21 @@ __host__ __device__ inline uint32_t tile_blocks(uint32_t b, uint32_t w, uint32_t
   return tb * sub;
 }
 
-// Blocks per tile of the classification and index passes: at least
-// kClsMin (a multiple of 256, the workgroup size) and a multiple of every
-// encode tile.
-constexpr uint32_t kClsMin = 1024;
-__host__ __device__ inline uint32_t cls_blocks(uint32_t b, uint32_t w) {
-  const uint32_t t = tile_blocks(b, w);
-  return t > kClsMin ? t : kClsMin;
+// Values per lane of the encode pass, and blocks per encode tile. Sixteen
+// float32 values a lane share the per-row work (ranks, prefix sums, K and
+// code writes) among twice the values of eight: the float32 encoder issues 18
+// vector instructions a value instead of 24. Sixteen doubles would take all
+// the registers of four waves per SIMD (b = 1024 has no other split).
+__host__ __device__ constexpr uint32_t enc_epl(uint32_t b, uint32_t w) {
+  return w == 4 ? (b >= 16 ? 16 : 8) : (b >= 1024 ? 16 : 8);
 }
+__host__ __device__ constexpr uint32_t enc_blocks(uint32_t b, uint32_t w) {
+  return kEncodeTileBytes / (b * w) < 8 ? 8 : kEncodeTileBytes / (b * w);
+}
+
+// Blocks per tile of the classification and index passes (four a thread, a
+// multiple of every encode tile).
+constexpr uint32_t kClsBlocks = 1024;
 
 // Ticket classes of the persistent encode pass (per element type).
 constexpr uint32_t kTicketClasses = 8;
@@ -131,8 +137,8 @@ struct FieldTiles {
 __host__ __device__ inline FieldTiles field_tiles(uint64_t n, uint64_t nblk, uint32_t w, uint32_t b) {
   FieldTiles t;
   t.chunks = cdiv(cdiv(n, row_values(b)), kStatsChunk);
-  t.cls = cdiv(nblk, cls_blocks(b, w));
-  t.enc = cdiv(nblk, tile_blocks(b, w));
+  t.cls = cdiv(nblk, kClsBlocks);
+  t.enc = cdiv(nblk, enc_blocks(b, w));
   t.dec = cdiv(nblk, tile_blocks(b, w, kDecodeTileBytes));
   return t;
 }

@@ -1,0 +1,54 @@
+"""The encoder's packing and tile order at the edges of its rows, rings and
+tickets, byte for byte against the oracle: strings of every length (kept bytes
+0 to the whole word), rows of constant, coded and raw blocks side by side,
+tiles that fill a wave's LDS ring, a short last block, and few persistent
+workgroups, so that each takes many tiles and its ring wraps again and again."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import gpu_compress
+from oracle import szref
+from paper_2201_13020_amd import szx
+
+pytestmark = pytest.mark.gpu
+
+
+def field(kind, n, dtype, block):
+    """Values whose blocks keep few bytes, many, all of them, or none."""
+    r = np.random.default_rng(len(kind) * 1000 + n + block)
+    x = r.standard_normal(n)
+    if kind == "smooth":  # few mid bytes a value: several strings a dword
+        x = np.cumsum(x) * 1e-3
+    elif kind == "noise":  # every mantissa byte: the ring fills
+        x = x * np.exp2(r.integers(-30, 30, n))
+    elif kind == "mixed":  # blocks of every sort next to each other
+        nblk = -(-n // block)
+        sort = r.integers(0, 5, nblk)
+        amp = np.choose(sort, [0.0, 1e-6, 1e-3, 1.0, 1.0])
+        x = x * np.repeat(amp, block)[:n] + np.repeat(r.standard_normal(nblk), block)[:n]
+        raw = np.repeat(sort == 4, block)[:n] & (r.random(n) < 0.02)
+        x[raw] = np.nan
+    return x.astype(dtype)
+
+
+CASES = [  # values, wgs: one tile, ragged tiles, tens of tiles on eight workgroups
+    (1, 0), (4097, 0), (8191, 0), (40_000, 0), (600_007, 8), (300_000, 9)]
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [8, 16, 64, 128, 512, 1024])
+@pytest.mark.parametrize("kind", ["smooth", "noise", "mixed"])
+def test_streams_equal_the_oracle(kind, block, dtype):
+    dt = torch.float32 if dtype == "float32" else torch.float64
+    for n, wgs in CASES:
+        x = field(kind, n, dtype, block)
+        cls = szx.size_class(x.nbytes)
+        for eb, mode in ((1e-3, "rel"), (0.0, "abs")):
+            ref = szref.compress(x, eb, mode, block)
+            try:
+                szx.set_geometry(dt, cls, wgs)
+                out, size = gpu_compress(x, eb, mode, block)
+            finally:
+                szx.set_geometry(dt, cls, 0)
+            assert size == ref.size and np.array_equal(out[:size].cpu().numpy(), ref), (n, wgs, eb)
