@@ -156,7 +156,7 @@ __device__ __forceinline__ U group_scan_last(U v) {
 // twice the values of eight; sixteen doubles would not fit the registers.
 template <typename T, int B>
 struct EncGeo {
-  static constexpr int EPL = (int)enc_epl(B, sizeof(T));
+  static constexpr int EPL = (int)lane_values(B, sizeof(T));
   static constexpr int LPB = B / EPL;       // lanes per block
   static constexpr int GPW = kWave / LPB;   // blocks per row
   static constexpr int ROW = kWave * EPL;   // values per row
@@ -673,12 +673,6 @@ __global__ __launch_bounds__(256) void k_classify(CBatch b) {
 
 // ---------------------------------------------------------------- encode ---
 
-// A wave-uniform value held in scalar registers.
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ uint64_t uniform(uint64_t v) {
-  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
-}
-
 // Whether every valid value of a lane's run reconstructs within e exactly
 // when K leading bits of x - mu are kept.
 template <typename T, int EPL>
@@ -823,37 +817,9 @@ __device__ __forceinline__ void copy_out(uint8_t* __restrict__ out, uint64_t dst
   }
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <typename T>
-__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t rs, uint32_t off);
-template <>
-__device__ __forceinline__ float buffer_value<float>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
-}
-template <>
-__device__ __forceinline__ double buffer_value<double>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
-  using v2u = unsigned int __attribute__((ext_vector_type(2)));
-  const v2u u = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
-  return __longlong_as_double((long long)(((uint64_t)u.y << 32) | u.x));
-}
-
 // The previous lane's value over the whole wave (wave_shr:1; lane 0 gets 0).
 __device__ __forceinline__ uint32_t wave_before(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, false);
-}
-
-// Lanes that begin a group of LPB.
-template <int LPB>
-__device__ __forceinline__ constexpr uint64_t first_lanes() {
-  return LPB == 64   ? 1ull
-         : LPB == 32 ? 0x0000000100000001ull
-         : LPB == 16 ? 0x0001000100010001ull
-         : LPB == 8  ? 0x0101010101010101ull
-         : LPB == 4  ? 0x1111111111111111ull
-         : LPB == 2  ? 0x5555555555555555ull
-                     : ~0ull;
 }
 
 // Plan of a wave's blocks: each row's mu and plan byte (both left by the

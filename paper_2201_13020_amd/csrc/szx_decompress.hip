@@ -11,12 +11,13 @@
 //             2-bit code shares, and a second light prefix sum gives the first
 //             mid byte of every decode tile (Sec. V-B locates the mid bytes by
 //             a prefix sum of these counts before they are read).
-//   k_decode  every decode tile on its own, no waiting: it stages its mid bytes
-//             in LDS with aligned 16-byte loads, resolves leading bytes -- byte
-//             j of value i is the stored byte j of the nearest value i' <= i
-//             whose code stores byte j (Sec. V-B, index propagation) -- with one
-//             inclusive scan over (code, top bytes) pairs under the associative
-//             operator (c_a, S_a) . (c_b, S_b) = (min(c_a, c_b),
+//   k_decode  every wave of a decode tile on its own, no waiting: it stages its
+//             mid bytes in LDS with aligned 16-byte loads, resolves leading
+//             bytes -- byte j of value i is the stored byte j of the nearest
+//             value i' <= i whose code stores byte j (Sec. V-B, index
+//             propagation) -- lane by lane, then across the lanes of a block
+//             with one inclusive scan over (code, top bytes) pairs under the
+//             associative operator (c_a, S_a) . (c_b, S_b) = (min(c_a, c_b),
 //             (S_a & top(c_b)) | S_b), and writes x' = mu + (q' << s);
 //             constant blocks get mu, raw blocks their stored bytes.
 // Every read of the stream is bounded by in_bytes; a malformed stream sets
@@ -35,7 +36,11 @@ constexpr uint32_t kDirectRankTiles = 256;  // index tiles that count their firs
 // Field of a call, or of a batch entry (a copy with its pointers typed as
 // global memory).
 __device__ __forceinline__ FieldD field_at(const DBatch& b, uint32_t fi) {
-  FieldD f = b.fields ? b.fields[fi] : b.one;
+  FieldD f;
+  if (b.fields)
+    f = *as_constant(b.fields + fi);
+  else
+    f = b.one;
   f.in = as_global(f.in);
   f.out = as_global(f.out);
   f.status = as_global(f.status);
@@ -44,7 +49,7 @@ __device__ __forceinline__ FieldD field_at(const DBatch& b, uint32_t fi) {
   f.mid_st = as_global(f.mid_st);
   return f;
 }
-__device__ __forceinline__ uint32_t dfield_of(const uint32_t* map, uint64_t t) { return map ? map[t] : 0u; }
+__device__ __forceinline__ uint32_t dfield_of(const uint32_t* map, uint64_t t) { return map ? *as_constant(map + t) : 0u; }
 
 // Only for calls without index tiles (every field empty): their status words.
 __global__ __launch_bounds__(256) void k_dinit(DBatch b) {
@@ -108,8 +113,9 @@ __device__ __forceinline__ void gate_wait(const DBatch& b, uint32_t* status) {
   __syncthreads();
 }
 
-__device__ __forceinline__ uint64_t rd64(const uint8_t* p) { return *reinterpret_cast<const uint64_t*>(p); }
-__device__ __forceinline__ uint32_t rd32(const uint8_t* p) { return *reinterpret_cast<const uint32_t*>(p); }
+// Header words (nothing writes a stream that is being decoded: scalar loads).
+__device__ __forceinline__ uint64_t rd64(const uint8_t* p) { return *as_constant(reinterpret_cast<const uint64_t*>(p)); }
+__device__ __forceinline__ uint32_t rd32(const uint8_t* p) { return *as_constant(reinterpret_cast<const uint32_t*>(p)); }
 
 // Mask of the top c bytes (c in [0, 3]) of the 24-bit leading field kept in
 // bits 31..8, branch-free: the field's mask shifted left by 8 (3 - c).
@@ -123,105 +129,68 @@ __device__ __forceinline__ uint32_t lead_compose(uint32_t a, uint32_t b) {
   return s | (ca < cb ? ca : cb);
 }
 
-template <typename U>
-__device__ __forceinline__ uint32_t top24(U q) {
-  return (uint32_t)(q >> (sizeof(U) * 8 - 32)) & 0xFFFFFF00u;
-}
-template <typename U>
-__device__ __forceinline__ U from_top24(uint32_t t) {
-  return (U)t << (sizeof(U) * 8 - 32);
-}
-
-// Read L <= sizeof(U) bytes at byte offset off of the staged stream; the first
-// byte lands in the low byte of the result.
-__device__ __forceinline__ uint32_t lds_get32(const uint32_t* stage, uint32_t off) {
-  const uint32_t d = off >> 2, sh = (off & 3u) * 8u;
-  const uint64_t v = (uint64_t)stage[d] | ((uint64_t)stage[d + 1] << 32);
-  return (uint32_t)(v >> sh);
-}
-__device__ __forceinline__ uint64_t lds_get64(const uint32_t* stage, uint32_t off) {
-  const uint32_t d = off >> 2, sh = (off & 3u) * 8u;
-  const uint64_t lo = (uint64_t)stage[d] | ((uint64_t)stage[d + 1] << 32);
-  const uint64_t hi = stage[d + 2];
-  return sh ? ((lo >> sh) | (hi << (64u - sh))) : lo;
-}
-template <typename U>
-__device__ __forceinline__ U lds_get(const uint32_t* stage, uint32_t off);
-template <>
-__device__ __forceinline__ uint32_t lds_get<uint32_t>(const uint32_t* stage, uint32_t off) {
-  return lds_get32(stage, off);
-}
-template <>
-__device__ __forceinline__ uint64_t lds_get<uint64_t>(const uint32_t* stage, uint32_t off) {
-  return lds_get64(stage, off);
-}
-
-// The top c bytes of a word, from s8 = 8 c (c in [0, 3]): the complement of
-// the all-ones word shifted right by s8.
-template <typename U>
-__device__ __forceinline__ U top_bytes_of(uint32_t s8) {
-  return (U)~((U)~(U)0 >> s8);
-}
-
-// Bytes of a decode tile's LDS stage: the tile's mid bytes at most (a value
-// stores at most its width), the 15-byte misalignment of their start and the
-// round-up to whole 16-byte chunks, then room for the unguarded reads of a
-// lane: it starts at most at the end of all stored bytes, advances at most a
-// word per value before its last read, and a read takes up to 12 bytes.
+// Geometry of the decode pass: a workgroup's tile is about 16 KiB of values (at
+// least 8 blocks, so that it owns whole state bytes), each of its four waves a
+// contiguous quarter of it, in SUB rows (mostly one) of EPL consecutive values
+// a lane. Sixteen float32 values a lane share the per-row work among twice the
+// values of eight (with eight, and tiles of 8 KiB: 42 us where sixteen take 35).
+constexpr uint32_t kStageHead = 16;
 template <typename T, int B>
-constexpr int dec_stage_words() {
-  using G = GeoD<T, B>;
-  return (G::TILE * G::SUB * (int)sizeof(T) + 32 + G::EPL * (int)sizeof(T) + 16) / 4;
+struct DecGeo {
+  static constexpr int EPL = (int)lane_values(B, sizeof(T));
+  static constexpr int LPB = B / EPL;       // lanes per block
+  static constexpr int GPW = kWave / LPB;   // blocks per row
+  static constexpr int ROW = kWave * EPL;   // values per row
+  static constexpr int TBLK = (int)dec_blocks(B, sizeof(T));
+  static constexpr int WBLK = TBLK / kWavesPerWG;  // blocks per wave
+  static constexpr int SUB = WBLK / GPW;    // rows per wave
+  static constexpr uint32_t MOST = (uint32_t)(ROW * SUB * (int)sizeof(T));  // mid bytes of a wave
+  // the wave's LDS stage: kStageHead bytes that reads before the first mid
+  // byte may touch, its mid bytes at most, the 15-byte misalignment of
+  // their start and the round-up to whole 16-byte chunks, then room for the
+  // unguarded reads of a lane: it starts at most at the end of all stored
+  // bytes, advances at most a word per value before its last read, and a read
+  // takes up to 12 bytes
+  static constexpr uint32_t STAGE = kStageHead + MOST + 32u + (uint32_t)(EPL * (int)sizeof(T)) + 16u;
+  static_assert(LPB >= 1 && LPB <= 64 && SUB * GPW * kWavesPerWG == TBLK, "whole rows");
+  static_assert(STAGE % 16 == 0, "stages start 16-byte aligned");
+  // Waves per SIMD, as the LDS allows; sixteen float32 values a lane take 76
+  // registers, so six (held to eight waves they spill: 35 -> 50 us for the
+  // decompression of the 100x500x500 float32 field at REL 1e-3).
+  static constexpr int WAVES = STAGE > 17000u ? 2 : STAGE > 5000u ? 4 : sizeof(T) == 4 && EPL == 16 ? 6 : 8;
+};
+
+// Four bytes at LDS byte offset off of the staged stream, the first in the low
+// byte: two aligned dwords and a byte funnel shift (an unaligned LDS read takes
+// a clock a lane, 64 against 9).
+__device__ __forceinline__ uint32_t stage_get(const uint8_t* stage, uint32_t off) {
+  const uint32_t* p = reinterpret_cast<const uint32_t*>(stage + (off & ~3u));
+  return __builtin_amdgcn_alignbyte(p[1], p[0], off);
 }
 
-// Previous lane's value within groups of G lanes (lanes with lig < d get
-// garbage, which callers discard): DPP row shifts for G <= 16.
+// The lane's codes with those of values past cn cleared (first value in the
+// top bits).
+template <int EPL>
+__device__ __forceinline__ uint32_t valid_codes(uint32_t c, int cn) {
+  return c & (uint32_t)(((1ull << (2 * cn)) - 1) << (2 * (EPL - cn)));
+}
+
+// Smallest of a lane's EPL two-bit codes.
+template <int EPL>
+__device__ __forceinline__ uint32_t min_code(uint32_t c) {
+  constexpr uint32_t LO = EPL == 16 ? 0x55555555u : 0x5555u;
+  const uint32_t hi = (c >> 1) & LO, lo = c & LO;
+  return hi == LO ? (lo == LO ? 3u : 2u) : ((hi | lo) == LO ? 1u : 0u);
+}
+
+// D lanes before, within groups of G lanes (lanes with lig < D get garbage,
+// which callers discard): DPP row shifts for G <= 16.
 template <int G, int D>
 __device__ __forceinline__ uint32_t lane_up(uint32_t v) {
   if constexpr (G <= 16) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + D, 0xF, 0xF, false);  // row_shr:D
   } else {
     return __shfl_up(v, D, G);
-  }
-}
-
-template <typename T, int EPL>
-__device__ __forceinline__ void store_run(T* __restrict__ y, uint64_t i0, int cnt, const T (&v)[EPL]) {
-  if (cnt == EPL) {
-    constexpr int PER16 = 16 / sizeof(T);
-    uint4* p = reinterpret_cast<uint4*>(y + i0);
-#pragma unroll
-    for (int c = 0; c < EPL / PER16; ++c) {
-      uint4 u;
-      if constexpr (sizeof(T) == 4) {
-        u.x = __float_as_uint(v[c * 4 + 0]);
-        u.y = __float_as_uint(v[c * 4 + 1]);
-        u.z = __float_as_uint(v[c * 4 + 2]);
-        u.w = __float_as_uint(v[c * 4 + 3]);
-      } else {
-        const uint64_t a = (uint64_t)__double_as_longlong(v[c * 2 + 0]);
-        const uint64_t b = (uint64_t)__double_as_longlong(v[c * 2 + 1]);
-        u.x = (uint32_t)a;
-        u.y = (uint32_t)(a >> 32);
-        u.z = (uint32_t)b;
-        u.w = (uint32_t)(b >> 32);
-      }
-      if constexpr (sizeof(T) == 4) {
-        // streamed past the caches: the values are not read again here, and
-        // the field's other passes keep the cache. (Each store of a wave
-        // covers 16 bytes of every 32; float64 lanes, 16 of every 64, ran
-        // four times slower this way and keep ordinary stores.)
-        using v4u = unsigned int __attribute__((ext_vector_type(4)));
-        const v4u nv = {u.x, u.y, u.z, u.w};
-        __builtin_nontemporal_store(nv, reinterpret_cast<v4u*>(p + c));
-      } else {
-        p[c] = u;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < EPL; ++i)
-      if (i < cnt) y[i0 + i] = v[i];
   }
 }
 
@@ -321,16 +290,27 @@ __device__ __forceinline__ uint32_t block_mid_bytes(const BlockCodes<B>& c, uint
   return nk * nb - sum;
 }
 
+// An entry of the decode tiles' index: the tile's first mid byte (48 bits) and
+// first rank (32), and the mid bytes before its waves 1, 2 and 3 (16 bits
+// each: a tile holds at most 64 KiB).
+__device__ __forceinline__ void index_store(uint64_t* e, uint64_t mid, uint64_t rank, uint32_t w1, uint32_t w2,
+                                            uint32_t w3) {
+  *reinterpret_cast<ulonglong2*>(e) =
+      make_ulonglong2(mid | ((uint64_t)w1 << 48), rank | ((uint64_t)w2 << 32) | ((uint64_t)w3 << 48));
+}
+constexpr uint64_t kIndexMid = (1ull << 48) - 1;
+
 // Per tile of CLS blocks (four per thread): ranks of the non-constant blocks
-// and mid bytes, each through a light single-pass prefix sum; writes the first
-// rank and first mid byte of every decode tile in it.
+// and mid bytes, each through a light single-pass prefix sum; writes the index
+// entry of every decode tile in it.
 template <typename T, int B>
 __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, uint32_t t, uint32_t* s_scan,
-                                            uint64_t* s_r0p, uint64_t* s_m0p, int* s_flag) {
+                                            uint64_t* s_r0p, uint64_t* s_m0p, uint32_t* s_wave, int* s_flag) {
   constexpr int BYTES = Traits<T>::BYTES;
   constexpr int CLS = (int)kClsBlocks;
   constexpr int BPT = CLS / kWG;
-  static_assert(GeoD<T, B>::TBLK % BPT == 0, "every decode tile starts at some thread's first block");
+  using D = DecGeo<T, B>;
+  static_assert(D::TBLK % BPT == 0 && CLS % D::TBLK == 0, "every decode tile starts at some thread's first block");
   uint64_t& s_r0 = *s_r0p;
   uint64_t& s_m0 = *s_m0p;
   const StreamInfo h = read_header<BYTES, B>(a);
@@ -413,10 +393,11 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
     // they are counted, which keeps their registers in bounds
     if constexpr (B <= 128) load_codes<B>(rc_, live ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i]);
   }
-  uint32_t mid = 0;
+  uint32_t mid = 0, midb[BPT];
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
     const uint64_t k = k0 + i;
+    midb[i] = mid;  // the thread's mid bytes before its block i
     if ((ncb >> i) & 1u) {
       const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
       if ((uint64_t)rl < have_nc) {
@@ -435,18 +416,21 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
     const uint64_t p = lookback_resolve_n(a.mid_st, t, tmid, a.status, kStatusDevice, ntiles);
     if (threadIdx.x == 0) s_m0 = p;
   }
+  // mid bytes before every wave of a decode tile, within this tile
+#pragma unroll
+  for (int i = 0; i < BPT; ++i)
+    if ((threadIdx.x * BPT + i) % D::WBLK == 0) s_wave[(threadIdx.x * BPT + i) / D::WBLK] = mex + midb[i];
   __syncthreads();
   const uint64_t M0 = s_m0;
-  constexpr int DTBLK = GeoD<T, B>::TBLK;  // index entries per decode tile
-  if ((k0 % DTBLK) == 0 && k0 < a.nblk) {
-    a.index[2 * (k0 / DTBLK)] = R0 + rex;
-    a.index[2 * (k0 / DTBLK) + 1] = M0 + mex;
+  if ((k0 % D::TBLK) == 0 && k0 < a.nblk) {
+    const uint32_t w = threadIdx.x * BPT / D::WBLK;
+    const uint32_t m = s_wave[w];
+    index_store(a.index + 2 * (k0 / D::TBLK), M0 + m, R0 + rex, s_wave[w + 1] - m, s_wave[w + 2] - m, s_wave[w + 3] - m);
   }
   if (t == ntiles - 1 && threadIdx.x == 0) {
     if (R0 + tnc != h.n_nc || M0 + tmid != h.mid_total) bad = true;
     // the end of the last decode tile
-    a.index[2 * cdiv(a.nblk, DTBLK)] = h.n_nc;
-    a.index[2 * cdiv(a.nblk, DTBLK) + 1] = h.mid_total;
+    index_store(a.index + 2 * cdiv(a.nblk, D::TBLK), h.mid_total, h.n_nc, 0, 0, 0);
   }
   if (__ballot(bad) != 0 && lane_id() == 0) atomicMax(a.status, kStatusCorrupt);
 }
@@ -455,307 +439,363 @@ template <typename T, int B>
 __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
   __shared__ uint32_t s_scan[2 * kWavesPerWG];
   __shared__ uint64_t s_r0, s_m0;
+  __shared__ uint32_t s_wave[kClsBlocks / DecGeo<T, B>::WBLK];
   __shared__ int s_flag;
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_idx[Traits<T>::BYTES / 8], g));
-  dindex_tile<T, B>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, &s_flag);
+  dindex_tile<T, B>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
 }
 
+// One decode tile, each wave its quarter by itself: no barrier, nothing shared.
+//
+// Bound: the stream's reads and the values' writes (100x500x500 float32 at REL
+// 1e-3: 41 MB in and 100 MB out, 27 us at the copy rate of 5.2 TB/s; measured
+// 24 us, part of the stream coming from the last-level cache; 31.5 us with four
+// barriers a tile, byte masks a value and gaps in every store). 2^28 float64
+// values at REL 1e-5: 456 us (533), the copy rate as well.
 template <typename T, int B>
-__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, uint32_t* s_scan, uint32_t* s_stage) {
+__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, uint8_t* s_stage) {
   using U = typename Traits<T>::U;
-  using G = GeoD<T, B>;
-  constexpr int EPL = G::EPL, LPB = G::LPB, TB = G::TB, SUB = G::SUB, TBLK = G::TBLK;
+  using G = DecGeo<T, B>;
+  constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB, TBLK = G::TBLK;
   constexpr int BYTES = Traits<T>::BYTES;
+  using v4u = unsigned int __attribute__((ext_vector_type(4)));
 
   const StreamInfo h = read_header<BYTES, B>(a);
   if (!h.ok) return;  // k_dindex reported it
-  const uint32_t ntiles = (uint32_t)cdiv(a.nblk, TBLK);
-  if (t >= ntiles) return;
   const uint8_t* in = a.in;
-  const int g = threadIdx.x / LPB, lig = threadIdx.x % LPB;
-  const int lane = lane_id();
-  const T* mus = reinterpret_cast<const T*>(in + h.sec.mu);
-  T* y = reinterpret_cast<T*>(a.out);
+  const uint32_t wave = uniform(threadIdx.x / kWave);
+  const uint32_t lane = (uint32_t)lane_id(), lig = lane % LPB;
+  uint8_t* const stage = s_stage + wave * G::STAGE;
   bool bad = false;
 
-  // the tile's mid bytes: [m0, m1) of the mid section, staged as soon as known
-  const uint64_t r0 = a.index[2 * t];
-  const uint64_t m0 = a.index[2 * t + 1];
-  uint64_t m1 = a.index[2 * t + 3];
-  if (m1 < m0 || m1 - m0 > (uint64_t)G::TILE * SUB * BYTES) {
-    bad = true;
-    m1 = m0;
-  }
-  const uint32_t tile_bytes = (uint32_t)(m1 - m0);
-  const uint64_t src = h.sec.mid + m0;
-  const uint32_t st = (uint32_t)(src & 15u);
-  {
-    // 64-bit positions stay with the tile (wave-uniform); lanes use 32-bit
-    // offsets from them
-    const uint64_t src0 = src - st;
-    const uint8_t* base = in + src0;
-    const uint64_t left = a.in_bytes > src0 ? a.in_bytes - src0 : 0;
-    const uint32_t avail = (uint32_t)std::min<uint64_t>(left, 0xFFFFFFFFull);
-    const uint32_t nchunk = (st + tile_bytes + 15) / 16;
-    // every chunk of this thread's loads first, then the one chunk that
-    // holds the stream's end byte by byte (no read past in_bytes), then the
-    // stores to LDS: loads return in order, so a store waiting on its chunk
-    // between loads would hold back the next chunk's load
-    constexpr uint32_t NCH = ((15u + (uint32_t)(G::TILE * G::SUB * BYTES) + 15u) / 16u + kWG - 1u) / kWG;
-    uint4 u[NCH];
-#pragma unroll
-    for (uint32_t j = 0; j < NCH; ++j) {
-      const uint32_t ch = threadIdx.x + j * kWG;
-      u[j] = make_uint4(0, 0, 0, 0);
-      if (ch < nchunk && ch * 16 + 16 <= avail) u[j] = *reinterpret_cast<const uint4*>(base + ch * 16);
-    }
-#pragma unroll
-    for (uint32_t j = 0; j < NCH; ++j) {
-      const uint32_t ch = threadIdx.x + j * kWG;
-      if (ch < nchunk && ch * 16 + 16 > avail) {
-        const uint32_t off = ch * 16;
-        uint32_t wv[4] = {0, 0, 0, 0};
-        for (uint32_t bq = 0; bq < 16; ++bq)
-          if (off + bq < avail) wv[bq >> 2] |= (uint32_t)base[off + bq] << ((bq & 3) * 8);
-        u[j] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-      }
-    }
-#pragma unroll
-    for (uint32_t j = 0; j < NCH; ++j) {
-      const uint32_t ch = threadIdx.x + j * kWG;
-      if (ch < nchunk) reinterpret_cast<uint4*>(s_stage)[ch] = u[j];
-    }
-  }
-
-  // the tile's first block and value (wave-uniform), its block and value
-  // counts; lanes index from them with 32-bit offsets
+  // the tile's first block, its block and value counts (wave-uniform); lanes
+  // index from them with 32-bit offsets
   const uint64_t kb = (uint64_t)t * TBLK;
   const uint32_t nblk_t = (uint32_t)std::min<uint64_t>(a.nblk - kb, (uint64_t)TBLK);
   const uint32_t nval_t = (uint32_t)std::min<uint64_t>(a.n - kb * B, (uint64_t)TBLK * B);
-  const uint8_t* state_t = in + h.sec.state + (kb >> 3);  // a tile owns whole state bytes
-  const T* mus_t = mus + kb;
-  T* y_t = y + kb * B;
+  const bool tail = nval_t != (uint32_t)(TBLK * B);
 
-  // ranks of the tile's non-constant blocks, their K bytes and codes
-  bool nc[SUB];
-  int cnt[SUB];
-  uint32_t first_of[SUB];
-  T mu[SUB];
-  // every row's state byte and mu load before any is used (loads return in
-  // order: a row's loads issued after the previous row's use would wait)
-  uint32_t sbyte[SUB];
+  // State bits: of the lane's block in every row, and of the tile's blocks
+  // before the wave (one block a lane where the tile has no more blocks than
+  // a wave lanes, else words of 32). mu. All before anything waits.
+  const __amdgpu_buffer_rsrc_t rst = buffer_of(in + h.sec.state + (kb >> 3), (nblk_t + 7) / 8);
+  const __amdgpu_buffer_rsrc_t rmu =
+      buffer_of(reinterpret_cast<const T*>(in + h.sec.mu) + kb, nblk_t * (uint32_t)sizeof(T));
+  uint32_t ahead, sbyte[SUB];
+  if constexpr (TBLK <= kWave) {
+    ahead = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rst, (int)(lane >> 3), 0, 0);
+  } else {
+    ahead = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+        buffer_of(in + h.sec.state + (kb >> 3), (nblk_t + 31) / 32 * 4), (int)(lane * 4u), 0, 0);
 #pragma unroll
-  for (int s = 0; s < SUB; ++s) {
-    const uint32_t lk = (uint32_t)(s * TB + g);
-    sbyte[s] = 0;
-    mu[s] = (T)0;
-    if (lk < nblk_t) {
-      sbyte[s] = state_t[lk >> 3];
-      mu[s] = mus_t[lk];
+    for (int s = 0; s < SUB; ++s)
+      sbyte[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(
+          rst, (int)((wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / LPB) >> 3), 0, 0);
+  }
+  T mu[SUB];
+#pragma unroll
+  for (int s = 0; s < SUB; ++s)
+    mu[s] = buffer_value<T>(rmu, (wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / LPB) * (uint32_t)sizeof(T));
+
+  // the wave's mid bytes: [m0, m1) of the mid section, from the tile's entry
+  // of the index and the next one's
+  const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
+  const uint64_t e0 = e[0], e1 = e[1], e2 = e[2];
+  const uint64_t r0_t = e1 & 0xFFFFFFFFull;
+  const uint64_t m0_t = e0 & kIndexMid;
+  const uint32_t w1 = (uint32_t)(e0 >> 48), w2 = (uint32_t)(e1 >> 32) & 0xFFFFu, w3 = (uint32_t)(e1 >> 48);
+  const uint64_t m0 = m0_t + (wave == 0 ? 0u : wave == 1 ? w1 : wave == 2 ? w2 : w3);
+  uint64_t m1 = wave == 3 ? e2 & kIndexMid : m0_t + (wave == 0 ? w1 : wave == 1 ? w2 : w3);
+  if (m1 < m0 || m1 - m0 > (uint64_t)G::MOST || h.sec.mid + m1 > a.in_bytes) {
+    bad = true;
+    m1 = m0;
+  }
+  const uint32_t wbytes = (uint32_t)(m1 - m0);
+  const uint64_t src = h.sec.mid + m0;
+  const uint32_t st = (uint32_t)(src & 15u);
+  // Staged with 16-byte loads, all of them before the stores to LDS (loads
+  // return in order). The chunk that holds the stream's end goes byte by byte:
+  // nothing is read past in_bytes.
+  constexpr uint32_t NCH = ((15u + G::MOST + 15u) / 16u + kWave - 1u) / kWave;
+  v4u u[NCH];
+  {
+    const uint8_t* base = in + (src - st);
+    const uint32_t nchunk = wbytes ? (st + wbytes + 15u) / 16u : 0u;
+    const uint64_t room = a.in_bytes - (src - st);
+    const uint32_t nwhole = (uint32_t)std::min<uint64_t>(room / 16u, (uint64_t)nchunk);
+    const __amdgpu_buffer_rsrc_t rs = buffer_of(base, nwhole * 16u);
+#pragma unroll
+    for (uint32_t j = 0; j < NCH; ++j) {
+      if (j * kWave < nwhole)  // wave-uniform
+        u[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((lane + j * kWave) * 16u), 0, 0);
+    }
+    if (nwhole < nchunk && lane < (uint32_t)(room - nwhole * 16u)) stage[kStageHead + nwhole * 16u + lane] = base[nwhole * 16u + lane];
+#pragma unroll
+    for (uint32_t j = 0; j < NCH; ++j) {
+      if (lane + j * kWave < nwhole) reinterpret_cast<v4u*>(stage + kStageHead)[lane + j * kWave] = u[j];
     }
   }
-#pragma unroll
-  for (int s = 0; s < SUB; ++s) {
-    const uint32_t lk = (uint32_t)(s * TB + g);
-    const bool inb = lk < nblk_t;
-    nc[s] = inb && ((sbyte[s] >> (lk & 7)) & 1u);
-    // values from this lane's first one to the tile's end
-    const int rem = (int)nval_t - (int)(lk * B) - lig * EPL;
-    cnt[s] = inb ? (rem < 0 ? 0 : (rem > EPL ? EPL : rem)) : 0;
-    first_of[s] = (lig == 0 && nc[s]) ? 1u : 0u;
+
+  wave_sync();
+
+  // ranks of the wave's non-constant blocks, their K bytes and codes
+  uint64_t tile_nc = 0;  // the tile's blocks, one bit each (TBLK <= 64)
+  uint32_t wrank;        // rank of the wave's first block, within the tile
+  if constexpr (TBLK <= kWave) {
+    tile_nc = __ballot(lane < nblk_t && ((ahead >> (lane & 7u)) & 1u));
+    wrank = (uint32_t)__popcll(tile_nc & ((1ull << (wave * G::WBLK)) - 1ull));
+  } else {
+    const int left = (int)(wave * G::WBLK) - (int)lane * 32;
+    const uint32_t mask = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
+    wrank = wave_total_u32((uint32_t)__popc(ahead & mask));
   }
-  uint32_t rk[SUB], rtot[SUB];
-  wg_excl_scan_multi<SUB>(first_of, rk, rtot, s_scan);
-  int Ks[SUB];       // kept bits; -1 raw; 0 constant or unusable
-  uint32_t cw[SUB];  // this lane's EPL codes, first value in the top bits
-  uint32_t nbytes[SUB];
-  // ranks from r0 on, 32-bit within the tile
-  const uint32_t nnc_t = (uint32_t)std::min<uint64_t>(h.n_nc > r0 ? h.n_nc - r0 : 0, (uint64_t)TBLK);
-  const uint8_t* kbytes_t = in + h.sec.kbytes + r0;
-  const uint8_t* codes_t = in + h.sec.codes + r0 * (B / 4);
-  // every row's K byte and codes first (loads return in order: a row's
-  // loads issued after the previous row's use would wait on them)
+  // what the stream holds of the tile's ranks
+  const uint32_t nnc_t = (uint32_t)std::min<uint64_t>(h.n_nc > r0_t ? h.n_nc - r0_t : 0, (uint64_t)TBLK);
+  const __amdgpu_buffer_rsrc_t rk = buffer_of(in + h.sec.kbytes + r0_t, nnc_t);
+  const __amdgpu_buffer_rsrc_t rc = buffer_of(in + h.sec.codes + r0_t * (B / 4), nnc_t * (uint32_t)(B / 4));
+  bool nc[SUB];
   uint32_t kraw[SUB], craw[SUB];
 #pragma unroll
   for (int s = 0; s < SUB; ++s) {
-    const uint32_t rl = rk[s] - ((lig != 0 && nc[s]) ? 1u : 0u);
-    const bool have = nc[s] && rl < nnc_t;
-    kraw[s] = have ? (uint32_t)kbytes_t[rl] : 0u;
-    craw[s] = 0;
-    if (have) {  // loaded beside K, used only for a coded block
-      const uint8_t* cp = codes_t + rl * (B / 4) + (uint32_t)lig * (EPL / 4);
-      if constexpr (EPL == 8) {
-        craw[s] = *reinterpret_cast<const uint16_t*>(cp);  // byte order fixed below
-      } else {
-        uint32_t c = 0;
-#pragma unroll
-        for (int j = 0; j < EPL / 4; ++j) c = (c << 8) | cp[j];
-        craw[s] = c;
-      }
-    }
+    const uint32_t lk = wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / LPB;
+    if constexpr (TBLK <= kWave)
+      nc[s] = (tile_nc >> lk) & 1u;
+    else
+      nc[s] = lk < nblk_t && ((sbyte[s] >> (lk & 7u)) & 1u);
+    const uint64_t firsts = __ballot(nc[s]) & first_lanes<LPB>();
+    // the group's first lane does not count its own block; the others see it
+    // counted
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, wrank - (lig != 0 ? 1u : 0u)));
+    wrank += (uint32_t)__popcll(firsts);
+    bad = bad || (nc[s] && rank >= nnc_t);
+    kraw[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rk, (int)(nc[s] ? rank : 0x40000000u), 0, 0);
+    const uint32_t coff = nc[s] ? rank * (uint32_t)(B / 4) + lig * (EPL / 4) : 0x40000000u;
+    if constexpr (EPL == 8)
+      craw[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rc, (int)coff, 0, 0);
+    else
+      craw[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rc, (int)coff, 0, 0);
   }
+
+  uint32_t done = kStageHead + st;  // stage offset of the row's first mid byte
 #pragma unroll
   for (int s = 0; s < SUB; ++s) {
-    // the group's first lane counted its block; the others see it counted
-    const uint32_t rl = rk[s] - ((lig != 0 && nc[s]) ? 1u : 0u);
-    const bool have = nc[s] && rl < nnc_t;
-    bad = bad || (nc[s] && rl >= nnc_t);
-    int K = (int)kraw[s];
-    if (K == kRawK) {
-      K = -1;
-    } else if (have && (K < Traits<T>::KMIN || K > Traits<T>::W)) {
+    const uint32_t lk = wave * G::WBLK + (uint32_t)(s * G::GPW) + lane / LPB;
+    int cnt = EPL;
+    if (tail) {
+      const int rem = (int)nval_t - (int)(lk * B + lig * EPL);  // values from this lane's first one to the tile's end
+      cnt = rem < 0 ? 0 : (rem > EPL ? EPL : rem);
+    }
+    // kept bits K (0: constant, absent or unusable), stored bytes a value
+    uint32_t K = kraw[s];
+    const bool raw = K == kRawK;
+    if (nc[s] && !raw && ((int)K < Traits<T>::KMIN || (int)K > Traits<T>::W)) {
       bad = true;
       K = 0;
     }
-    const int nb = K > 0 ? bytes_of(K) : 0;
-    uint32_t c = craw[s];
-    if constexpr (EPL == 8) c = ((c & 0xFFu) << 8) | (c >> 8);
-    // stored bytes of the lane: nb per live value less its code. Codes of
-    // values past the end are cleared; a code above nb marks the stream bad
-    // and its row is then read as if all codes were 0, which keeps every
-    // offset within the stage.
-    const int cn = cnt[s];
-    uint32_t lb = 0;
-    if (K > 0) {
-      c &= (uint32_t)(((1ull << (2 * cn)) - 1) << (2 * (EPL - cn)));
+    if (raw) K = 0;
+    uint32_t nb = (K + 7u) >> 3;
+    const uint32_t sh = 8u * nb - K;
+    uint32_t c;  // the lane's codes, first value in the top bits
+    if constexpr (EPL == 8)
+      c = ((craw[s] & 0xFFu) << 8) | (craw[s] >> 8);
+    else
+      c = __builtin_bswap32(craw[s]);
+    // Codes of values past the end are cleared; a code above nb marks the
+    // stream bad and its lane is then read as if all codes were 0, which
+    // keeps every offset within the stage.
+    if (tail) c = valid_codes<EPL>(c, cnt);
+    c = K ? c : 0u;
+    if (__ballot(K && nb < 3u) != 0) {
       const uint32_t hi = c & 0xAAAAAAAAu, lo = c & 0x55555555u;
-      const bool over = (nb == 1 && hi != 0) || (nb == 2 && (lo & (hi >> 1)) != 0);
+      const bool over = K && ((nb == 1u && hi != 0) || (nb == 2u && (lo & (hi >> 1)) != 0));
       bad = bad || over;
       c = over ? 0u : c;
-      lb = (uint32_t)(nb * cn) - (uint32_t)(__popc(c & 0x55555555u) + 2 * __popc(c & 0xAAAAAAAAu));
-    } else {
-      c = 0;
-      lb = K < 0 ? (uint32_t)(BYTES * cn) : 0u;
     }
-    Ks[s] = K;
-    cw[s] = c;
-    nbytes[s] = lb;
-  }
-  uint32_t off[SUB], tot[SUB];
-  wg_excl_scan_multi<SUB>(nbytes, off, tot, s_scan);  // its barriers also cover the staging
-  uint32_t sum = 0;
-#pragma unroll
-  for (int s = 0; s < SUB; ++s) sum += tot[s];
-  if (sum != tile_bytes) bad = true;
+    const bool some_raw = __ballot(raw) != 0;
+    if (some_raw) nb = raw ? (uint32_t)BYTES : nb;
+    // stored bytes of the lane, and its first one's place in the stage
+    const uint32_t lb =
+        (uint32_t)__umul24(nb, (uint32_t)cnt) - ((uint32_t)__popc(c) + (uint32_t)__popc(c & 0xAAAAAAAAu));
+    const uint32_t inc = wave_incl_sum_u32(lb);
+    uint32_t o = done + inc - lb;
+    done += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
 
-  // values, row by row
-#pragma unroll
-  for (int s = 0; s < SUB; ++s) {
-    const int K = Ks[s];
-    T v[EPL];
-    uint32_t o = st + off[s];
-    // Reads of the stage go unguarded: a lane starts at most at the end of
-    // the tile's stored bytes and advances at most a word per value, which
+    // Values. Reads of the stage go unguarded: a lane starts at most at the end
+    // of the wave's stored bytes and advances at most a word per value, which
     // the stage's size allows for. Values past the end of a short block read
     // whatever lies there and are not stored; being last in their lane and
-    // block, they only reach other such values.
-    if (K == 0) {  // constant: mu
+    // block, they only reach other such values. (Lanes of constant blocks run
+    // along with nb = 0.)
+    const uint32_t nbh = nb < 4u ? nb : 4u;
+    const bool longer = sizeof(T) == 8 && __ballot(nb > 4u) != 0;  // some value stores bytes of its low word
+    uint32_t got[EPL], gotl[sizeof(T) == 8 ? EPL : 1], own[EPL];
+    uint32_t run = 0;
+    const uint32_t o0 = o;
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) v[i] = mu[s];
-    } else if (K < 0) {  // raw: the stored words
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) v[i] = from_bits<T>(lds_get<U>(s_stage, o + (uint32_t)(i * BYTES)));
-    } else {
-      const int nb = bytes_of(K);
-      const int sh = shift_of(K);
-      const U keep = top_bytes_mask<U>(nb);
-      U q0[EPL];
-      uint32_t cmin[EPL];
-      U run = 0;
-      uint32_t cm = 3;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        // ci <= nb here (checked above), so the value stores nb - ci bytes
-        const uint32_t ci = (cw[s] >> (2 * (EPL - 1 - i))) & 3u;
-        const uint32_t s8 = ci << 3;
-        // the word at o holds this value's stored bytes, then whatever
-        // follows; after the shift and byte swap those land below the kept
-        // bytes, where `keep` clears them at the end (ci <= 3: shift < 32)
-        const U got = lds_get<U>(s_stage, o);
-        o += (uint32_t)nb - ci;
-        const U stored = byte_swap((U)(got << s8));
-        run = (run & top_bytes_of<U>(s8)) | stored;
-        cm = ci < cm ? ci : cm;
-        q0[i] = run;
-        cmin[i] = cm;
+    for (int i = 0; i < EPL; ++i) {
+      // o: where the value's word would start if its leading bytes were stored
+      // too, so that its stored bytes lie in place; shared bytes come from the
+      // word before, whatever follows the stored ones is cleared by `keep`
+      const uint32_t ci = (c >> (2 * (EPL - 1 - i))) & 3u;
+      o = i == 0 ? o - ci : __builtin_amdgcn_sad_u8(nb, ci, o);  // o + nb - ci
+      got[i] = __builtin_bswap32(stage_get(stage, o));
+      if constexpr (sizeof(T) == 8) {
+        if (longer) gotl[i] = stage_get(stage, o + 4u);
       }
-      // carry of the leading bytes from the lanes before this one in the
-      // block; bytes below the kept ones never reach a kept byte (every mask
-      // here keeps at most the top min(3, nb) bytes of a live value)
-      uint32_t pk = top24<U>(run) | cm;
-      {
-        uint32_t o2 = lane_up<LPB, 1>(pk);
-        pk = lig >= 1 ? lead_compose(o2, pk) : pk;
-        if constexpr (LPB > 2) {
-          o2 = lane_up<LPB, 2>(pk);
-          pk = lig >= 2 ? lead_compose(o2, pk) : pk;
-        }
-        if constexpr (LPB > 4) {
-          o2 = lane_up<LPB, 4>(pk);
-          pk = lig >= 4 ? lead_compose(o2, pk) : pk;
-        }
-        if constexpr (LPB > 8) {
-          o2 = lane_up<LPB, 8>(pk);
-          pk = lig >= 8 ? lead_compose(o2, pk) : pk;
-        }
-        if constexpr (LPB > 16) {
-          o2 = __shfl_up(pk, 16, LPB);
-          pk = lig >= 16 ? lead_compose(o2, pk) : pk;
-        }
-        if constexpr (LPB > 32) {
-          o2 = __shfl_up(pk, 32, LPB);
-          pk = lig >= 32 ? lead_compose(o2, pk) : pk;
-        }
+      own[i] = __builtin_amdgcn_alignbyte(~0u, 0u, ci);  // the top ci bytes: the shared ones
+      run = (run & own[i]) | (got[i] & ~own[i]);
+    }
+    // Leading bytes from the lanes before this one in the block: the lanes'
+    // (smallest code, top three bytes) pairs scanned under lead_compose.
+    // Bytes below the kept ones never reach a kept byte (a code keeps at most
+    // the top min(3, nb) bytes of a live value).
+    uint32_t carry = 0;
+    if constexpr (LPB > 1) {
+      uint32_t pk = (run & 0xFFFFFF00u) | min_code<EPL>(c);
+      uint32_t o2 = lane_up<LPB, 1>(pk);
+      pk = lig >= 1 ? lead_compose(o2, pk) : pk;
+      if constexpr (LPB > 2) {
+        o2 = lane_up<LPB, 2>(pk);
+        pk = lig >= 2 ? lead_compose(o2, pk) : pk;
       }
-      uint32_t carry = LPB > 1 ? lane_up<LPB, 1>(pk) & 0xFFFFFF00u : 0u;
+      if constexpr (LPB > 4) {
+        o2 = lane_up<LPB, 4>(pk);
+        pk = lig >= 4 ? lead_compose(o2, pk) : pk;
+      }
+      if constexpr (LPB > 8) {
+        o2 = lane_up<LPB, 8>(pk);
+        pk = lig >= 8 ? lead_compose(o2, pk) : pk;
+      }
+      if constexpr (LPB > 16) {
+        o2 = __shfl_up(pk, 16, LPB);
+        pk = lig >= 16 ? lead_compose(o2, pk) : pk;
+      }
+      if constexpr (LPB > 32) {
+        o2 = __shfl_up(pk, 32, LPB);
+        pk = lig >= 32 ? lead_compose(o2, pk) : pk;
+      }
+      carry = lane_up<LPB, 1>(pk) & 0xFFFFFF00u;
       carry = lig == 0 ? 0u : carry;
-      const U cfull = from_top24<U>(carry);
+    }
+    // x' = mu + (q' << s), the words once more with the carried bytes in front
+    T v[EPL];
+    run = carry;
+    if constexpr (sizeof(T) == 4) {
+      const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
-        const U qi = (q0[i] | (cfull & top_bytes_of<U>(cmin[i] << 3))) & keep;
-        v[i] = mu[s] + from_bits<T>((U)(qi << sh));
+        run = (run & own[i]) | (got[i] & ~own[i]);
+        v[i] = mu[s] + from_bits<T>((run << sh) & keep);
+      }
+    } else if (!longer) {
+      const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        run = (run & own[i]) | (got[i] & ~own[i]);
+        v[i] = mu[s] + from_bits<T>((U)((run << sh) & keep) << (sizeof(U) * 8 - 32));
+      }
+    } else {
+      const U keep = (U)(top_bytes_mask<U>((int)nb) << sh);
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        run = (run & own[i]) | (got[i] & ~own[i]);
+        const U q = ((U)run << (sizeof(U) * 8 - 32)) | (U)__builtin_bswap32(gotl[i]);
+        v[i] = mu[s] + from_bits<T>((U)(q << sh) & keep);
       }
     }
-    if constexpr (sizeof(T) == 8 && SUB == 1) {
-      // float64 tiles of one row: the values pass through the stage so that
-      // every store of a wave covers 1 KiB of the row without gaps and can
-      // stream past the caches. Value i of thread L (row value L EPL + i)
-      // sits at stage slot i kWG + L: the writes of a wave fill consecutive
-      // slots (no bank conflicts; lane-major slots put 64 lanes on two banks)
-      __syncthreads();  // every lane is done with the staged mid bytes
-      T* sv = reinterpret_cast<T*>(s_stage);
+    if (__ballot(K == 0) != 0) {
+      if (K == 0) {  // constant: mu itself (mu + 0 would lose a zero's sign)
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) sv[i * kWG + threadIdx.x] = v[i];
-      __syncthreads();
-      using v4u = unsigned int __attribute__((ext_vector_type(4)));
-      for (uint32_t c = threadIdx.x; c < (uint32_t)G::TILE / 2; c += kWG) {
-        const uint32_t i0 = 2 * c;  // row values i0 and i0 + 1 (EPL is even)
-        const uint32_t slot = (i0 % EPL) * kWG + i0 / EPL;
-        if (i0 + 2 <= nval_t) {
-          const uint64_t a = (uint64_t)__double_as_longlong(sv[slot]);
-          const uint64_t b = (uint64_t)__double_as_longlong(sv[slot + kWG]);
-          const v4u nv = {(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
-          __builtin_nontemporal_store(nv, reinterpret_cast<v4u*>(y_t + i0));
-        } else if (i0 < nval_t) {
-          y_t[i0] = sv[slot];
+        for (int i = 0; i < EPL; ++i) v[i] = mu[s];
+      }
+      if (some_raw && raw) {  // the stored words
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          const uint32_t lo = stage_get(stage, o0 + (uint32_t)(i * BYTES));
+          if constexpr (sizeof(T) == 4)
+            v[i] = from_bits<T>(lo);
+          else
+            v[i] = from_bits<T>((U)lo | ((U)stage_get(stage, o0 + (uint32_t)(i * BYTES) + 4u) << (sizeof(U) * 8 - 32)));
+        }
+      }
+    }
+
+    T* const y = reinterpret_cast<T*>(a.out) + kb * B;  // of the tile
+    const uint32_t i0 = (wave * G::WBLK + (uint32_t)(s * G::GPW)) * (uint32_t)B;  // the row's first value
+    constexpr uint32_t CH = (uint32_t)(EPL * BYTES) / 16u;  // 16-byte chunks a lane
+    if constexpr (SUB == 1) {
+      // The row passes through the stage (its mid bytes are used up), so that
+      // every store of the wave covers 1 KiB without gaps and can stream past
+      // the caches (the values are not read again here). Chunk c of lane L
+      // sits at slot L CH + (c ^ (L / (16 / CH)) mod CH): 16 lanes writing one
+      // chunk each, or reading 16 consecutive ones, touch all 64 banks.
+      v4u* const slots = reinterpret_cast<v4u*>(stage);
+      constexpr uint32_t PER = 16u / CH;
+      wave_sync();
+#pragma unroll
+      for (uint32_t k = 0; k < CH; ++k) {
+        v4u w;
+        if constexpr (sizeof(T) == 4) {
+          w = v4u{(uint32_t)bits_of(v[4 * k]), (uint32_t)bits_of(v[4 * k + 1]), (uint32_t)bits_of(v[4 * k + 2]),
+                  (uint32_t)bits_of(v[4 * k + 3])};
+        } else {
+          const U p = bits_of(v[2 * k]), q = bits_of(v[2 * k + 1]);
+          w = v4u{(uint32_t)p, (uint32_t)(p >> (sizeof(U) * 8 - 32)), (uint32_t)q, (uint32_t)(q >> (sizeof(U) * 8 - 32))};
+        }
+        slots[lane * CH + (k ^ ((lane / PER) % CH))] = w;
+      }
+      wave_sync();
+#pragma unroll
+      for (uint32_t k = 0; k < CH; ++k) {
+        const uint32_t d = k * kWave + lane;  // chunk of the row
+        const uint32_t L = d / CH;
+        const v4u w = slots[L * CH + ((d % CH) ^ ((L / PER) % CH))];
+        const uint32_t first = i0 + d * (16u / BYTES);  // its first value
+        if (!tail || first + 16u / BYTES <= nval_t) {
+          __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(y + first));
+        } else {
+          uint32_t* const yw = reinterpret_cast<uint32_t*>(y + first);
+#pragma unroll
+          for (uint32_t j = 0; j < 4; ++j)
+            if (first + j * 4u / BYTES < nval_t) yw[j] = w[j];
         }
       }
     } else {
-      if (cnt[s] > 0) store_run<T, EPL>(y_t, (uint32_t)((s * TB + g) * B + lig * EPL), cnt[s], v);
+      T* const yl = y + (i0 + lane * EPL);
+      if (cnt == EPL) {
+#pragma unroll
+        for (uint32_t k = 0; k < CH; ++k) {
+          v4u w;
+          if constexpr (sizeof(T) == 4) {
+            w = v4u{(uint32_t)bits_of(v[4 * k]), (uint32_t)bits_of(v[4 * k + 1]), (uint32_t)bits_of(v[4 * k + 2]),
+                    (uint32_t)bits_of(v[4 * k + 3])};
+          } else {
+            const U p = bits_of(v[2 * k]), q = bits_of(v[2 * k + 1]);
+            w = v4u{(uint32_t)p, (uint32_t)(p >> (sizeof(U) * 8 - 32)), (uint32_t)q,
+                    (uint32_t)(q >> (sizeof(U) * 8 - 32))};
+          }
+          reinterpret_cast<v4u*>(yl)[k] = w;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+          if (i < cnt) yl[i] = v[i];
+      }
     }
   }
+  if (done - kStageHead - st != wbytes) bad = true;
   if (__ballot(bad) != 0 && lane == 0) atomicMax(a.status, kStatusCorrupt);
 }
 
 template <typename T, int B>
-__global__ __launch_bounds__(256) void k_decode(DBatch b) {
-  using G = GeoD<T, B>;
-  __shared__ uint32_t s_scan[G::SUB * kWavesPerWG];
-  __shared__ __align__(16) uint32_t s_stage[dec_stage_words<T, B>()];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DecGeo<T, B>::WAVES))) void k_decode(DBatch b) {
+  using G = DecGeo<T, B>;
+  __shared__ __align__(16) uint8_t s_stage[kWavesPerWG * G::STAGE];
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_dec[Traits<T>::BYTES / 8], g));
-  decode_tile<T, B>(f, (uint32_t)(g - f.base_dec), s_scan, s_stage);
+  decode_tile<T, B>(f, (uint32_t)(g - f.base_dec), s_stage);
   // the call's last decode launch advances the gate's epoch (no index tile
   // reads it any more); at the end, so that no load comes after the atomic
   if (g == 0 && threadIdx.x == 0 && (sizeof(T) == 8 || b.tiles_dec[1] == 0))

@@ -65,36 +65,17 @@ struct Traits<double> {
   static constexpr int KMIN = 1 + E;
 };
 
-// Launch geometry that depends only on the block size b: each lane owns EPL
-// consecutive values, LPB lanes share one block, a 256-thread workgroup tile
-// holds TB whole blocks. It changes no output byte.
-// A tile is SUB such rows of TB blocks: about TARGET bytes of input (and at
-// least 8 blocks, so that a tile owns whole bytes of the state bits). The
-// encoder's tiles are large, so that the per-tile costs of its prefix sums
-// are rare; the decoder's are half that size, so that more workgroups fit a
-// compute unit (its tiles wait on nothing).
-constexpr int geo_sub(int tile_bytes, int tb, int target) {
-  int s = target / tile_bytes;
-  s = s < 1 ? 1 : s;
-  while (tb * s < 8) s *= 2;
-  return s;
-}
-
-template <typename T, int B, int TARGET = (int)kEncodeTileBytes>
+// Geometry of the extrema pass, by the block size b: each lane owns EPL
+// consecutive values, LPB lanes share one block, a row of a 256-thread
+// workgroup holds TB whole blocks. It changes no output byte.
+template <typename T, int B>
 struct Geo {
   static constexpr int EPL = B >= 512 ? B / 64 : 8;
   static constexpr int LPB = B / EPL;  // 1..64, divides 64
   static constexpr int TB = kWG / LPB;
   static constexpr int TILE = TB * B;  // values per row
-  static constexpr int SUB = geo_sub(TILE * (int)sizeof(T), TB, TARGET);
-  static constexpr int TBLK = TB * SUB;  // blocks per tile
   static_assert(LPB >= 1 && LPB <= 64 && (64 % LPB) == 0, "group must fit a wave");
-  static_assert(TBLK % 8 == 0, "a tile owns whole state bytes");
 };
-
-// Decoder tiles (each a whole number of them per encode tile).
-template <typename T, int B>
-using GeoD = Geo<T, B, (int)kDecodeTileBytes>;
 
 __device__ __forceinline__ uint32_t bits_of(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint64_t bits_of(double v) { return (uint64_t)__double_as_longlong(v); }
@@ -254,6 +235,15 @@ __device__ __forceinline__ uint64_t byte_swap(uint64_t v) { return __builtin_bsw
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// Orders a wave's LDS accesses: what its lanes stored before is there for its
+// other lanes' loads after (the LDS serves a wave in order, so this only holds
+// the compiler).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Inclusive sum of 32-bit values over the 64 lanes of a wave with DPP: row
 // shifts by 1, 2, 4, 8 within each row of 16 lanes, then the last lane of
 // rows 0 and 2 added to rows 1 and 3 (row_bcast:15) and the last lane of row 1
@@ -299,6 +289,42 @@ __device__ __forceinline__ U lane_before(U v) {
   } else {
     return __shfl_up(v, 1, G);
   }
+}
+
+// A wave-uniform value held in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
+
+// Lanes that begin a group of LPB.
+template <int LPB>
+__device__ __forceinline__ constexpr uint64_t first_lanes() {
+  return LPB == 64   ? 1ull
+         : LPB == 32 ? 0x0000000100000001ull
+         : LPB == 16 ? 0x0001000100010001ull
+         : LPB == 8  ? 0x0101010101010101ull
+         : LPB == 4  ? 0x1111111111111111ull
+         : LPB == 2  ? 0x5555555555555555ull
+                     : ~0ull;
+}
+
+// A buffer resource over bytes bytes at p: reads past them return zeros and
+// stores past them do nothing, without touching memory.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t rs, uint32_t off);
+template <>
+__device__ __forceinline__ float buffer_value<float>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+}
+template <>
+__device__ __forceinline__ double buffer_value<double>(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  using v2u = unsigned int __attribute__((ext_vector_type(2)));
+  const v2u u = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+  return __longlong_as_double((long long)(((uint64_t)u.y << 32) | u.x));
 }
 
 // Inclusive sum over groups of G consecutive lanes (G a power of two <= 64).

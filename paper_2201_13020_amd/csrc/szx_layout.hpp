@@ -69,34 +69,24 @@ struct Job {
   uint32_t w;
 };
 
-// Input bytes per tile of the encode and of the decode pass (targets; a decode
-// tile is a whole number of rows and at least 8 blocks).
+// Input bytes per tile of the encode and of the decode pass (a tile is at least
+// 8 blocks, so that it owns whole bytes of the state bits).
 constexpr uint32_t kEncodeTileBytes = 32768;
 constexpr uint32_t kDecodeTileBytes = 16384;
 
-// Blocks per tile of about `target` input bytes (the decode pass) for block
-// size b and element size w (mirrors Geo in szx_device.hpp).
-__host__ __device__ inline uint32_t tile_blocks(uint32_t b, uint32_t w, uint32_t target) {
-  const uint32_t epl = b >= 512 ? b / 64 : 8;
-  const uint32_t lpb = b / epl;
-  const uint32_t tb = 256 / lpb;
-  uint32_t sub = target / (tb * b * w);
-  sub = sub < 1 ? 1 : sub;
-  while (tb * sub < 8) sub *= 2;
-  return tb * sub;
-}
-
-// Values per lane of the encode pass, and blocks per encode tile. Sixteen
+// Values per lane of the encode and decode passes, and blocks per tile. Sixteen
 // float32 values a lane share the per-row work (ranks, prefix sums, K and
 // code writes) among twice the values of eight: the float32 encoder issues 18
 // vector instructions a value instead of 24. Sixteen doubles would take all
 // the registers of four waves per SIMD (b = 1024 has no other split).
-__host__ __device__ constexpr uint32_t enc_epl(uint32_t b, uint32_t w) {
+__host__ __device__ constexpr uint32_t lane_values(uint32_t b, uint32_t w) {
   return w == 4 ? (b >= 16 ? 16 : 8) : (b >= 1024 ? 16 : 8);
 }
-__host__ __device__ constexpr uint32_t enc_blocks(uint32_t b, uint32_t w) {
-  return kEncodeTileBytes / (b * w) < 8 ? 8 : kEncodeTileBytes / (b * w);
+__host__ __device__ constexpr uint32_t tile_blocks(uint32_t b, uint32_t w, uint32_t bytes) {
+  return bytes / (b * w) < 8 ? 8 : bytes / (b * w);
 }
+__host__ __device__ constexpr uint32_t enc_blocks(uint32_t b, uint32_t w) { return tile_blocks(b, w, kEncodeTileBytes); }
+__host__ __device__ constexpr uint32_t dec_blocks(uint32_t b, uint32_t w) { return tile_blocks(b, w, kDecodeTileBytes); }
 
 // Blocks per tile of the classification and index passes (four a thread, a
 // multiple of every encode tile).
@@ -139,7 +129,7 @@ __host__ __device__ inline FieldTiles field_tiles(uint64_t n, uint64_t nblk, uin
   t.chunks = cdiv(cdiv(n, row_values(b)), kStatsChunk);
   t.cls = cdiv(nblk, kClsBlocks);
   t.enc = cdiv(nblk, enc_blocks(b, w));
-  t.dec = cdiv(nblk, tile_blocks(b, w, kDecodeTileBytes));
+  t.dec = cdiv(nblk, dec_blocks(b, w));
   return t;
 }
 
