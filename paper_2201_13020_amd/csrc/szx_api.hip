@@ -160,6 +160,7 @@ szx::FieldD single_field_d(const szx::Job& j, const void* in, uint64_t in_bytes,
   f.index = (uint64_t*)(ws + W.dec_index);
   f.rank_st = (uint64_t*)(ws + W.dec_rank);
   f.mid_st = (uint64_t*)(ws + W.dec_mid);
+  f.totals = (uint32_t*)f.mid_st;
   f.n = j.n;
   f.nblk = j.nblk;
   f.dtype = j.dtype;
@@ -399,6 +400,7 @@ sz_status plan_decompress(const sz_dfield* fs, uint32_t n, uint8_t* ws, std::vec
   szx::FieldD* F = (szx::FieldD*)(host->data() + P.fields_off);
   uint32_t* maps[4];
   for (int m = 0; m < 4; ++m) maps[m] = (uint32_t*)(host->data() + P.maps_off[m]);
+  uint32_t direct = 1, any_empty = 0;
   uint64_t bi[2] = {0, 0}, bd[2] = {0, 0};
   for (uint32_t i = 0; i < n; ++i) {
     const szx::Job& j = jobs[i];
@@ -416,12 +418,15 @@ sz_status plan_decompress(const sz_dfield* fs, uint32_t n, uint8_t* ws, std::vec
     f.index = (uint64_t*)(ws + index_off[i]);
     f.rank_st = (uint64_t*)(ws + rank_off[i]);
     f.mid_st = (uint64_t*)(ws + mid_off[i]);
+    f.totals = (uint32_t*)f.mid_st;
     f.n = j.n;
     f.nblk = j.nblk;
     f.dtype = j.dtype;
     f.ndims = j.ndims;
     for (int k = 0; k < 4; ++k) f.dims[k] = j.dims[k];
     const uint32_t dt = j.dtype;
+    if (ft.cls > szx::kDirectTiles) direct = 0;
+    if (j.nblk == 0) any_empty = 1;
     f.base_idx = bi[dt];
     f.base_dec = bd[dt];
     F[i] = f;
@@ -441,6 +446,8 @@ sz_status plan_decompress(const sz_dfield* fs, uint32_t n, uint8_t* ws, std::vec
   }
   b.zero_begin = (uint64_t*)(ws + P.zero_off);
   b.zero_words = (P.zero_end - P.zero_off) / 8;
+  b.direct = direct;
+  b.any_empty = any_empty;
   b.gate = (uint64_t*)ws;  // the first line (zero in the image: the first run clears)
   b.nfields = n;
   *block_out = block;
@@ -596,6 +603,8 @@ sz_status sz_decompress(const void* d_in, uint64_t in_bytes, const sz_params* ex
   b.tiles_dec[j.dtype] = ft.dec;
   b.zero_begin = (uint64_t*)(ws + W.dec_rank);
   b.zero_words = (W.zero_end - W.dec_rank) / 8;
+  b.direct = ft.cls <= szx::kDirectTiles;
+  b.any_empty = j.nblk == 0;
   b.gate = (uint64_t*)(ws + W.clean);
   b.nfields = 1;
   const hipError_t e = szx::launch_decompress(b, j.b, stream, current_hook());

@@ -5,12 +5,15 @@
 //             non-constant blocks and their ranks (hence their K byte and
 //             codes) -- the population count of the state bits before the
 //             tile for the first 256 tiles, a light single-pass prefix count
-//             after them; workgroup 0 first clears the status words that the
-//             prefix sums use (a gate holds the others); per value the number of
-//             stored mid bytes is the kept bytes minus the leading bytes its
-//             2-bit code shares, and a second light prefix sum gives the first
-//             mid byte of every decode tile (Sec. V-B locates the mid bytes by
-//             a prefix sum of these counts before they are read).
+//             after them; per value the number of stored mid bytes is the kept
+//             bytes minus the leading bytes its 2-bit code shares, and their
+//             prefix sum gives the first mid byte of every wave of a decode
+//             tile (Sec. V-B locates the mid bytes by a prefix sum of these
+//             counts before they are read). Where every field has at most 256
+//             index tiles the tiles wait on nothing: each leaves its total,
+//             which the decode tiles add up. Else a second light prefix sum
+//             chains them, and workgroup 0 first clears the status words of
+//             both (a gate holds the others).
 //   k_decode  every wave of a decode tile on its own, no waiting: it stages its
 //             mid bytes in LDS with aligned 16-byte loads, resolves leading
 //             bytes -- byte j of value i is the stored byte j of the nearest
@@ -31,7 +34,6 @@ namespace szx {
 
 constexpr uint32_t kStatusCorrupt = 3;  // SZ_ECORRUPT
 constexpr uint32_t kStatusDevice = 4;   // SZ_EDEVICE: a bounded wait gave up
-constexpr uint32_t kDirectRankTiles = 256;  // index tiles that count their first rank directly
 
 // Field of a call, or of a batch entry (a copy with its pointers typed as
 // global memory).
@@ -47,6 +49,7 @@ __device__ __forceinline__ FieldD field_at(const DBatch& b, uint32_t fi) {
   f.index = as_global(f.index);
   f.rank_st = as_global(f.rank_st);
   f.mid_st = as_global(f.mid_st);
+  f.totals = as_global(f.totals);
   return f;
 }
 __device__ __forceinline__ uint32_t dfield_of(const uint32_t* map, uint64_t t) { return map ? *as_constant(map + t) : 0u; }
@@ -59,7 +62,7 @@ __global__ __launch_bounds__(256) void k_dinit(DBatch b) {
 }
 
 // ---------------------------------------------------------------- gate ---
-// The index pass's status words and every field's status word must be zero
+// (Only the chained index has one.) The index pass's status words and every field's status word must be zero
 // before any index tile publishes or reports an error, and no launch of its
 // own clears them. Workgroup 0 of the call's first index launch (dispatched
 // first) clears them and then stores the call's token in the go word; every
@@ -299,11 +302,15 @@ __device__ __forceinline__ void index_store(uint64_t* e, uint64_t mid, uint64_t 
       make_ulonglong2(mid | ((uint64_t)w1 << 48), rank | ((uint64_t)w2 << 32) | ((uint64_t)w3 << 48));
 }
 constexpr uint64_t kIndexMid = (1ull << 48) - 1;
+// In a direct index the first mid byte counts from its index tile's start (24
+// bits) and the tile's mid bytes follow it (17 bits).
+__device__ __forceinline__ uint64_t index_direct(uint32_t mid, uint32_t bytes) { return mid | ((uint64_t)bytes << 24); }
+constexpr uint32_t kTotalBad = 0x80000000u;  // in an index tile's total: the stream failed validation there
 
 // Per tile of CLS blocks (four per thread): ranks of the non-constant blocks
 // and mid bytes, each through a light single-pass prefix sum; writes the index
 // entry of every decode tile in it.
-template <typename T, int B>
+template <typename T, int B, bool DIRECT>
 __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, uint32_t t, uint32_t* s_scan,
                                             uint64_t* s_r0p, uint64_t* s_m0p, uint32_t* s_wave, int* s_flag) {
   constexpr int BYTES = Traits<T>::BYTES;
@@ -314,11 +321,22 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   uint64_t& s_r0 = *s_r0p;
   uint64_t& s_m0 = *s_m0p;
   const StreamInfo h = read_header<BYTES, B>(a);
-  if (blockIdx.x == 0) gate_open(b, s_flag);
-  if (!h.ok) {
-    gate_wait(b, a.status);
-    if (t == 0 && threadIdx.x == 0) atomicMax(a.status, kStatusCorrupt);
-    return;
+  if constexpr (DIRECT) {
+    // tile 0 sets the field's status (the decode pass raises it), and the
+    // launch's first workgroup those of fields without values
+    if (t == 0 && threadIdx.x == 0) *a.status = h.ok ? 0u : kStatusCorrupt;
+    if (blockIdx.x == 0 && b.any_empty && b.fields) {
+      for (uint32_t i = threadIdx.x; i < b.nfields; i += kWG)
+        if (b.fields[i].nblk == 0) *as_global(b.fields[i].status) = 0;
+    }
+    if (!h.ok) return;
+  } else {
+    if (blockIdx.x == 0) gate_open(b, s_flag);
+    if (!h.ok) {
+      gate_wait(b, a.status);
+      if (t == 0 && threadIdx.x == 0) atomicMax(a.status, kStatusCorrupt);
+      return;
+    }
   }
   const uint32_t ntiles = (uint32_t)cdiv(a.nblk, CLS);
   const uint8_t* in = a.in;
@@ -335,24 +353,28 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
     ncb |= (nc ? 1u : 0u) << i;
     cnt += nc ? 1u : 0u;
   }
-  // A tile whose preceding state bits are few (the first kDirectRankTiles
+  // A tile whose preceding state bits are few (the first kDirectTiles
   // tiles: at most 32 KiB of them) counts its first rank directly, as the
   // population count of those bits (16-byte words from a 16-byte aligned
   // section, all loads issued at once), and publishes it as inclusive; later
   // tiles chain by look-back and stop at those words.
-  const bool direct = t < kDirectRankTiles;
+  const bool direct = DIRECT || t < kDirectTiles;
   uint32_t pop = 0;
   if (direct) {
-    constexpr uint32_t W16 = kDirectRankTiles * (CLS / 8) / 16 / kWG;  // words per thread, at most
+    constexpr uint32_t W16 = kDirectTiles * (CLS / 8) / 16 / kWG;  // words per thread, at most
     const uint32_t n16 = t * (CLS / 8) / 16;
-    // a buffer resource over exactly those bytes: words past it read zero,
-    // so every lane issues the same loads (no branch, no waits between them)
+    // a buffer resource over exactly those bytes: words past it read zero, so
+    // every lane issues the same loads (no branch but a wave-uniform one, no
+    // waits between them)
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(in + h.sec.state), (short)0, (int)(n16 * 16u), 0x00020000);
     using v4u = unsigned int __attribute__((ext_vector_type(4)));
     v4u u[W16];
 #pragma unroll
-    for (uint32_t j = 0; j < W16; ++j) u[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((threadIdx.x + j * kWG) * 16u), 0, 0);
+    for (uint32_t j = 0; j < W16; ++j) {
+      u[j] = v4u{0, 0, 0, 0};
+      if (j * kWG < n16) u[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((threadIdx.x + j * kWG) * 16u), 0, 0);
+    }
 #pragma unroll
     for (uint32_t j = 0; j < W16; ++j) pop += __popc(u[j].x) + __popc(u[j].y) + __popc(u[j].z) + __popc(u[j].w);
   }
@@ -360,17 +382,20 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   uint32_t ex2[2], tot2[2];
   wg_excl_scan_multi<2>(v2, ex2, tot2, s_scan);
   const uint32_t rex = ex2[0], tnc = tot2[0];
-  gate_wait(b, a.status);
-  if (direct) {
-    if (threadIdx.x == 0) status_store(a.rank_st + t, kFlagIncl | (((uint64_t)tot2[1] + tnc) & kValueMask));
-    if (threadIdx.x == 0) s_r0 = tot2[1];
-  } else if (threadIdx.x < kWave) {
-    if (threadIdx.x == 0) lookback_publish(a.rank_st, t, tnc);
-    const uint64_t p = lookback_resolve_n(a.rank_st, t, tnc, a.status, kStatusDevice, ntiles);
-    if (threadIdx.x == 0) s_r0 = p;
+  uint64_t R0 = tot2[1];
+  if constexpr (!DIRECT) {
+    gate_wait(b, a.status);
+    if (direct) {
+      if (threadIdx.x == 0) status_store(a.rank_st + t, kFlagIncl | (((uint64_t)tot2[1] + tnc) & kValueMask));
+      if (threadIdx.x == 0) s_r0 = tot2[1];
+    } else if (threadIdx.x < kWave) {
+      if (threadIdx.x == 0) lookback_publish(a.rank_st, t, tnc);
+      const uint64_t p = lookback_resolve_n(a.rank_st, t, tnc, a.status, kStatusDevice, ntiles);
+      if (threadIdx.x == 0) s_r0 = p;
+    }
+    __syncthreads();
+    R0 = s_r0;
   }
-  __syncthreads();
-  const uint64_t R0 = s_r0;
   // The K bytes and codes of the tile's ranks [R0, R0 + tnc) that the
   // stream holds, through buffer resources over just those bytes (32-bit
   // offsets from the tile's first rank; reads past them return zeros): every
@@ -411,39 +436,81 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   }
   uint32_t tmid;
   const uint32_t mex = wg_excl_sum<uint32_t>(mid, s_scan, tmid);
-  if (threadIdx.x < kWave) {
-    if (threadIdx.x == 0) lookback_publish(a.mid_st, t, tmid);
-    const uint64_t p = lookback_resolve_n(a.mid_st, t, tmid, a.status, kStatusDevice, ntiles);
-    if (threadIdx.x == 0) s_m0 = p;
+  if constexpr (!DIRECT) {
+    if (threadIdx.x < kWave) {
+      if (threadIdx.x == 0) lookback_publish(a.mid_st, t, tmid);
+      const uint64_t p = lookback_resolve_n(a.mid_st, t, tmid, a.status, kStatusDevice, ntiles);
+      if (threadIdx.x == 0) s_m0 = p;
+    }
   }
   // mid bytes before every wave of a decode tile, within this tile
 #pragma unroll
   for (int i = 0; i < BPT; ++i)
     if ((threadIdx.x * BPT + i) % D::WBLK == 0) s_wave[(threadIdx.x * BPT + i) / D::WBLK] = mex + midb[i];
+  if (DIRECT) {
+    if (threadIdx.x == 0) s_wave[CLS / D::WBLK] = tmid;
+    if (t == ntiles - 1 && R0 + tnc != h.n_nc) bad = true;
+    const uint64_t any = __ballot(bad);
+    if (lane_id() == 0) s_scan[kWavesPerWG + threadIdx.x / kWave] = any != 0 ? 1u : 0u;  // past the sums' words
+  }
   __syncthreads();
-  const uint64_t M0 = s_m0;
   if ((k0 % D::TBLK) == 0 && k0 < a.nblk) {
     const uint32_t w = threadIdx.x * BPT / D::WBLK;
     const uint32_t m = s_wave[w];
-    index_store(a.index + 2 * (k0 / D::TBLK), M0 + m, R0 + rex, s_wave[w + 1] - m, s_wave[w + 2] - m, s_wave[w + 3] - m);
+    const uint64_t m0 = DIRECT ? index_direct(m, s_wave[w + 4] - m) : s_m0 + m;
+    index_store(a.index + 2 * (k0 / D::TBLK), m0, R0 + rex, s_wave[w + 1] - m, s_wave[w + 2] - m, s_wave[w + 3] - m);
   }
-  if (t == ntiles - 1 && threadIdx.x == 0) {
-    if (R0 + tnc != h.n_nc || M0 + tmid != h.mid_total) bad = true;
-    // the end of the last decode tile
-    index_store(a.index + 2 * cdiv(a.nblk, D::TBLK), h.mid_total, h.n_nc, 0, 0, 0);
+  if constexpr (DIRECT) {
+    if (threadIdx.x == 0) {
+      uint32_t any = 0;
+#pragma unroll
+      for (int i = 0; i < kWavesPerWG; ++i) any |= s_scan[kWavesPerWG + i];
+      a.totals[t] = tmid | (any ? kTotalBad : 0u);
+    }
+  } else {
+    if (t == ntiles - 1 && threadIdx.x == 0) {
+      if (R0 + tnc != h.n_nc || s_m0 + tmid != h.mid_total) bad = true;
+      // the end of the last decode tile
+      index_store(a.index + 2 * cdiv(a.nblk, D::TBLK), h.mid_total, h.n_nc, 0, 0, 0);
+    }
+    if (__ballot(bad) != 0 && lane_id() == 0) atomicMax(a.status, kStatusCorrupt);
   }
-  if (__ballot(bad) != 0 && lane_id() == 0) atomicMax(a.status, kStatusCorrupt);
 }
 
-template <typename T, int B>
+template <typename T, int B, bool DIRECT>
 __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
   __shared__ uint32_t s_scan[2 * kWavesPerWG];
   __shared__ uint64_t s_r0, s_m0;
-  __shared__ uint32_t s_wave[kClsBlocks / DecGeo<T, B>::WBLK];
+  __shared__ uint32_t s_wave[kClsBlocks / DecGeo<T, B>::WBLK + 1];
   __shared__ int s_flag;
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_idx[Traits<T>::BYTES / 8], g));
-  dindex_tile<T, B>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+  dindex_tile<T, B, DIRECT>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+}
+
+// A direct index's totals of the first n <= kDirectTiles index tiles, four a
+// lane; their sum (every lane the same), and whether one of the tiles found the
+// stream corrupt.
+static_assert(kDirectTiles == 4 * kWave, "four totals a lane");
+struct Totals {
+  uint32_t v[4];
+};
+__device__ __forceinline__ Totals totals_load(const uint32_t* totals, uint32_t n) {
+  using v4u = unsigned int __attribute__((ext_vector_type(4)));
+  const v4u u = __builtin_amdgcn_raw_buffer_load_b128(buffer_of(totals, (n + 3u) / 4u * 16u), lane_id() * 16, 0, 0);
+  Totals t;
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) t.v[k] = (uint32_t)lane_id() * 4u + k < n ? u[k] : 0u;
+  return t;
+}
+__device__ __forceinline__ uint32_t totals_sum(const Totals& t) {
+  uint32_t sum = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k) sum += t.v[k] & ~kTotalBad;
+  return wave_total_u32(sum);
+}
+__device__ __forceinline__ bool totals_bad(const Totals& t) {
+  return __ballot(((t.v[0] | t.v[1] | t.v[2] | t.v[3]) & kTotalBad) != 0) != 0;
 }
 
 // One decode tile, each wave its quarter by itself: no barrier, nothing shared.
@@ -454,13 +521,18 @@ __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
 // barriers a tile, byte masks a value and gaps in every store). 2^28 float64
 // values at REL 1e-5: 456 us (533), the copy rate as well.
 template <typename T, int B>
-__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, uint8_t* s_stage) {
+__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool direct, uint8_t* s_stage) {
   using U = typename Traits<T>::U;
   using G = DecGeo<T, B>;
   constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB, TBLK = G::TBLK;
   constexpr int BYTES = Traits<T>::BYTES;
   using v4u = unsigned int __attribute__((ext_vector_type(4)));
 
+  // the index first: its loads go out beside the header's
+  const uint32_t it = t / (uint32_t)(kClsBlocks / TBLK);  // the index tile
+  const Totals sums = totals_load(a.totals, direct ? it : 0u);
+  const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
+  const uint64_t e0 = e[0], e1 = e[1], e2 = e[2];
   const StreamInfo h = read_header<BYTES, B>(a);
   if (!h.ok) return;  // k_dindex reported it
   const uint8_t* in = a.in;
@@ -500,13 +572,22 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, uint8_t
 
   // the wave's mid bytes: [m0, m1) of the mid section, from the tile's entry
   // of the index and the next one's
-  const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
-  const uint64_t e0 = e[0], e1 = e[1], e2 = e[2];
   const uint64_t r0_t = e1 & 0xFFFFFFFFull;
-  const uint64_t m0_t = e0 & kIndexMid;
+  uint64_t m0_t = e0 & kIndexMid, m1_t = e2 & kIndexMid;
+  if (direct) {
+    const uint32_t base = totals_sum(sums);
+    const uint32_t rel = (uint32_t)m0_t & 0xFFFFFFu;
+    m1_t = (uint64_t)base + rel + ((uint32_t)(m0_t >> 24) & 0x1FFFFu);
+    m0_t = (uint64_t)base + rel;
+    // once a field: the index tiles' own findings, and the sum of all
+    if (kb + nblk_t == a.nblk) {
+      const Totals all = totals_load(a.totals, it + 1);
+      if (totals_sum(all) != h.mid_total || totals_bad(all)) bad = true;
+    }
+  }
   const uint32_t w1 = (uint32_t)(e0 >> 48), w2 = (uint32_t)(e1 >> 32) & 0xFFFFu, w3 = (uint32_t)(e1 >> 48);
   const uint64_t m0 = m0_t + (wave == 0 ? 0u : wave == 1 ? w1 : wave == 2 ? w2 : w3);
-  uint64_t m1 = wave == 3 ? e2 & kIndexMid : m0_t + (wave == 0 ? w1 : wave == 1 ? w2 : w3);
+  uint64_t m1 = wave == 3 ? m1_t : m0_t + (wave == 0 ? w1 : wave == 1 ? w2 : w3);
   if (m1 < m0 || m1 - m0 > (uint64_t)G::MOST || h.sec.mid + m1 > a.in_bytes) {
     bad = true;
     m1 = m0;
@@ -795,10 +876,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DecGeo<T, B
   __shared__ __align__(16) uint8_t s_stage[kWavesPerWG * G::STAGE];
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_dec[Traits<T>::BYTES / 8], g));
-  decode_tile<T, B>(f, (uint32_t)(g - f.base_dec), s_stage);
+  decode_tile<T, B>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage);
   // the call's last decode launch advances the gate's epoch (no index tile
   // reads it any more); at the end, so that no load comes after the atomic
-  if (g == 0 && threadIdx.x == 0 && (sizeof(T) == 8 || b.tiles_dec[1] == 0))
+  if (g == 0 && threadIdx.x == 0 && !b.direct && (sizeof(T) == 8 || b.tiles_dec[1] == 0))
     __hip_atomic_fetch_add((__attribute__((address_space(1))) uint64_t*)(as_global(b.gate) + kGateEpochWord), 1ull,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -819,8 +900,18 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
     const uint32_t gi = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cdiv(nf, 256), 1024));
     run("k_dinit", [&] { k_dinit<<<gi, 256, 0, stream>>>(b); });
   }
-  if (b.tiles_idx[0]) run("k_dindex", [&] { k_dindex<float, B><<<(uint32_t)b.tiles_idx[0], 256, 0, stream>>>(b); });
-  if (b.tiles_idx[1]) run("k_dindex", [&] { k_dindex<double, B><<<(uint32_t)b.tiles_idx[1], 256, 0, stream>>>(b); });
+  for (int dt = 0; dt < 2; ++dt) {
+    const uint32_t n = (uint32_t)b.tiles_idx[dt];
+    if (!n) continue;
+    if (dt == 0 && b.direct)
+      run("k_dindex", [&] { k_dindex<float, B, true><<<n, 256, 0, stream>>>(b); });
+    else if (dt == 0)
+      run("k_dindex", [&] { k_dindex<float, B, false><<<n, 256, 0, stream>>>(b); });
+    else if (b.direct)
+      run("k_dindex", [&] { k_dindex<double, B, true><<<n, 256, 0, stream>>>(b); });
+    else
+      run("k_dindex", [&] { k_dindex<double, B, false><<<n, 256, 0, stream>>>(b); });
+  }
   if (b.tiles_dec[0]) run("k_decode", [&] { k_decode<float, B><<<(uint32_t)b.tiles_dec[0], 256, 0, stream>>>(b); });
   if (b.tiles_dec[1]) run("k_decode", [&] { k_decode<double, B><<<(uint32_t)b.tiles_dec[1], 256, 0, stream>>>(b); });
   return hipGetLastError();

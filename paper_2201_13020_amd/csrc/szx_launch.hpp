@@ -70,6 +70,7 @@ struct FieldD {
   uint64_t* index;    // per decode tile: first rank, first mid byte
   uint64_t* rank_st;  // scan status words of the index pass
   uint64_t* mid_st;
+  uint32_t* totals;   // direct index: each index tile's mid bytes (in place of mid_st)
   uint64_t n, nblk;
   uint32_t dtype, ndims;
   uint64_t dims[4];
@@ -84,7 +85,10 @@ struct DBatch {
   uint64_t* zero_begin;  // the index pass's status words (its gate clears them)
   uint64_t zero_words;
   uint64_t* gate;        // the workspace line of the gate's epoch and go words
-  uint32_t nfields, pad;
+  uint32_t nfields;
+  uint32_t direct;       // every field has at most kDirectTiles index tiles
+  uint32_t any_empty;    // some field has no values
+  uint32_t pad;
   FieldD one;
 };
 

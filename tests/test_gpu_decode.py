@@ -4,9 +4,11 @@ across lanes, rows of constant, coded and raw blocks side by side, stages filled
 to their end, a short last block, every block size."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import gpu_decompress, same_bits
 from oracle import szref
+from paper_2201_13020_amd import szx
 from test_gpu_encode import field
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +24,29 @@ def test_values_equal_the_oracle(kind, block, dtype):
             ref = szref.compress(x, eb, mode, block)
             y, status = gpu_decompress(ref)
             assert status == 0 and same_bits(y, szref.decompress(ref)), (n, eb)
+
+
+@pytest.mark.parametrize("tiles", [255, 256, 257])
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_index_direct_and_chained(dtype, tiles):
+    """The index at the line between its two forms (256 tiles of 1024 blocks),
+    from workspaces of arbitrary bytes that a call of the other form used last;
+    then a stream whose mid-byte total or state bits disagree."""
+    ref = {}
+    for n in (tiles * 8192 - 3, 30_001 if tiles > 256 else 260 * 8192 + 1):
+        s = szref.compress(field("mixed", n, dtype, 8), 1e-2, "rel", 8)
+        ref[n] = (s, szref.decompress(s), szx.inspect(s[:96].tobytes()))
+    ws = torch.full((max(szx.workspace_size(i["dtype"], i["dims"], 0.0, "rel", 8) for _, _, i in ref.values()),), 0xA5,
+                    dtype=torch.uint8, device="cuda")
+    for n in list(ref) * 2:
+        s, want, info = ref[n]
+        y, st = szx.decompress(torch.from_numpy(s).cuda(), s.size, info, ws=ws)
+        torch.cuda.synchronize()
+        assert int(st.cpu().view(torch.int32)) == 0 and same_bits(y.cpu().numpy(), want), n
+    s, _, info = ref[tiles * 8192 - 3]
+    for at in (88, 96 + 5):  # the header's mid-byte total, a state byte
+        bad = s.copy()
+        bad[at] ^= 1
+        _, st = szx.decompress(torch.from_numpy(bad).cuda(), s.size, info, ws=ws)
+        torch.cuda.synchronize()
+        assert int(st.cpu().view(torch.int32)) == 3, at
