@@ -172,12 +172,35 @@ def workspace_size(dtype, dims, eb=0.0, mode="rel", block=128):
 
 
 def _stream_handle(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    # the current stream's handle without a Stream object around it (3 us)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+
+
+def _on(stream, device):
+    """Context in which buffers made for a call belong to the stream its
+    kernels run on, so that the caching allocator does not hand them out again
+    while that stream still uses them. Entered only where a buffer is made:
+    it costs 8 us, more than a small call's launches."""
+    return torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(device))
 
 
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+
+
+def _sizes(pp, failed=None):
+    """(compress bound, workspace size) of the parameters at pp; raises for
+    invalid ones, else `failed` if given (the error of a call that was made
+    without looking at the sizes first)."""
+    cap = int(lib().sz_compress_bound(pp))
+    wsz = int(lib().sz_workspace_size(pp))
+    if cap == 0 or wsz == 0:
+        raise SzError(1, "invalid parameters: " + lib().sz_last_error().decode())
+    if failed is not None:
+        raise failed
+    return cap, wsz
 
 
 def compress(x, eb, mode="rel", block=128, dims=None, out=None, out_size=None, ws=None, stream=None):
@@ -190,23 +213,20 @@ def compress(x, eb, mode="rel", block=128, dims=None, out=None, out_size=None, w
     if len(dims) == 0:
         dims = (1,)
     p = make_params(x.dtype, dims, eb, mode, block)
-    cap = int(lib().sz_compress_bound(ctypes.byref(p)))
-    wsz = int(lib().sz_workspace_size(ctypes.byref(p)))
-    if cap == 0 or wsz == 0:
-        raise SzError(1, "invalid parameters: " + lib().sz_last_error().decode())
-    # buffers made here belong to the stream the kernels run on, so that the
-    # caching allocator does not hand them out again while that stream still
-    # uses them
-    with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(x.device)):
-        if out is None:
-            out = torch.empty(cap, dtype=torch.uint8, device=x.device)
-        if out_size is None:
-            out_size = torch.empty(1, dtype=torch.uint64, device=x.device)
-        if ws is None:
-            ws = torch.empty(wsz, dtype=torch.uint8, device=x.device)
-    rc = lib().sz_compress(ctypes.byref(p), _ptr(x), _ptr(out), out.numel(), _ptr(out_size),
-                           _ptr(ws), ws.numel(), _stream_handle(stream))
-    _check(rc, "sz_compress")
+    pp = ctypes.byref(p)
+    if out is None or out_size is None or ws is None:
+        cap, wsz = _sizes(pp)
+        with _on(stream, x.device):
+            if out is None:
+                out = torch.empty(cap, dtype=torch.uint8, device=x.device)
+            if out_size is None:
+                out_size = torch.empty(1, dtype=torch.uint64, device=x.device)
+            if ws is None:
+                ws = torch.empty(wsz, dtype=torch.uint8, device=x.device)
+    rc = lib().sz_compress(pp, _ptr(x), _ptr(out), out.numel(), _ptr(out_size), _ptr(ws), ws.numel(),
+                           _stream_handle(stream))
+    if rc != 0:
+        _sizes(pp, SzError(rc, f"sz_compress: {lib().sz_last_error().decode()}"))
     return out, out_size
 
 
@@ -325,25 +345,27 @@ def decompress(data, nbytes, expected, out=None, status=None, ws=None, stream=No
     `expected`: dict with dtype, dims, block (e.g. from inspect()). Returns
     (out, status): the values and a 1-element uint32 device tensor (0 = ok,
     3 = corrupt stream). Asynchronous on `stream`."""
+    if not data.is_cuda:
+        raise ValueError("data must be a device tensor")
     p = make_params(expected["dtype"], expected["dims"], expected.get("eb", 0.0),
                     expected.get("mode", "rel"), expected["block"])
-    wsz = int(lib().sz_workspace_size(ctypes.byref(p)))
-    if wsz == 0:
-        raise SzError(1, "invalid parameters: " + lib().sz_last_error().decode())
-    dt = torch.float32 if p.dtype == SZ_F32 else torch.float64
-    n = 1
-    for d in expected["dims"]:
-        n *= int(d)
-    with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(data.device)):
-        if out is None:
-            out = torch.empty(n, dtype=dt, device=data.device)
-        if status is None:
-            status = torch.empty(1, dtype=torch.uint32, device=data.device)
-        if ws is None:
-            ws = torch.empty(wsz, dtype=torch.uint8, device=data.device)
-    rc = lib().sz_decompress(_ptr(data), int(nbytes), ctypes.byref(p), _ptr(out), out.numel() * out.element_size(),
-                             _ptr(status), _ptr(ws), ws.numel(), _stream_handle(stream))
-    _check(rc, "sz_decompress")
+    pp = ctypes.byref(p)
+    if out is None or status is None or ws is None:
+        _, wsz = _sizes(pp)
+        n = 1
+        for d in expected["dims"]:
+            n *= int(d)
+        with _on(stream, data.device):
+            if out is None:
+                out = torch.empty(n, dtype=torch.float32 if p.dtype == SZ_F32 else torch.float64, device=data.device)
+            if status is None:
+                status = torch.empty(1, dtype=torch.uint32, device=data.device)
+            if ws is None:
+                ws = torch.empty(wsz, dtype=torch.uint8, device=data.device)
+    rc = lib().sz_decompress(_ptr(data), int(nbytes), pp, _ptr(out), out.numel() * out.element_size(), _ptr(status),
+                             _ptr(ws), ws.numel(), _stream_handle(stream))
+    if rc != 0:
+        _sizes(pp, SzError(rc, f"sz_decompress: {lib().sz_last_error().decode()}"))
     return out, status
 
 
