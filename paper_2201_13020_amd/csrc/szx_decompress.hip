@@ -307,12 +307,21 @@ constexpr uint64_t kIndexMid = (1ull << 48) - 1;
 __device__ __forceinline__ uint64_t index_direct(uint32_t mid, uint32_t bytes) { return mid | ((uint64_t)bytes << 24); }
 constexpr uint32_t kTotalBad = 0x80000000u;  // in an index tile's total: the stream failed validation there
 
+// How the index pass finds what lies before a tile: kChained by single-pass
+// prefix sums, kDirect by counting it, kOne where the field is one index tile
+// that every workgroup of the decode pass indexes for itself.
+enum : int { kChained = 0, kDirect = 1, kOne = 2 };
+
 // Per tile of CLS blocks (four per thread): ranks of the non-constant blocks
 // and mid bytes, each through a light single-pass prefix sum; writes the index
 // entry of every decode tile in it.
-template <typename T, int B, bool DIRECT>
-__device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, uint32_t t, uint32_t* s_scan,
-                                            uint64_t* s_r0p, uint64_t* s_m0p, uint32_t* s_wave, int* s_flag) {
+// kOne: the entry of decode tile dt goes to `entry` instead, and decode tile
+// 0 sets the field's status; returns whether the tile may be decoded.
+template <typename T, int B, int MODE>
+__device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, uint32_t t, uint32_t* s_scan,
+                                            uint64_t* s_r0p, uint64_t* s_m0p, uint32_t* s_wave, int* s_flag,
+                                            uint32_t dt = 0, uint64_t* entry = nullptr) {
+  constexpr bool DIRECT = MODE != kChained;
   constexpr int BYTES = Traits<T>::BYTES;
   constexpr int CLS = (int)kClsBlocks;
   constexpr int BPT = CLS / kWG;
@@ -324,18 +333,18 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   if constexpr (DIRECT) {
     // tile 0 sets the field's status (the decode pass raises it), and the
     // launch's first workgroup those of fields without values
-    if (t == 0 && threadIdx.x == 0) *a.status = h.ok ? 0u : kStatusCorrupt;
-    if (blockIdx.x == 0 && b.any_empty && b.fields) {
+    if (t == 0 && dt == 0 && threadIdx.x == 0 && (MODE == kDirect || !h.ok)) *a.status = h.ok ? 0u : kStatusCorrupt;
+    if (MODE == kDirect && blockIdx.x == 0 && b.any_empty && b.fields) {
       for (uint32_t i = threadIdx.x; i < b.nfields; i += kWG)
         if (b.fields[i].nblk == 0) *as_global(b.fields[i].status) = 0;
     }
-    if (!h.ok) return;
+    if (!h.ok) return false;
   } else {
     if (blockIdx.x == 0) gate_open(b, s_flag);
     if (!h.ok) {
       gate_wait(b, a.status);
       if (t == 0 && threadIdx.x == 0) atomicMax(a.status, kStatusCorrupt);
-      return;
+      return false;
     }
   }
   const uint32_t ntiles = (uint32_t)cdiv(a.nblk, CLS);
@@ -358,7 +367,7 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   // population count of those bits (16-byte words from a 16-byte aligned
   // section, all loads issued at once), and publishes it as inclusive; later
   // tiles chain by look-back and stop at those words.
-  const bool direct = DIRECT || t < kDirectTiles;
+  const bool direct = MODE == kDirect || (MODE == kChained && t < kDirectTiles);
   uint32_t pop = 0;
   if (direct) {
     constexpr uint32_t W16 = kDirectTiles * (CLS / 8) / 16 / kWG;  // words per thread, at most
@@ -450,22 +459,26 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
   if (DIRECT) {
     if (threadIdx.x == 0) s_wave[CLS / D::WBLK] = tmid;
     if (t == ntiles - 1 && R0 + tnc != h.n_nc) bad = true;
+    if (MODE == kOne && tmid != h.mid_total) bad = true;
     const uint64_t any = __ballot(bad);
     if (lane_id() == 0) s_scan[kWavesPerWG + threadIdx.x / kWave] = any != 0 ? 1u : 0u;  // past the sums' words
   }
   __syncthreads();
-  if ((k0 % D::TBLK) == 0 && k0 < a.nblk) {
+  if ((k0 % D::TBLK) == 0 && k0 < a.nblk && (MODE != kOne || k0 / D::TBLK == dt)) {
     const uint32_t w = threadIdx.x * BPT / D::WBLK;
     const uint32_t m = s_wave[w];
     const uint64_t m0 = DIRECT ? index_direct(m, s_wave[w + 4] - m) : s_m0 + m;
-    index_store(a.index + 2 * (k0 / D::TBLK), m0, R0 + rex, s_wave[w + 1] - m, s_wave[w + 2] - m, s_wave[w + 3] - m);
+    index_store(MODE == kOne ? entry : a.index + 2 * (k0 / D::TBLK), m0, R0 + rex, s_wave[w + 1] - m, s_wave[w + 2] - m, s_wave[w + 3] - m);
   }
   if constexpr (DIRECT) {
     if (threadIdx.x == 0) {
       uint32_t any = 0;
 #pragma unroll
       for (int i = 0; i < kWavesPerWG; ++i) any |= s_scan[kWavesPerWG + i];
-      a.totals[t] = tmid | (any ? kTotalBad : 0u);
+      if constexpr (MODE == kDirect)
+        a.totals[t] = tmid | (any ? kTotalBad : 0u);
+      else if (dt == 0)
+        *a.status = any ? kStatusCorrupt : 0u;
     }
   } else {
     if (t == ntiles - 1 && threadIdx.x == 0) {
@@ -475,9 +488,10 @@ __device__ __forceinline__ void dindex_tile(const DBatch& b, const FieldD& a, ui
     }
     if (__ballot(bad) != 0 && lane_id() == 0) atomicMax(a.status, kStatusCorrupt);
   }
+  return true;
 }
 
-template <typename T, int B, bool DIRECT>
+template <typename T, int B, int MODE>
 __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
   __shared__ uint32_t s_scan[2 * kWavesPerWG];
   __shared__ uint64_t s_r0, s_m0;
@@ -485,7 +499,7 @@ __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
   __shared__ int s_flag;
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_idx[Traits<T>::BYTES / 8], g));
-  dindex_tile<T, B, DIRECT>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+  dindex_tile<T, B, MODE>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
 }
 
 // A direct index's totals of the first n <= kDirectTiles index tiles, four a
@@ -520,8 +534,11 @@ __device__ __forceinline__ bool totals_bad(const Totals& t) {
 // 24 us, part of the stream coming from the last-level cache; 31.5 us with four
 // barriers a tile, byte masks a value and gaps in every store). 2^28 float64
 // values at REL 1e-5: 456 us (533), the copy rate as well.
-template <typename T, int B>
-__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool direct, uint8_t* s_stage) {
+// `entry`: the tile's entry of the index where the workgroup made it itself
+// (kOne), else null.
+template <typename T, int B, bool ONE>
+__device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool direct, uint8_t* s_stage,
+                                            const uint64_t* entry) {
   using U = typename Traits<T>::U;
   using G = DecGeo<T, B>;
   constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB, TBLK = G::TBLK;
@@ -530,9 +547,18 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
 
   // the index first: its loads go out beside the header's
   const uint32_t it = t / (uint32_t)(kClsBlocks / TBLK);  // the index tile
-  const Totals sums = totals_load(a.totals, direct ? it : 0u);
-  const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
-  const uint64_t e0 = e[0], e1 = e[1], e2 = e[2];
+  Totals sums;
+  uint64_t e0, e1, e2 = 0;
+  if constexpr (ONE) {
+    e0 = uniform(entry[0]);
+    e1 = uniform(entry[1]);
+  } else {
+    sums = totals_load(a.totals, direct ? it : 0u);
+    const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
+    e0 = e[0];
+    e1 = e[1];
+    e2 = e[2];
+  }
   const StreamInfo h = read_header<BYTES, B>(a);
   if (!h.ok) return;  // k_dindex reported it
   const uint8_t* in = a.in;
@@ -574,13 +600,13 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
   // of the index and the next one's
   const uint64_t r0_t = e1 & 0xFFFFFFFFull;
   uint64_t m0_t = e0 & kIndexMid, m1_t = e2 & kIndexMid;
-  if (direct) {
-    const uint32_t base = totals_sum(sums);
+  if (ONE || direct) {
+    const uint32_t base = ONE ? 0u : totals_sum(sums);
     const uint32_t rel = (uint32_t)m0_t & 0xFFFFFFu;
     m1_t = (uint64_t)base + rel + ((uint32_t)(m0_t >> 24) & 0x1FFFFu);
     m0_t = (uint64_t)base + rel;
     // once a field: the index tiles' own findings, and the sum of all
-    if (kb + nblk_t == a.nblk) {
+    if (!ONE && kb + nblk_t == a.nblk) {
       const Totals all = totals_load(a.totals, it + 1);
       if (totals_sum(all) != h.mid_total || totals_bad(all)) bad = true;
     }
@@ -867,7 +893,9 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
     }
   }
   if (done - kStageHead - st != wbytes) bad = true;
-  if (__ballot(bad) != 0 && lane == 0) atomicMax(a.status, kStatusCorrupt);
+  // (kOne: the index has looked at every K byte, code and sum of the field,
+  // and decode tile 0 has stored what it found)
+  if (!ONE && __ballot(bad) != 0 && lane == 0) atomicMax(a.status, kStatusCorrupt);
 }
 
 template <typename T, int B>
@@ -876,12 +904,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DecGeo<T, B
   __shared__ __align__(16) uint8_t s_stage[kWavesPerWG * G::STAGE];
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_dec[Traits<T>::BYTES / 8], g));
-  decode_tile<T, B>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage);
+  decode_tile<T, B, false>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage, nullptr);
   // the call's last decode launch advances the gate's epoch (no index tile
   // reads it any more); at the end, so that no load comes after the atomic
   if (g == 0 && threadIdx.x == 0 && !b.direct && (sizeof(T) == 8 || b.tiles_dec[1] == 0))
     __hip_atomic_fetch_add((__attribute__((address_space(1))) uint64_t*)(as_global(b.gate) + kGateEpochWord), 1ull,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A small field's decompression in one launch: every workgroup indexes the whole
+// field (one index tile, kept in LDS) and decodes its own tile. Two launches
+// spend most of a small call in their latencies: 4099 float32 values take 10.3
+// us a call in two, 8.0 in one.
+template <typename T, int B>
+__global__ __launch_bounds__(256) void k_dsmall(DBatch b) {
+  using G = DecGeo<T, B>;
+  __shared__ uint32_t s_scan[2 * kWavesPerWG];
+  __shared__ uint32_t s_wave[kClsBlocks / G::WBLK + 1];
+  __shared__ __align__(16) uint64_t s_entry[2];
+  __shared__ __align__(16) uint8_t s_stage[kWavesPerWG * G::STAGE];
+  FieldD f = b.one;
+  f.in = as_global(f.in);
+  f.out = as_global(f.out);
+  f.status = as_global(f.status);
+  if (!dindex_tile<T, B, kOne>(b, f, 0, s_scan, s_entry, s_entry, s_wave, nullptr, blockIdx.x, s_entry)) return;
+  __syncthreads();
+  decode_tile<T, B, true>(f, blockIdx.x, true, s_stage, s_entry);
 }
 
 // ---------------------------------------------------------------- launch ---
@@ -900,17 +948,27 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
     const uint32_t gi = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cdiv(nf, 256), 1024));
     run("k_dinit", [&] { k_dinit<<<gi, 256, 0, stream>>>(b); });
   }
+  // The line: one index tile, and codes that every workgroup can look through
+  // (131072 values: 32 KiB of them). At 131072 float32 values, b = 128, 32
+  // workgroups: one launch 8.3 us, two 10.3.
+  if (!b.fields && b.tiles_idx[0] + b.tiles_idx[1] == 1 && b.one.n <= 131072) {
+    if (b.tiles_idx[0])
+      run("k_dsmall", [&] { k_dsmall<float, B><<<(uint32_t)b.tiles_dec[0], 256, 0, stream>>>(b); });
+    else
+      run("k_dsmall", [&] { k_dsmall<double, B><<<(uint32_t)b.tiles_dec[1], 256, 0, stream>>>(b); });
+    return hipGetLastError();
+  }
   for (int dt = 0; dt < 2; ++dt) {
     const uint32_t n = (uint32_t)b.tiles_idx[dt];
     if (!n) continue;
     if (dt == 0 && b.direct)
-      run("k_dindex", [&] { k_dindex<float, B, true><<<n, 256, 0, stream>>>(b); });
+      run("k_dindex", [&] { k_dindex<float, B, kDirect><<<n, 256, 0, stream>>>(b); });
     else if (dt == 0)
-      run("k_dindex", [&] { k_dindex<float, B, false><<<n, 256, 0, stream>>>(b); });
+      run("k_dindex", [&] { k_dindex<float, B, kChained><<<n, 256, 0, stream>>>(b); });
     else if (b.direct)
-      run("k_dindex", [&] { k_dindex<double, B, true><<<n, 256, 0, stream>>>(b); });
+      run("k_dindex", [&] { k_dindex<double, B, kDirect><<<n, 256, 0, stream>>>(b); });
     else
-      run("k_dindex", [&] { k_dindex<double, B, false><<<n, 256, 0, stream>>>(b); });
+      run("k_dindex", [&] { k_dindex<double, B, kChained><<<n, 256, 0, stream>>>(b); });
   }
   if (b.tiles_dec[0]) run("k_decode", [&] { k_decode<float, B><<<(uint32_t)b.tiles_dec[0], 256, 0, stream>>>(b); });
   if (b.tiles_dec[1]) run("k_decode", [&] { k_decode<double, B><<<(uint32_t)b.tiles_dec[1], 256, 0, stream>>>(b); });

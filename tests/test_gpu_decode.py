@@ -50,3 +50,20 @@ def test_index_direct_and_chained(dtype, tiles):
         _, st = szx.decompress(torch.from_numpy(bad).cuda(), s.size, info, ws=ws)
         torch.cuda.synchronize()
         assert int(st.cpu().view(torch.int32)) == 3, at
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [8, 64, 128, 1024])
+def test_one_launch_and_two_meet(block, dtype):
+    """Sizes on both sides of where a single call goes from one launch to two
+    (1024 blocks, 131072 values), and what a flipped byte of every section does
+    to the status there."""
+    line = min(1024 * block, 131072)
+    for n in (line - 1, line, line + 1):
+        s = szref.compress(field("mixed", n, dtype, block), 1e-2, "rel", block)
+        y, st = gpu_decompress(s)
+        assert st == 0 and same_bits(y, szref.decompress(s)), n
+        for at in (0, 80, 88, 97):  # magic, block count, mid-byte total, a state byte
+            bad = s.copy()
+            bad[at] ^= 1
+            assert gpu_decompress(bad, szx.inspect(s[:96].tobytes()))[1] == 3, (n, at)
