@@ -52,3 +52,25 @@ def test_streams_equal_the_oracle(kind, block, dtype):
             finally:
                 szx.set_geometry(dt, cls, 0)
             assert size == ref.size and np.array_equal(out[:size].cpu().numpy(), ref), (n, wgs, eb)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [8, 32, 128, 1024])
+def test_one_launch_and_three_meet(block, dtype):
+    """Sizes on both sides of where a single call goes from one workgroup to
+    three launches (32 and 128 KiB of values), with non-finite values, and a
+    workspace that holds anything."""
+    w = 4 if dtype == "float32" else 8
+    for kib in (32, 128):
+        for n in (kib * 1024 // w - 1, kib * 1024 // w, kib * 1024 // w + 1):
+            for kind in ("mixed", "noise"):
+                x = field(kind, n, dtype, block)
+                x[n // 3] = np.inf
+                for eb, mode in ((1e-2, "rel"), (1e-3, "abs"), (0.0, "rel")):
+                    ref = szref.compress(x, eb, mode, block)
+                    ws = torch.full((szx.workspace_size(dtype, (n,), eb, mode, block),), 0x5A, dtype=torch.uint8,
+                                    device="cuda")
+                    out, size = szx.compress(torch.from_numpy(x).cuda(), eb, mode, block, ws=ws)
+                    torch.cuda.synchronize()
+                    m = int(size.cpu().view(torch.int64))
+                    assert m == ref.size and np.array_equal(out[:m].cpu().numpy(), ref), (n, kind, eb, mode)
