@@ -26,6 +26,8 @@
 //               encoded. Bytes are packed in LDS and leave in aligned 16-byte
 //               stores. In a single call workgroup 0 ends the stream: the
 //               mid-byte total and the stream size.
+//   Short single calls take fewer launches: one of one workgroup (k_small), or
+//   k_stats and one more launch that classifies and encodes (k_mid).
 //   k_finalize  batches: every field's mid-byte total and stream size, and
 //               the header of fields without values (a single call only
 //               runs it when its field has no values)
@@ -37,7 +39,7 @@
 namespace szx {
 
 // The stream size while a compression runs (the classification pass sets
-// it, the end of the encode pass replaces it).
+// it, the end of the encode pass replaces it; the launch that does both, too).
 constexpr uint64_t kSizePending = ~0ull;
 
 // Field of a call, or of a batch entry, as the kernels see it (a copy with
@@ -163,6 +165,7 @@ struct EncGeo {
   static constexpr int TBLK = (int)enc_blocks(B, sizeof(T));
   static constexpr int WBLK = TBLK / kWavesPerWG;  // blocks per wave
   static constexpr int SUB = WBLK / GPW;    // rows per wave
+  static constexpr int ROWS = SUB * kWavesPerWG;
   // the wave's LDS ring holds its worst case (every value stored whole); the
   // slack behind it, the run of the lane that crosses the ring's end
   static constexpr uint32_t RING = (uint32_t)(ROW * SUB * (int)sizeof(T));
@@ -319,6 +322,19 @@ __device__ __forceinline__ uint64_t bound_of(const FieldC& f, uint64_t lo, uint6
                       : (uint64_t)bits_of(bound_from<double>(rel, f.eb, lo, hi));
 }
 
+// The bound of a field from its range slots, folded by each wave, one per lane.
+__device__ __forceinline__ uint64_t slots_bound(const FieldC& f) {
+  const uint32_t l = lane_id();
+  uint64_t lo_inv = 0, hi = 0;
+  if (l < f.nslots) {
+    lo_inv = f.range[l * (kRangeStride / 8)];
+    hi = f.range[l * (kRangeStride / 8) + 1];
+  }
+  lo_inv = group_max<kWave, uint64_t>(lo_inv);
+  hi = group_max<kWave, uint64_t>(hi);
+  return bound_of(f, ~lo_inv, hi);
+}
+
 // The bound e of a field (as the bits of a T) from its parameters and, for
 // the relative bound, the field's finite range (no finite value: the range
 // is empty and e = 0). Every thread of classification tile t calls it.
@@ -350,16 +366,7 @@ __device__ __forceinline__ uint64_t field_bound(const FieldC& f, uint32_t t, boo
     return f.dtype == 0 ? (uint64_t)bits_of(round_down_to<float>(f.eb * (hi - lo)))
                         : (uint64_t)bits_of(round_down_to<double>(f.eb * (hi - lo)));
   }
-  if (clean) {
-    uint64_t lo_inv = 0, hi = 0;
-    if (l < f.nslots) {
-      lo_inv = f.range[l * (kRangeStride / 8)];
-      hi = f.range[l * (kRangeStride / 8) + 1];
-    }
-    lo_inv = group_max<kWave, uint64_t>(lo_inv);
-    hi = group_max<kWave, uint64_t>(hi);
-    return bound_of(f, ~lo_inv, hi);
-  }
+  if (clean) return slots_bound(f);
   if (t == 0) {
     uint64_t lo = ~0ull, hi = 0;
     // eight partials in flight per thread
@@ -451,6 +458,24 @@ __device__ __forceinline__ BlockPlan<T> plan_block(typename Traits<T>::U kmin, t
   const bool slack_normal = slack > (T)0 && (bits_of(slack) & emask) != 0;
   p.verify = !(slack_normal && exp_of<T>(slack) >= exp_of<T>(M) - (MANT - 2));
   return p;
+}
+
+// The lanes whose block is not constant: plan_block's K != 0 for the whole
+// wave. The rounded half ranges decide (rounding is monotone) unless one equals
+// e, which sends the wave through the exact test.
+template <typename T>
+__device__ __forceinline__ uint64_t stored_blocks(typename Traits<T>::U kmin, typename Traits<T>::U kmax, T e,
+                                                 bool present) {
+  using U = typename Traits<T>::U;
+  const bool finite = kmin >= FiniteKeys<T>::LO && kmax <= FiniteKeys<T>::HI;
+  const T mn = from_bits<T>(key_to_bits<U>(kmin)), mx = from_bits<T>(key_to_bits<U>(kmax));
+  const T mu = (T)0.5 * mn + (T)0.5 * mx;
+  const T up = mx - mu, down = mu - mn;
+  const T d = up > down ? up : down;
+  uint64_t stored = __ballot(present && !(finite && d < e));
+  if (__ballot(present && finite && d == e) != 0)
+    stored = __ballot(present && !(finite && exact_le<T>(mx, mu, e) && exact_le<T>(mu, mn, e)));
+  return stored;
 }
 
 // A block's plan in one byte: 0 constant, 0xFF raw, else K with bit 7 set
@@ -1319,20 +1344,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<T, B
 
 // ------------------------------------------------------------------ small ---
 
-// Waves of the one workgroup that compresses a small field of at most `bytes`
-// bytes (their rings fill as much LDS: up to 128 of the 160 KiB).
-constexpr uint32_t kSmallBytes = 128u << 10, kSmallestBytes = 32u << 10;
+// The largest field that one workgroup compresses (its rings take as much LDS),
+// and the workgroup's waves for a field of at most `bytes` bytes.
+constexpr uint32_t kSmallestBytes = 32u << 10;
+template <typename T>
+constexpr uint32_t kSmallBytes = sizeof(T) == 4 ? 64u << 10 : 96u << 10;
 template <typename T, int B>
 constexpr uint32_t small_waves(uint32_t bytes) {
   return bytes / EncGeo<T, B>::RING;
 }
 
-// A single field of at most 128 KiB in one launch of one workgroup: each wave
+// A single field of at most 64 KiB (float64: 96) in one launch of one workgroup: each wave
 // reads its blocks once and keeps them in registers through their extrema, the
 // bound, the plan, the codes and the packing; the waves meet at three
 // barriers (finite range, ranks, byte counts), and no word of the workspace is
 // used. Three launches spend a small call in their latencies and in look-backs:
-// 4099 float32 values take 15.6 us a call in three, 7.3 in one.
+// 4099 float32 values took 15.6 us a call in three, 7.3 in one.
 template <typename T, int B, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) void k_small(CBatch b) {
   using U = typename Traits<T>::U;
@@ -1474,6 +1501,237 @@ __global__ __launch_bounds__(64 * NW) void k_small(CBatch b) {
   if (threadIdx.x == 0) *f.out_size = total;
 }
 
+// -------------------------------------------------------------------- mid ---
+
+constexpr uint32_t kMidBlocks = 8192, kMidTiles = 256;  // (at most 2^24 mid bytes)
+
+// Classification and encoding of a single field of a few hundred tiles in one
+// launch: a workgroup a tile, one row a wave. Every workgroup counts the
+// field's non-constant blocks by itself, from the extrema and the bound (a
+// wave tests 64 blocks at a time, so the counts are scalar ones), which takes
+// the place of the classification pass and its scan; each tile's own plans
+// stay in registers. Tiles are few enough for a wave to read every earlier
+// tile's byte count at once, four a lane, so the offset is one trip to the
+// device's coherence point after the last of them is published. (A tile waits
+// only on lower-numbered ones, which publish before they wait.) The last tile
+// ends the stream; it has seen every tile's count, so every tile has read the
+// range, and it clears the slots for the next call.
+//
+// Bound: latencies (a launch, the extrema, the earlier tiles' counts) and the
+// count, 22 vector instructions for 64 blocks: 365x731 float64 values, b = 128,
+// absolute bound, 17.9 us a call in three launches, 12.4 in two; 2^20 float32
+// values 18.4 and 15.2. With a scan workgroup, an offset takes two trips: 196608
+// float32 values 12.9 us, so 11.3.
+template <typename T, int B>
+__global__ __launch_bounds__((64 * EncGeo<T, B>::ROWS)) void k_mid(CBatch b) {
+  using U = typename Traits<T>::U;
+  using G = EncGeo<T, B>;
+  constexpr int EPL = G::EPL, LPB = G::LPB, BYTES = Traits<T>::BYTES;
+  constexpr uint32_t NW = G::ROWS, RING = G::RING / G::SUB;
+  constexpr int U4 = 4;  // words of 64 blocks in flight
+  __shared__ uint32_t s_all[NW], s_ahead[NW], s_row[NW], s_tot[NW], s_base, s_ok;
+  __shared__ __align__(16) uint8_t s_ring[NW * (RING + G::SLACK)];
+  const FieldC f = field_at<kSingle>(b, 0);
+  const uint32_t nblk = (uint32_t)f.nblk, t = blockIdx.x, kb = t * G::TBLK;
+  const bool last = t + 1 == gridDim.x;
+  const uint32_t wave = uniform(threadIdx.x / kWave);
+  const uint32_t lane = (uint32_t)lane_id(), lig = lane % LPB;
+  const uint32_t lk = wave * G::GPW + lane / LPB;  // the lane's block of the tile
+
+  // the extrema of a block, and of the field's blocks 64 at a time
+  using v2u = unsigned int __attribute__((ext_vector_type(2)));
+  using v4u = unsigned int __attribute__((ext_vector_type(4)));
+  const __amdgpu_buffer_rsrc_t re = buffer_of(f.stats, nblk * 2u * (uint32_t)sizeof(U));
+  auto extrema = [&](uint32_t k, U& lo, U& hi) {
+    if constexpr (sizeof(U) == 4) {
+      const v2u u = __builtin_amdgcn_raw_buffer_load_b64(re, (int)(k * 8u), 0, 0);
+      lo = u.x;
+      hi = u.y;
+    } else {
+      const v4u u = __builtin_amdgcn_raw_buffer_load_b128(re, (int)(k * 16u), 0, 0);
+      lo = ((uint64_t)u.y << 32) | u.x;
+      hi = ((uint64_t)u.w << 32) | u.z;
+    }
+  };
+  const uint32_t words = (nblk + 63) / 64;
+  U lo[U4], hi[U4], kmin, kmax;
+#pragma unroll
+  for (int u = 0; u < U4; ++u) extrema((wave + (uint32_t)u * NW) * 64u + lane, lo[u], hi[u]);
+  extrema(kb + lk, kmin, kmax);
+  T x[EPL];
+  {
+    const uint64_t i0 = (uint64_t)kb * B;
+    const __amdgpu_buffer_rsrc_t rs =
+        buffer_of(reinterpret_cast<const T*>(f.in) + i0,
+                  (uint32_t)std::min<uint64_t>(f.n - i0, (uint64_t)G::TBLK * B) * (uint32_t)sizeof(T));
+    row_load<T, B, EPL>(x, rs, 0, (int)wave, 1u);
+  }
+  uint64_t e_bits;
+  if (f.eb_mode != 1) {
+    e_bits = bound_of(f, ~0ull, 0ull);
+  } else {
+    const bool clean = *f.clean == kCleanWord;
+    e_bits = slots_bound(f);  // (of any words where they are not clean)
+    if (!clean) {  // first use of the workspace: the chunks' partials
+      const uint64_t nchunks = cdiv(cdiv(f.n, (uint64_t)Geo<T, B>::TILE), (uint64_t)kStatsChunk);
+      uint64_t plo = ~0ull, phi = 0;
+      for (uint64_t i = lane; i < nchunks; i += kWave) {
+        const ulonglong2 p = reinterpret_cast<const ulonglong2*>(f.parts)[i];
+        plo = p.x < plo ? p.x : plo;
+        phi = p.y > phi ? p.y : phi;
+      }
+      e_bits = bound_of(f, group_min<kWave, uint64_t>(plo), group_max<kWave, uint64_t>(phi));
+    }
+  }
+  const T e = from_bits<T>((U)e_bits);
+
+  uint32_t all = 0, ahead = 0;
+  for (uint32_t w0 = wave; w0 < words; w0 += U4 * NW) {
+    U nlo[U4], nhi[U4];
+#pragma unroll
+    for (int u = 0; u < U4; ++u) extrema((w0 + (uint32_t)(U4 + u) * NW) * 64u + lane, nlo[u], nhi[u]);
+#pragma unroll
+    for (int u = 0; u < U4; ++u) {
+      const uint32_t k0 = (w0 + (uint32_t)u * NW) * 64u;
+      if (u > 0 && k0 >= nblk) break;
+      const uint64_t m = stored_blocks<T>(lo[u], hi[u], e, k0 + lane < nblk);
+      const uint64_t below = k0 + 64u <= kb ? ~0ull : k0 >= kb ? 0ull : (1ull << (kb - k0)) - 1ull;
+      all += (uint32_t)__popcll(m);
+      ahead += (uint32_t)__popcll(m & below);
+      // state bits leave with the tile of their first block
+      if (k0 - kb < (uint32_t)G::TBLK && lane == 0) {
+        uint8_t* const to = f.out + 96 + k0 / 8;
+        if (k0 + 64u <= nblk) {
+          *reinterpret_cast<uint64_t*>(to) = m;
+        } else {
+          for (uint32_t i = 0; i < (nblk - k0 + 7) / 8; ++i) to[i] = (uint8_t)(m >> (8 * i));
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U4; ++u) {
+      lo[u] = nlo[u];
+      hi[u] = nhi[u];
+    }
+  }
+  BlockPlan<T> plan = plan_block<T>(kmin, kmax, e);
+  const bool present = kb + lk < nblk;
+  if (!present) plan.K = 0;
+  int K = plan.K;
+  T mu = plan.mu;
+  const uint64_t has = __ballot(K != 0);
+  if (lane == 0) {
+    s_all[wave] = all;
+    s_ahead[wave] = ahead;
+    s_row[wave] = (uint32_t)__popcll(has & first_lanes<LPB>());
+  }
+  __syncthreads();
+  uint32_t n_nc = 0, rank0 = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < NW; ++i) {
+    n_nc += s_all[i];
+    rank0 += s_ahead[i] + (i < wave ? s_row[i] : 0u);
+  }
+  n_nc = uniform(n_nc);
+  rank0 = uniform(rank0);
+
+  const Sections sec = sections(nblk, n_nc, BYTES, B, 0);
+  const uint32_t ring0 = uniform(lds_address(s_ring + wave * (RING + G::SLACK)));
+  uint32_t wbytes = 0;
+  if (has != 0) {
+    const int rem = (int)(uint32_t)std::min<uint64_t>(f.n - (uint64_t)kb * B, (uint64_t)G::TBLK * B) -
+                    (int)(lk * B + lig * EPL);
+    const int cnt = rem < 0 ? 0 : (rem > EPL ? EPL : rem);
+    const bool stored = K != 0;
+    const bool tail = __ballot(stored && cnt != EPL) != 0;
+    RowWords<T, B> w;
+    w.code(x, mu, K, K > 0 && plan.verify, __ballot(K < 0 || (K > 0 && plan.verify)) != 0, e, cnt, tail, lig);
+    if (K < 0) mu = (T)0;
+    const uint32_t inc = wave_incl_sum_u32(w.lb);
+    const uint64_t firsts = has & first_lanes<LPB>();
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, rank0 - (lig != 0 ? 1u : 0u)));
+    wbytes = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    const uint32_t start = ring0 + inc - w.lb, end = start + w.lb;
+    RunPacker pk(end);
+    w.pack(pk, cnt, tail, end);
+    pk.or_head(start);
+    if (stored) {
+      if (lig == 0) f.out[sec.kbytes + rank] = K < 0 ? kRawK : (uint8_t)K;
+      uint8_t* const cdst = f.out + sec.codes + ((uint64_t)rank * (uint32_t)(B / 4) + lig * (EPL / 4));
+      if constexpr (EPL == 8)
+        *reinterpret_cast<uint16_t*>(cdst) = (uint16_t)(((w.codes >> 8) & 0xFFu) | ((w.codes & 0xFFu) << 8));
+      else
+        *reinterpret_cast<uint32_t*>(cdst) = __builtin_bswap32(w.codes);
+    }
+  }
+  if (lig == 0 && present) reinterpret_cast<T*>(f.out + sec.mu)[kb + lk] = mu;
+  if (lane == 0) s_tot[wave] = wbytes;
+  __syncthreads();
+  uint32_t total = 0, before = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < NW; ++i) {
+    const uint32_t v = uniform(s_tot[i]);
+    before += i < wave ? v : 0u;
+    total += v;
+  }
+  if (threadIdx.x == 0) status_store(f.enc_mid + t, kFlagAgg | total);
+  if (last) {
+    write_stream_header(f, e_bits, n_nc, 0);
+    if (threadIdx.x == 0) {
+      f.ctr->n_nc = n_nc;
+      *f.out_size = kSizePending;
+    }
+  }
+  if (wave == 0) {
+    constexpr int R = (int)kMidTiles / kWave;
+    uint32_t sum = 0, spins = 0;
+    bool ok = true;
+    for (;;) {
+      bool missing = false;
+      sum = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // (lanes past the tile read word 0, as its wait may need it anyway)
+        const uint32_t j = (uint32_t)(r * kWave) + lane;
+        const uint64_t w = status_load(f.enc_mid + (j < t ? j : 0u));
+        missing |= j < t && (w >> 62) == 0;
+        sum += j < t ? (uint32_t)w : 0u;
+      }
+      if (__ballot(missing) == 0) break;
+      if (++spins > kSpinLimit) {
+        ok = false;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    sum = wave_total_u32(sum);
+    if (lane == 0) {
+      s_base = sum;
+      s_ok = ok;
+    }
+  }
+  __syncthreads();
+  const uint32_t base = uniform(s_base);
+  if (s_ok == 0) {  // a bounded wait gave up: the field has no stream (finish_stream)
+    if (threadIdx.x == 0) {
+      atomicMax(&f.ctr->err, 1u);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
+      __hip_atomic_store(f.out_size, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return;
+  }
+  copy_out(f.out, sec.mid + base + before, s_ring + wave * (RING + G::SLACK), 0, RING / 16 - 1, wbytes);
+  if (last) {
+    if (threadIdx.x < kRangeSlots)
+      *reinterpret_cast<ulonglong2*>(f.range + threadIdx.x * (kRangeStride / 8)) = make_ulonglong2(0, 0);
+    if (threadIdx.x == 0) {
+      *f.clean = kCleanWord;
+      finish_stream(f, (uint64_t)base + total);
+    }
+  }
+}
+
 // --------------------------------------------------------------- finalize ---
 
 // The finishing pass of a batch, one workgroup a field (a single call
@@ -1501,11 +1759,11 @@ __global__ void k_finalize(CBatch b) {
 
 // ---------------------------------------------------------------- launch ---
 
-// (The smallest fields ask for a quarter of the LDS, so that a busy compute unit
+// (The smallest fields ask for a half or a third of the LDS, so that a busy compute unit
 // takes them too.)
 template <typename T, int B>
 void launch_small(const CBatch& b, hipStream_t stream) {
-  constexpr uint32_t few = small_waves<T, B>(kSmallestBytes), all = small_waves<T, B>(kSmallBytes);
+  constexpr uint32_t few = small_waves<T, B>(kSmallestBytes), all = small_waves<T, B>(kSmallBytes<T>);
   const uint32_t waves = (uint32_t)cdiv(b.one.nblk, EncGeo<T, B>::WBLK);
   if (waves <= few)
     k_small<T, B, few><<<1, 64 * waves, 0, stream>>>(b);
@@ -1520,14 +1778,34 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
     fn();
     if (hook) hook(name, stream, 0);
   };
-  // The line: the field fits one workgroup's LDS. At 128 KiB (32768 float32
-  // values, b = 128, sixteen waves) one launch takes 12.9 us a call, three 15.9
-  // (float64: 12.2 and 16.2). (A shard's bound comes from elsewhere.)
-  if (!b.fields && !b.any_empty && b.one.next_range == 0 && b.one.n * (b.one.dtype == 0 ? 4 : 8) <= kSmallBytes) {
+  // The lines lie where the ways meet (b = 128, us a call): one launch of one
+  // workgroup takes 8.5 at 64 KiB of float32 values, 10.9 at 96 KiB, two launches
+  // 10.1 and 10.3; float64 8.3 at 64 KiB, 10.5 at 96, 12.1 at 128 and 11.4, 10.6,
+  // 11.3. (A shard's bound comes from elsewhere.)
+  const bool single = !b.fields && !b.any_empty && b.one.next_range == 0;
+  if (single && b.one.n * (b.one.dtype == 0 ? 4 : 8) <= (b.one.dtype == 0 ? kSmallBytes<float> : kSmallBytes<double>)) {
     if (b.one.dtype == 0)
       run("k_small", [&] { launch_small<float, B>(b, stream); });
     else
       run("k_small", [&] { launch_small<double, B>(b, stream); });
+    return hipGetLastError();
+  }
+  // Two launches or three: beyond one tile a compute unit the persistent
+  // encoder overlaps its tiles, and every workgroup's count grows with the
+  // blocks. float32, b = 128: 8192 blocks in 128 tiles 15.2 us in two, 18.4 in
+  // three; 16384 blocks 19.4 and 18.9; b = 256, 256 tiles 16.7 and 19.2, 320
+  // tiles 21.6 and 21.0. float64, b = 128: 8192 blocks in 256 tiles 17.5 and
+  // 18.9, 10240 in 320 22.1 and 20.3.
+  if (single && b.one.nblk <= kMidBlocks && b.tiles_enc[0] + b.tiles_enc[1] <= kMidTiles) {
+    const uint32_t gs = (uint32_t)(b.tiles_stats[0] + b.tiles_stats[1]);
+    const uint32_t ge = (uint32_t)(b.tiles_enc[0] + b.tiles_enc[1]);
+    if (b.one.dtype == 0) {
+      run("k_stats", [&] { k_stats<float, B><<<gs, 256, 0, stream>>>(b); });
+      run("k_mid", [&] { k_mid<float, B><<<ge, 64 * EncGeo<float, B>::ROWS, 0, stream>>>(b); });
+    } else {
+      run("k_stats", [&] { k_stats<double, B><<<gs, 256, 0, stream>>>(b); });
+      run("k_mid", [&] { k_mid<double, B><<<ge, 64 * EncGeo<double, B>::ROWS, 0, stream>>>(b); });
+    }
     return hipGetLastError();
   }
   if (b.tiles_stats[0] + b.tiles_stats[1] > 0) {

@@ -56,21 +56,29 @@ def test_streams_equal_the_oracle(kind, block, dtype):
 
 @pytest.mark.parametrize("dtype", ["float32", "float64"])
 @pytest.mark.parametrize("block", [8, 32, 128, 1024])
-def test_one_launch_and_three_meet(block, dtype):
-    """Sizes on both sides of where a single call goes from one workgroup to
-    three launches (32 and 128 KiB of values), with non-finite values, and a
-    workspace that holds anything."""
+def test_one_two_and_three_launches_meet(block, dtype):
+    """Sizes on both sides of where a single call goes from one workgroup to two
+    launches (64 KiB of float32, 96 of float64) and on to three (8192 blocks or
+    256 tiles), a size of the smaller workgroup, and of ragged tiles: with
+    non-finite values, blocks whose half range is the bound itself, and a
+    workspace that first holds anything and then what a call left."""
     w = 4 if dtype == "float32" else 8
-    for kib in (32, 128):
-        for n in (kib * 1024 // w - 1, kib * 1024 // w, kib * 1024 // w + 1):
-            for kind in ("mixed", "noise"):
-                x = field(kind, n, dtype, block)
+    small, most = (16384 if w == 4 else 12288), min(8192 * block, 256 * max(8 * block, 32768 // w))
+    for line in (32768 // w, small, 100_003, most):
+        for n in (line - 1, line, line + 1):
+            for kind in ("mixed", "noise", "steps") if n < 1 << 18 else ("mixed",):
+                if kind == "steps":
+                    x = (np.random.default_rng(n).integers(0, 4, n) * 0.5).astype(dtype)
+                    x[: n // 2] = np.minimum(x[: n // 2], 1)
+                else:
+                    x = field(kind, n, dtype, block)
                 x[n // 3] = np.inf
-                for eb, mode in ((1e-2, "rel"), (1e-3, "abs"), (0.0, "rel")):
+                for eb, mode in ((1e-2, "rel"), (0.5, "abs"), (0.0, "rel")):
                     ref = szref.compress(x, eb, mode, block)
                     ws = torch.full((szx.workspace_size(dtype, (n,), eb, mode, block),), 0x5A, dtype=torch.uint8,
                                     device="cuda")
-                    out, size = szx.compress(torch.from_numpy(x).cuda(), eb, mode, block, ws=ws)
-                    torch.cuda.synchronize()
-                    m = int(size.cpu().view(torch.int64))
-                    assert m == ref.size and np.array_equal(out[:m].cpu().numpy(), ref), (n, kind, eb, mode)
+                    for use in range(2):
+                        out, size = szx.compress(torch.from_numpy(x).cuda(), eb, mode, block, ws=ws)
+                        torch.cuda.synchronize()
+                        m = int(size.cpu().view(torch.int64))
+                        assert m == ref.size and np.array_equal(out[:m].cpu().numpy(), ref), (n, kind, eb, mode, use)
