@@ -67,8 +67,8 @@ __global__ __launch_bounds__(256) void k_dinit(DBatch b) {
 // own clears them. Workgroup 0 of the call's first index launch (dispatched
 // first) clears them and then stores the call's token in the go word; every
 // other workgroup waits for the token before its first publish or report
-// (its stream loads are already out). The second index launch of a mixed
-// batch finds the token there and clears nothing. The token changes with
+// (its stream loads are already out). A second index launch (b = 1024, both
+// types) finds the token there and clears nothing. The token changes with
 // every call: the last decode launch advances the epoch it comes from, when
 // no index tile reads it any more.
 __device__ __forceinline__ uint64_t gate_token(const DBatch& b) {
@@ -114,6 +114,11 @@ __device__ __forceinline__ void gate_wait(const DBatch& b, uint32_t* status) {
     }
   }
   __syncthreads();
+}
+
+__device__ __forceinline__ void gate_advance(const DBatch& b) {
+  __hip_atomic_fetch_add((__attribute__((address_space(1))) uint64_t*)(as_global(b.gate) + kGateEpochWord), 1ull,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Header words (nothing writes a stream that is being decoded: scalar loads).
@@ -500,6 +505,33 @@ __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
   const uint64_t g = blockIdx.x;
   const FieldD f = field_at(b, dfield_of(b.field_idx[Traits<T>::BYTES / 8], g));
   dindex_tile<T, B, MODE>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+}
+
+// A batch of both element types runs each pass as one launch, the float32
+// fields' workgroups first, where the two types' kernels need alike registers
+// and LDS (below b = 1024): a launch for each type has its own start and its
+// own nearly empty end. Fields of 1 MiB on average, b = 128, in a launch a type,
+// and so: 8 of them 23.6 -> 13.5 us a call (graph replays), 256 of them 165 ->
+// 159; 32 fields of 256 KiB 24.2 -> 14.7, at b = 512 40.3 -> 22.9.
+template <int B>
+constexpr bool kOneLaunch = B < 1024;
+
+template <int B, int MODE>
+__global__ __launch_bounds__(256) void k_dindex_both(DBatch b) {
+  constexpr int W4 = DecGeo<float, B>::WBLK, W8 = DecGeo<double, B>::WBLK;
+  __shared__ uint32_t s_scan[2 * kWavesPerWG];
+  __shared__ uint64_t s_r0, s_m0;
+  __shared__ uint32_t s_wave[kClsBlocks / (W4 < W8 ? W4 : W8) + 1];
+  __shared__ int s_flag;
+  uint64_t g = blockIdx.x;
+  if (g < b.tiles_idx[0]) {
+    const FieldD f = field_at(b, dfield_of(b.field_idx[0], g));
+    dindex_tile<float, B, MODE>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+  } else {
+    g -= b.tiles_idx[0];
+    const FieldD f = field_at(b, dfield_of(b.field_idx[1], g));
+    dindex_tile<double, B, MODE>(b, f, (uint32_t)(g - f.base_idx), s_scan, &s_r0, &s_m0, s_wave, &s_flag);
+  }
 }
 
 // A direct index's totals of the first n <= kDirectTiles index tiles, four a
@@ -907,9 +939,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DecGeo<T, B
   decode_tile<T, B, false>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage, nullptr);
   // the call's last decode launch advances the gate's epoch (no index tile
   // reads it any more); at the end, so that no load comes after the atomic
-  if (g == 0 && threadIdx.x == 0 && !b.direct && (sizeof(T) == 8 || b.tiles_dec[1] == 0))
-    __hip_atomic_fetch_add((__attribute__((address_space(1))) uint64_t*)(as_global(b.gate) + kGateEpochWord), 1ull,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (g == 0 && threadIdx.x == 0 && !b.direct && (sizeof(T) == 8 || b.tiles_dec[1] == 0)) gate_advance(b);
+}
+
+template <int B>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    DecGeo<float, B>::WAVES < DecGeo<double, B>::WAVES ? DecGeo<float, B>::WAVES : DecGeo<double, B>::WAVES))) void
+k_decode_both(DBatch b) {
+  __shared__ __align__(16) uint8_t s_stage[kWavesPerWG * std::max(DecGeo<float, B>::STAGE, DecGeo<double, B>::STAGE)];
+  uint64_t g = blockIdx.x;
+  if (g < b.tiles_dec[0]) {
+    const FieldD f = field_at(b, dfield_of(b.field_dec[0], g));
+    decode_tile<float, B, false>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage, nullptr);
+  } else {
+    g -= b.tiles_dec[0];
+    const FieldD f = field_at(b, dfield_of(b.field_dec[1], g));
+    decode_tile<double, B, false>(f, (uint32_t)(g - f.base_dec), b.direct != 0, s_stage, nullptr);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !b.direct) gate_advance(b);
 }
 
 // A small field's decompression in one launch: every workgroup indexes the whole
@@ -957,6 +1004,17 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
     else
       run("k_dsmall", [&] { k_dsmall<double, B><<<(uint32_t)b.tiles_dec[1], 256, 0, stream>>>(b); });
     return hipGetLastError();
+  }
+  if constexpr (kOneLaunch<B>) {
+    if (b.fields && b.tiles_idx[0] && b.tiles_idx[1]) {
+      const uint32_t gi = (uint32_t)(b.tiles_idx[0] + b.tiles_idx[1]);
+      if (b.direct)
+        run("k_dindex", [&] { k_dindex_both<B, kDirect><<<gi, 256, 0, stream>>>(b); });
+      else
+        run("k_dindex", [&] { k_dindex_both<B, kChained><<<gi, 256, 0, stream>>>(b); });
+      run("k_decode", [&] { k_decode_both<B><<<(uint32_t)(b.tiles_dec[0] + b.tiles_dec[1]), 256, 0, stream>>>(b); });
+      return hipGetLastError();
+    }
   }
   for (int dt = 0; dt < 2; ++dt) {
     const uint32_t n = (uint32_t)b.tiles_idx[dt];

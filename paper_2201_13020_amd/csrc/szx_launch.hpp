@@ -40,8 +40,9 @@ struct CBatch {
   const FieldC* fields;          // device array, or nullptr: the single field `one`
   // Per element type (0: float32, 1: float64) each pass numbers the tiles of
   // that type's fields consecutively; the maps take such a number to its
-  // field (nullptr: field 0). Each pass runs one kernel per element type
-  // present, so no kernel carries the registers of both.
+  // field (nullptr: field 0). A pass over both types is one launch, the
+  // float32 fields' tiles first, or (b = 1024, where no kernel should carry the
+  // registers of both) one a type.
   const uint32_t* field_stats[2];  // extrema chunk -> field
   const uint32_t* field_cls[2];    // classification tile -> field
   const uint32_t* field_enc[2];    // encode tile -> field
