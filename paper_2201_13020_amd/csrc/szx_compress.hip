@@ -24,13 +24,12 @@
 //               from a single-pass prefix sum over the tiles (Sec. V-B) by
 //               workgroup 0, and while a tile waits for it the next tile is
 //               encoded. Bytes are packed in LDS and leave in aligned 16-byte
-//               stores. In a single call workgroup 0 ends the stream: the
-//               mid-byte total and the stream size.
+//               stores. The stream ends there too (mid-byte total, stream
+//               size): by workgroup 0 in a single call, with its field's last
+//               tile in a batch.
 //   Short single calls take fewer launches: one of one workgroup (k_small), or
 //   k_stats and one more launch that classifies and encodes (k_mid).
-//   k_finalize  batches: every field's mid-byte total and stream size, and
-//               the header of fields without values (a single call only
-//               runs it when its field has no values)
+//   k_finalize  the header of fields without values (only where there are any)
 #include <algorithm>
 
 #include "szx_device.hpp"
@@ -314,6 +313,31 @@ __global__ __launch_bounds__(256) void k_stats(CBatch b) {
   }
 }
 
+// A batch of both element types runs each pass as one launch, the float32
+// fields' workgroups first, where the two types' kernels need alike registers
+// and LDS (below b = 1024): a launch for each type has its own start and its
+// own nearly empty end. Fields of 1 MiB on average, b = 128, in a launch a type,
+// and so: 8 of them 40.6 -> 28.2 us a call (graph replays), 256 of them 359 ->
+// 344; 32 fields of 256 KiB 49.1 -> 33.4. (4.7 us of each is the pass that ended
+// the batch's streams, which the encode pass does now.)
+template <int B>
+constexpr bool kOneLaunch = B < 1024;
+
+template <int B>
+__global__ __launch_bounds__(256) void k_stats_both(CBatch b) {
+  __shared__ uint64_t s_lo[kWavesPerWG], s_hi[kWavesPerWG];
+  uint64_t g = blockIdx.x;
+  for (uint64_t i = g * kWG + threadIdx.x; i < b.zero_words; i += (uint64_t)gridDim.x * kWG) b.zero_begin[i] = 0;
+  if (g < b.tiles_stats[0]) {
+    const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_stats[0], g));
+    stats_chunk<float, B>(f, g - f.base_stats, s_lo, s_hi);
+  } else {
+    g -= b.tiles_stats[0];
+    const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_stats[1], g));
+    stats_chunk<double, B>(f, g - f.base_stats, s_lo, s_hi);
+  }
+}
+
 // ----------------------------------------------------------------- range ---
 
 __device__ __forceinline__ uint64_t bound_of(const FieldC& f, uint64_t lo, uint64_t hi) {
@@ -523,15 +547,17 @@ __device__ __forceinline__ uint64_t write_stream_header(const FieldC& f, uint64_
 // the mid-byte total (the header's last field) and the stream size, or 0
 // there if a bounded wait of this compression gave up. (A wait that gives up
 // meanwhile raises the error first and then clears the size itself; the error
-// is read once more after the size is stored, so one of the two sees the
-// other.)
+// is read once more after the size has been stored, so one of the two sees the
+// other. Both words are device-scope atomics, so the wait for the store orders
+// them; a fence would drop the XCD's L2, once a field: 256 batched fields 357
+// us a call, so 344.)
 __device__ __forceinline__ void finish_stream(const FieldC& f, uint64_t mid_total) {
   const uint64_t mid_off = sections(f.nblk, f.ctr->n_nc, f.dtype == 0 ? 4 : 8, f.b, 0).mid;
   reinterpret_cast<uint64_t*>(f.out)[11] = mid_total;
   const uint64_t size = mid_off + mid_total;
   if (__hip_atomic_load(&f.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
     __hip_atomic_store(f.out_size, size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (__hip_atomic_load(&f.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
   }
   __hip_atomic_store(f.out_size, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -694,6 +720,23 @@ __global__ __launch_bounds__(256) void k_classify(CBatch b) {
   const uint64_t g = blockIdx.x;
   const FieldC f = field_at(b, field_of(b.field_cls[Traits<T>::BYTES / 8], g));
   classify_tile<T, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+}
+
+template <int B>
+__global__ __launch_bounds__(256) void k_classify_both(CBatch b) {
+  __shared__ uint32_t s_scan[2 * kWavesPerWG];
+  __shared__ uint32_t s_state[kClsBlocks / 32];
+  __shared__ uint64_t s_base;
+  __shared__ uint64_t s_red[2 * kWavesPerWG];
+  uint64_t g = blockIdx.x;
+  if (g < b.tiles_cls[0]) {
+    const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_cls[0], g));
+    classify_tile<float, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+  } else {
+    g -= b.tiles_cls[0];
+    const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_cls[1], g));
+    classify_tile<double, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+  }
 }
 
 // ---------------------------------------------------------------- encode ---
@@ -1089,8 +1132,9 @@ struct EncShared {
 // dword and tickets for constant tiles); a batch of 256 float32 fields, 175 us
 // (239). Smaller workgroups without the pending tile, eight a compute unit,
 // took 51 us: every tile then waits 4-5 us for its offset.
+// wid is the workgroup's number among wgs.
 template <typename T, int B, int BATCH>
-__device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint8_t* s_ring) {
+__device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint8_t* s_ring, uint32_t wid, uint32_t wgs) {
   using U = typename Traits<T>::U;
   using G = EncGeo<T, B>;
   constexpr int EPL = G::EPL, LPB = G::LPB, SUB = G::SUB;
@@ -1098,9 +1142,8 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint
   constexpr uint32_t RING = G::RING;
   constexpr uint32_t MASK16 = RING / 16 - 1;
   constexpr int DT = sizeof(T) == 4 ? 0 : 1;
-  const uint32_t wid = blockIdx.x - 1;
   const uint32_t cls = wid % kTicketClasses;
-  const bool direct = gridDim.x > b.tiles_enc[DT];  // a workgroup for every tile
+  const bool direct = wgs >= b.tiles_enc[DT];  // a workgroup for every tile
   const FieldC* const one = BATCH == kSingle ? field_ref<BATCH>(b, 0) : nullptr;
   const uint64_t ntiles = BATCH == kSingle ? as_constant(one->ctr)->n_tiles : b.tiles_enc[DT];
   const uint32_t* const list = BATCH == kSingle ? as_global(one->enc_list) : nullptr;
@@ -1196,6 +1239,11 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint
     // is checked against it)
     if (ok && mid + base + p_total <= sections(nblk, nblk, BYTES, B, fp->n * BYTES).total)
       copy_out(as_global(fp->out), mid + base + p_before, stage, p_at / 16, MASK16, p_bytes);
+    // a batch's field ends with its last tile
+    if constexpr (BATCH == kBatch) {
+      if (ok && p_tile == (uint32_t)cdiv(nblk, (uint64_t)G::TBLK) - 1 && threadIdx.x == 0)
+        finish_stream(field_at<kBatch>(b, p_field), base + p_total);
+    }
     pend = false;
   };
 
@@ -1339,7 +1387,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<T, B
     }
     return;
   }
-  encode_pass<T, B, BATCH>(b, s_sh.enc, s_ring);
+  encode_pass<T, B, BATCH>(b, s_sh.enc, s_ring, blockIdx.x - 1, gridDim.x - 1);
+}
+
+// Both types of a batch: the float32 tiles and then the float64 tiles, also for
+// workgroup 0, which scans them (a scan workgroup for the float64 tiles alone
+// would wait through all of the others').
+template <int B>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<float, B>::WAVES))) void k_encode_both(
+    CBatch b) {
+  using G4 = EncGeo<float, B>;
+  using G8 = EncGeo<double, B>;
+  static_assert(G4::WAVES == G8::WAVES, "the two types need alike registers and LDS");
+  __shared__ union {
+    EncShared enc;
+    ScanShared scan;
+  } s_sh;
+  __shared__ __align__(16) uint8_t s_ring[kWavesPerWG * std::max(G4::RING + G4::SLACK, G8::RING + G8::SLACK)];
+  if (blockIdx.x == 0) {
+#pragma unroll 1
+    for (uint32_t dt = 0; dt < 2; ++dt) {
+      const FieldC* f = field_ref<kBatch>(b, *as_constant(b.field_enc[dt]));
+      scan_workgroup(as_global(f->enc_mid), b.tiles_enc[dt], &as_global(f->ctr)->err, 1u, s_sh.scan);
+      __syncthreads();
+    }
+    return;
+  }
+  const uint32_t wid = blockIdx.x - 1, wgs = gridDim.x - 1;
+  encode_pass<float, B, kBatch>(b, s_sh.enc, s_ring, wid, wgs);
+  __syncthreads();
+  encode_pass<double, B, kBatch>(b, s_sh.enc, s_ring, wid, wgs);
 }
 
 // ------------------------------------------------------------------ small ---
@@ -1734,22 +1811,12 @@ __global__ __launch_bounds__((64 * EncGeo<T, B>::ROWS)) void k_mid(CBatch b) {
 
 // --------------------------------------------------------------- finalize ---
 
-// The finishing pass of a batch, one workgroup a field (a single call
-// finishes its stream in the encode pass and needs this pass only when it has
-// no values): a field with values gets its mid-byte total and stream size;
-// a field without values has no extrema, classification or encode tiles and
-// gets its whole header (the bound from an empty range) and size.
+// Fields without values, one workgroup a field of the call: they have no
+// extrema, classification or encode tiles and get their whole header here (the
+// bound from an empty range) and their size.
 __global__ void k_finalize(CBatch b) {
   const FieldC f = field_at(b, blockIdx.x);
-  if (f.nblk != 0) {
-    if (threadIdx.x == 0) {
-      // the scan over the type's tiles: the sum up to the field's last one
-      // less the sum before its first
-      const uint64_t last = f.enc_mid[cdiv(f.nblk, enc_blocks(f.b, f.dtype == 0 ? 4 : 8)) - 1] & kValueMask;
-      finish_stream(f, last - (f.base_enc > 0 ? f.enc_mid[-1] & kValueMask : 0));
-    }
-    return;
-  }
+  if (f.nblk != 0) return;
   const int rel = f.eb_mode == 1;
   const uint64_t e_bits = f.dtype == 0 ? (uint64_t)bits_of(bound_from<float>(rel, f.eb, ~0ull, 0ull))
                                        : (uint64_t)bits_of(bound_from<double>(rel, f.eb, ~0ull, 0ull));
@@ -1808,17 +1875,31 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
     }
     return hipGetLastError();
   }
-  if (b.tiles_stats[0] + b.tiles_stats[1] > 0) {
+  // at least one workgroup per ticket class: tiles of a class without one
+  // would never be encoded (and every later tile would wait for them)
+  auto encoders = [&](int dt) {
+    return (uint32_t)std::min<uint64_t>(b.tiles_enc[dt], std::max<uint64_t>(g.encode_wgs[dt], kTicketClasses));
+  };
+  bool done = b.tiles_stats[0] + b.tiles_stats[1] == 0;
+  if constexpr (kOneLaunch<B>) {
+    if (b.fields && b.tiles_stats[0] && b.tiles_stats[1]) {
+      const uint32_t gs = (uint32_t)(b.tiles_stats[0] + b.tiles_stats[1]);
+      const uint32_t gc = (uint32_t)(b.tiles_cls[0] + b.tiles_cls[1]);
+      const uint32_t ge = std::max(encoders(0), encoders(1)) + 1;
+      run("k_stats", [&] { k_stats_both<B><<<gs, 256, 0, stream>>>(b); });
+      run("k_classify", [&] { k_classify_both<B><<<gc, 256, 0, stream>>>(b); });
+      run("k_encode", [&] { k_encode_both<B><<<ge, 256, 0, stream>>>(b); });
+      done = true;
+    }
+  }
+  if (!done) {
     if (b.tiles_stats[0]) run("k_stats", [&] { k_stats<float, B><<<(uint32_t)b.tiles_stats[0], 256, 0, stream>>>(b); });
     if (b.tiles_stats[1]) run("k_stats", [&] { k_stats<double, B><<<(uint32_t)b.tiles_stats[1], 256, 0, stream>>>(b); });
     if (b.tiles_cls[0]) run("k_classify", [&] { k_classify<float, B><<<(uint32_t)b.tiles_cls[0], 256, 0, stream>>>(b); });
     if (b.tiles_cls[1]) run("k_classify", [&] { k_classify<double, B><<<(uint32_t)b.tiles_cls[1], 256, 0, stream>>>(b); });
     for (int dt = 0; dt < 2; ++dt) {
       if (!b.tiles_enc[dt]) continue;
-      // at least one workgroup per ticket class: tiles of a class without one
-      // would never be encoded (and every later tile would wait for them)
-      const uint64_t want = std::max<uint64_t>(g.encode_wgs[dt], kTicketClasses);
-      const uint32_t genc = (uint32_t)std::min<uint64_t>(b.tiles_enc[dt], want);
+      const uint32_t genc = encoders(dt);
       const bool batch = b.fields != nullptr;
       // workgroup 0 is the scan workgroup
       if (dt == 0 && !batch)
@@ -1831,8 +1912,7 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
         run("k_encode", [&] { k_encode<double, B, kBatch><<<genc + 1, 256, 0, stream>>>(b); });
     }
   }
-  // batches finish their streams here; a single call only without values
-  if (b.fields != nullptr || b.any_empty) run("k_finalize", [&] { k_finalize<<<b.nfields, 64, 0, stream>>>(b); });
+  if (b.any_empty) run("k_finalize", [&] { k_finalize<<<b.nfields, 64, 0, stream>>>(b); });
   return hipGetLastError();
 }
 

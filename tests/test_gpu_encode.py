@@ -82,3 +82,45 @@ def test_one_two_and_three_launches_meet(block, dtype):
                         torch.cuda.synchronize()
                         m = int(size.cpu().view(torch.int64))
                         assert m == ref.size and np.array_equal(out[:m].cpu().numpy(), ref), (n, kind, eb, mode, use)
+
+
+@pytest.mark.parametrize("block", [8, 32, 128, 512, 1024])
+@pytest.mark.parametrize("types", ["both", "float32", "float64", "few float32", "few float64"])
+def test_batches_of_one_and_both_types(types, block):
+    """Batches whose two types share their launches, and batches of one type:
+    fields without values, of one tile and of many, all workgroups or eight,
+    and (b = 8) an index that is chained; streams and decoded values against
+    the oracle, twice over the same workspace."""
+    sizes = [0, 1, 70_001, 30_000, 0, 250_003, block, 9]
+    fields = []
+    for i, n in enumerate(sizes):
+        for dt in ("float32", "float64"):
+            if types in ("both", dt) or (types[:3] == "few" and (types[4:] != dt or i == 3)):
+                x = field("mixed" if i % 2 else "smooth", max(n, 1), dt, block)[:n]
+                fields.append((x, (1e-3, 0.0, 1e-2)[i % 3], "rel" if i % 2 else "abs"))
+    if block == 8 and types == "both":
+        fields.append((field("smooth", 2_100_001, "float32", block), 1e-2, "rel"))
+    refs = [szref.compress(x, eb, mode, block) for x, eb, mode in fields]
+    b = szx.compress_batch([torch.from_numpy(x).cuda() for x, _, _ in fields], [f[1] for f in fields],
+                           [f[2] for f in fields], block)
+    for use in range(2):
+        if use:
+            b.set_geometry(8)
+        for o, size in zip(b.outs, b.sizes):
+            o.fill_(0xAB)
+            size.fill_(0xAB)
+        b.run()
+        torch.cuda.synchronize()
+        for i, ref in enumerate(refs):
+            m = int(b.sizes[i].cpu().view(torch.int64))
+            assert m == ref.size and np.array_equal(b.outs[i][:m].cpu().numpy(), ref), (i, use)
+    d = szx.decompress_batch(b.outs, [r.size for r in refs], [szx.inspect(r[:96].tobytes()) for r in refs])
+    for use in range(2):
+        for s in d.statuses:
+            s.fill_(0xAB)
+        d.run()
+        torch.cuda.synchronize()
+        for i, ref in enumerate(refs):
+            assert int(d.statuses[i].cpu().view(torch.int32)) == 0, (i, use)
+            y = szref.decompress(ref).ravel()
+            assert np.array_equal(d.outs[i][: y.size].cpu().numpy().view(np.uint8), y.view(np.uint8)), (i, use)
