@@ -278,20 +278,19 @@ __device__ __forceinline__ uint32_t block_mid_bytes(const BlockCodes<B>& c, uint
   }
   const uint32_t nb = (uint32_t)bytes_of((int)Kb);
   uint32_t sum = 0, over = 0;
-  // b/4 code bytes, 4 codes per byte, first value in the top bits
+  // b/4 code bytes, 4 codes per byte, first value in the top bits (a code's two
+  // bits lie in one byte, so only the short last block needs their order)
+  const bool brief = __ballot(nk < (uint32_t)B) != 0;
 #pragma unroll
   for (uint32_t j = 0; j < BlockCodes<B>::NW; ++j) {
-    uint32_t w;
-    if constexpr (B >= 16) {
-      w = __builtin_bswap32(c.raw[j]);
-    } else {
-      const uint32_t h2 = c.raw[0] & 0xFFFFu;
-      w = ((h2 & 0xFFu) << 24) | ((h2 >> 8) << 16);
+    uint32_t w = c.raw[j];
+    if constexpr (B < 16) w &= 0xFFFFu;
+    if (brief) {
+      const uint32_t first = 16 * j;  // value index of the word's first code
+      if (first >= nk) w = 0;
+      else if (nk - first < 16) w &= __builtin_bswap32(~0u << (2 * (16 - (nk - first))));  // codes past the block end
     }
-    const uint32_t first = 16 * j;  // value index of the top code of w
-    if (first >= nk) w = 0;
-    else if (nk - first < 16) w &= ~0u << (2 * (16 - (nk - first)));  // codes past the block end
-    sum += __popc(w & 0x55555555u) + 2u * __popc(w & 0xAAAAAAAAu);
+    sum += (uint32_t)__popc(w) + (uint32_t)__popc(w & 0xAAAAAAAAu);
     over |= w & (w >> 1) & 0x55555555u;  // a code of 3
   }
   if (nb == 2 && over) bad = true;
@@ -414,13 +413,19 @@ __device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, ui
   // stream holds, through buffer resources over just those bytes (32-bit
   // offsets from the tile's first rank; reads past them return zeros): every
   // load of the thread goes out before any of them is used.
+  // Blocks whose codes a thread has in flight: all, or two of b = 1024 (64
+  // registers a block). A load as each block is counted, in its branch, adds a
+  // memory latency a block: 32768 float32 values of b = 256, 512 and 1024 took
+  // 10.2, 15.1 and 25.2 us a call so, 8.2, 10.8 and 17.0 this way (with the count
+  // in memory order, of it 0.7 us at b = 128: 7.7 and 7.0).
+  constexpr int AHEAD = B < 1024 ? BPT : 2;
   const uint64_t have_nc = h.n_nc > R0 ? std::min<uint64_t>(h.n_nc - R0, (uint64_t)tnc) : 0;
   const __amdgpu_buffer_rsrc_t rk_ = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(in + h.sec.kbytes + R0), (short)0, (int)have_nc, 0x00020000);
   const __amdgpu_buffer_rsrc_t rc_ = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(in + h.sec.codes + R0 * (B / 4)), (short)0, (int)(have_nc * (B / 4)), 0x00020000);
   uint32_t kbv[BPT];
-  BlockCodes<B> cv[BPT];
+  BlockCodes<B> cv[AHEAD];
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
     // this block's rank from the tile's first: rex plus the thread's
@@ -428,9 +433,7 @@ __device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, ui
     const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
     const bool live = (ncb >> i) & 1u;
     kbv[i] = __builtin_amdgcn_raw_buffer_load_b8(rk_, live ? (int)rl : 0x40000000, 0, 0);
-    // up to b = 128 (32 code bytes a block); larger blocks load theirs as
-    // they are counted, which keeps their registers in bounds
-    if constexpr (B <= 128) load_codes<B>(rc_, live ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i]);
+    if (i < AHEAD) load_codes<B>(rc_, live ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i]);
   }
   uint32_t mid = 0, midb[BPT];
 #pragma unroll
@@ -441,11 +444,14 @@ __device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, ui
       const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
       if ((uint64_t)rl < have_nc) {
         const uint32_t nk = (uint32_t)std::min<uint64_t>((uint64_t)B, a.n - k * B);
-        if constexpr (B > 128) load_codes<B>(rc_, rl * (uint32_t)(B / 4), cv[i]);
-        mid += block_mid_bytes<T, B>(cv[i], kbv[i], nk, bad);
+        mid += block_mid_bytes<T, B>(cv[i % AHEAD], kbv[i], nk, bad);
       } else {
         bad = true;
       }
+    }
+    if (i + AHEAD < BPT) {
+      const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << (i + AHEAD)) - 1u));
+      load_codes<B>(rc_, (ncb >> (i + AHEAD)) & 1u ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i % AHEAD]);
     }
   }
   uint32_t tmid;
@@ -962,7 +968,7 @@ k_decode_both(DBatch b) {
 // A small field's decompression in one launch: every workgroup indexes the whole
 // field (one index tile, kept in LDS) and decodes its own tile. Two launches
 // spend most of a small call in their latencies: 4099 float32 values take 10.3
-// us a call in two, 8.0 in one.
+// us a call in two, 8.0 in one (7.3 with the shorter count).
 template <typename T, int B>
 __global__ __launch_bounds__(256) void k_dsmall(DBatch b) {
   using G = DecGeo<T, B>;
@@ -997,7 +1003,7 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
   }
   // The line: one index tile, and codes that every workgroup can look through
   // (131072 values: 32 KiB of them). At 131072 float32 values, b = 128, 32
-  // workgroups: one launch 8.3 us, two 10.3.
+  // workgroups: one launch 8.3 us, two 10.3 (7.5 in one with the shorter count).
   if (!b.fields && b.tiles_idx[0] + b.tiles_idx[1] == 1 && b.one.n <= 131072) {
     if (b.tiles_idx[0])
       run("k_dsmall", [&] { k_dsmall<float, B><<<(uint32_t)b.tiles_dec[0], 256, 0, stream>>>(b); });
