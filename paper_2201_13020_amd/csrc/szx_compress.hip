@@ -1129,9 +1129,10 @@ struct EncShared {
 // and, about as long, 18 vector instructions a value plus 250 a tile. Measured
 // there 36 us a launch, and 233 us on 2^28 float64 values at REL 1e-3 (43 and
 // 421 us with a barrier for every row's sums, LDS atomics for every packed
-// dword and tickets for constant tiles); a batch of 256 float32 fields, 175 us
-// (239). Smaller workgroups without the pending tile, eight a compute unit,
+// dword and tickets for constant tiles); 256 fields of 1 MiB on average, both
+// types, 219 us (then 239 and 35, a launch a type). Smaller workgroups without the pending tile, eight a compute unit,
 // took 51 us: every tile then waits 4-5 us for its offset.
+//
 // wid is the workgroup's number among wgs.
 template <typename T, int B, int BATCH>
 __device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint8_t* s_ring, uint32_t wid, uint32_t wgs) {
@@ -1795,6 +1796,7 @@ __global__ __launch_bounds__((64 * EncGeo<T, B>::ROWS)) void k_mid(CBatch b) {
       atomicMax(&f.ctr->err, 1u);
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
       __hip_atomic_store(f.out_size, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (last) *f.clean = 0;  // the slots keep this call's range
     }
     return;
   }

@@ -124,3 +124,23 @@ def test_batches_of_one_and_both_types(types, block):
             assert int(d.statuses[i].cpu().view(torch.int32)) == 0, (i, use)
             y = szref.decompress(ref).ravel()
             assert np.array_equal(d.outs[i][: y.size].cpu().numpy().view(np.uint8), y.view(np.uint8)), (i, use)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [128, 512, 1024])
+def test_few_workgroups_above_the_small_calls(block, dtype):
+    """Single calls beyond the one- and two-launch sizes on eight workgroups,
+    whose rings wrap many times, and on the default number."""
+    dt = torch.float32 if dtype == "float32" else torch.float64
+    n = 2_200_003
+    for kind in ("mixed", "noise"):
+        x = field(kind, n, dtype, block)
+        cls = szx.size_class(x.nbytes)
+        ref = szref.compress(x, 1e-3, "rel", block)
+        for wgs in (8, 0):
+            try:
+                szx.set_geometry(dt, cls, wgs)
+                out, size = gpu_compress(x, 1e-3, "rel", block)
+            finally:
+                szx.set_geometry(dt, cls, 0)
+            assert size == ref.size and np.array_equal(out[:size].cpu().numpy(), ref), (kind, wgs)
