@@ -317,11 +317,17 @@ __global__ __launch_bounds__(256) void k_stats(CBatch b) {
 // fields' workgroups first, where the two types' kernels need alike registers
 // and LDS (below b = 1024): a launch for each type has its own start and its
 // own nearly empty end. Fields of 1 MiB on average, b = 128, in a launch a type,
-// and so: 8 of them 40.6 -> 28.2 us a call (graph replays), 256 of them 359 ->
-// 344; 32 fields of 256 KiB 49.1 -> 33.4. (4.7 us of each is the pass that ended
-// the batch's streams, which the encode pass does now.)
+// and so: 8 of them 40.6 -> 28.2 us a call (graph replays), 256 of them (their
+// encode pass still a launch a type) 359 -> 343; 32 fields of 256 KiB 49.1 -> 33.4.
+// (5 us of each is the pass that ended the batch's streams, which the encode
+// pass does now.)
 template <int B>
 constexpr bool kOneLaunch = B < 1024;
+// The encode pass only up to this many tiles (512 MiB): beyond, what its code
+// for both types costs outweighs a launch. 256 fields of 512 KiB on average, a
+// launch a type and one, 194.3 and 189.8 us a call; of 1 MiB, 349.9 and 355.9; 2048
+// of 1 MiB 2176 and 2218.
+constexpr uint64_t kOneLaunchTiles = 16384;
 
 template <int B>
 __global__ __launch_bounds__(256) void k_stats_both(CBatch b) {
@@ -1129,9 +1135,10 @@ struct EncShared {
 // and, about as long, 18 vector instructions a value plus 250 a tile. Measured
 // there 36 us a launch, and 233 us on 2^28 float64 values at REL 1e-3 (43 and
 // 421 us with a barrier for every row's sums, LDS atomics for every packed
-// dword and tickets for constant tiles); 256 fields of 1 MiB on average, both
-// types, 219 us (then 239 and 35, a launch a type). Smaller workgroups without the pending tile, eight a compute unit,
-// took 51 us: every tile then waits 4-5 us for its offset.
+// dword and tickets for constant tiles); 256 fields of 1 MiB on average, 185 us
+// for the float32 ones and 31 for the float64 ones (239 and 35). Smaller
+// workgroups without the pending tile, eight a compute unit, took 51 us: every
+// tile then waits 4-5 us for its offset.
 //
 // wid is the workgroup's number among wgs.
 template <typename T, int B, int BATCH>
@@ -1882,7 +1889,7 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
   auto encoders = [&](int dt) {
     return (uint32_t)std::min<uint64_t>(b.tiles_enc[dt], std::max<uint64_t>(g.encode_wgs[dt], kTicketClasses));
   };
-  bool done = b.tiles_stats[0] + b.tiles_stats[1] == 0;
+  bool done = b.tiles_stats[0] + b.tiles_stats[1] == 0, encoded = false;
   if constexpr (kOneLaunch<B>) {
     if (b.fields && b.tiles_stats[0] && b.tiles_stats[1]) {
       const uint32_t gs = (uint32_t)(b.tiles_stats[0] + b.tiles_stats[1]);
@@ -1890,7 +1897,8 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
       const uint32_t ge = std::max(encoders(0), encoders(1)) + 1;
       run("k_stats", [&] { k_stats_both<B><<<gs, 256, 0, stream>>>(b); });
       run("k_classify", [&] { k_classify_both<B><<<gc, 256, 0, stream>>>(b); });
-      run("k_encode", [&] { k_encode_both<B><<<ge, 256, 0, stream>>>(b); });
+      encoded = b.tiles_enc[0] + b.tiles_enc[1] <= kOneLaunchTiles;
+      if (encoded) run("k_encode", [&] { k_encode_both<B><<<ge, 256, 0, stream>>>(b); });
       done = true;
     }
   }
@@ -1899,6 +1907,8 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
     if (b.tiles_stats[1]) run("k_stats", [&] { k_stats<double, B><<<(uint32_t)b.tiles_stats[1], 256, 0, stream>>>(b); });
     if (b.tiles_cls[0]) run("k_classify", [&] { k_classify<float, B><<<(uint32_t)b.tiles_cls[0], 256, 0, stream>>>(b); });
     if (b.tiles_cls[1]) run("k_classify", [&] { k_classify<double, B><<<(uint32_t)b.tiles_cls[1], 256, 0, stream>>>(b); });
+  }
+  if (!encoded) {
     for (int dt = 0; dt < 2; ++dt) {
       if (!b.tiles_enc[dt]) continue;
       const uint32_t genc = encoders(dt);

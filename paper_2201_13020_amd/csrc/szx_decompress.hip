@@ -521,6 +521,11 @@ __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
 // 159; 32 fields of 256 KiB 24.2 -> 14.7, at b = 512 40.3 -> 22.9.
 template <int B>
 constexpr bool kOneLaunch = B < 1024;
+// The decode pass only up to this many tiles (768 MiB): beyond, the waves that
+// the float32 kernel's registers cost the float64 tiles outweigh a launch. 256
+// fields of 1 MiB on average, a launch a type and one, 168.6 and 163.2 us a call;
+// 512 of them 375 and 385, 2048 1457 and 1496.
+constexpr uint64_t kOneLaunchTiles = 49152;
 
 template <int B, int MODE>
 __global__ __launch_bounds__(256) void k_dindex_both(DBatch b) {
@@ -1011,6 +1016,7 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
       run("k_dsmall", [&] { k_dsmall<double, B><<<(uint32_t)b.tiles_dec[1], 256, 0, stream>>>(b); });
     return hipGetLastError();
   }
+  bool indexed = false;
   if constexpr (kOneLaunch<B>) {
     if (b.fields && b.tiles_idx[0] && b.tiles_idx[1]) {
       const uint32_t gi = (uint32_t)(b.tiles_idx[0] + b.tiles_idx[1]);
@@ -1018,11 +1024,14 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
         run("k_dindex", [&] { k_dindex_both<B, kDirect><<<gi, 256, 0, stream>>>(b); });
       else
         run("k_dindex", [&] { k_dindex_both<B, kChained><<<gi, 256, 0, stream>>>(b); });
-      run("k_decode", [&] { k_decode_both<B><<<(uint32_t)(b.tiles_dec[0] + b.tiles_dec[1]), 256, 0, stream>>>(b); });
-      return hipGetLastError();
+      indexed = true;
+      if (b.tiles_dec[0] + b.tiles_dec[1] <= kOneLaunchTiles) {
+        run("k_decode", [&] { k_decode_both<B><<<(uint32_t)(b.tiles_dec[0] + b.tiles_dec[1]), 256, 0, stream>>>(b); });
+        return hipGetLastError();
+      }
     }
   }
-  for (int dt = 0; dt < 2; ++dt) {
+  for (int dt = 0; dt < 2 && !indexed; ++dt) {
     const uint32_t n = (uint32_t)b.tiles_idx[dt];
     if (!n) continue;
     if (dt == 0 && b.direct)
