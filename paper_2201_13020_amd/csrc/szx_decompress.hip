@@ -576,7 +576,8 @@ __device__ __forceinline__ bool totals_bad(const Totals& t) {
 // 1e-3: 41 MB in and 100 MB out, 27 us at the copy rate of 5.2 TB/s; measured
 // 24 us, part of the stream coming from the last-level cache; 31.5 us with four
 // barriers a tile, byte masks a value and gaps in every store). 2^28 float64
-// values at REL 1e-5: 456 us (533), the copy rate as well.
+// values at REL 1e-5: 443 us a call with the index pass (552), the copy rate as
+// well.
 // `entry`: the tile's entry of the index where the workgroup made it itself
 // (kOne), else null.
 template <typename T, int B, bool ONE>
@@ -737,137 +738,145 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
       const int rem = (int)nval_t - (int)(lk * B + lig * EPL);  // values from this lane's first one to the tile's end
       cnt = rem < 0 ? 0 : (rem > EPL ? EPL : rem);
     }
-    // kept bits K (0: constant, absent or unusable), stored bytes a value
-    uint32_t K = kraw[s];
-    const bool raw = K == kRawK;
-    if (nc[s] && !raw && ((int)K < Traits<T>::KMIN || (int)K > Traits<T>::W)) {
-      bad = true;
-      K = 0;
-    }
-    if (raw) K = 0;
-    uint32_t nb = (K + 7u) >> 3;
-    const uint32_t sh = 8u * nb - K;
-    uint32_t c;  // the lane's codes, first value in the top bits
-    if constexpr (EPL == 8)
-      c = ((craw[s] & 0xFFu) << 8) | (craw[s] >> 8);
-    else
-      c = __builtin_bswap32(craw[s]);
-    // Codes of values past the end are cleared; a code above nb marks the
-    // stream bad and its lane is then read as if all codes were 0, which
-    // keeps every offset within the stage.
-    if (tail) c = valid_codes<EPL>(c, cnt);
-    c = K ? c : 0u;
-    if (__ballot(K && nb < 3u) != 0) {
-      const uint32_t hi = c & 0xAAAAAAAAu, lo = c & 0x55555555u;
-      const bool over = K && ((nb == 1u && hi != 0) || (nb == 2u && (lo & (hi >> 1)) != 0));
-      bad = bad || over;
-      c = over ? 0u : c;
-    }
-    const bool some_raw = __ballot(raw) != 0;
-    if (some_raw) nb = raw ? (uint32_t)BYTES : nb;
-    // stored bytes of the lane, and its first one's place in the stage
-    const uint32_t lb =
-        (uint32_t)__umul24(nb, (uint32_t)cnt) - ((uint32_t)__popc(c) + (uint32_t)__popc(c & 0xAAAAAAAAu));
-    const uint32_t inc = wave_incl_sum_u32(lb);
-    uint32_t o = done + inc - lb;
-    done += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-
-    // Values. Reads of the stage go unguarded: a lane starts at most at the end
-    // of the wave's stored bytes and advances at most a word per value, which
-    // the stage's size allows for. Values past the end of a short block read
-    // whatever lies there and are not stored; being last in their lane and
-    // block, they only reach other such values. (Lanes of constant blocks run
-    // along with nb = 0.)
-    const uint32_t nbh = nb < 4u ? nb : 4u;
-    const bool longer = sizeof(T) == 8 && __ballot(nb > 4u) != 0;  // some value stores bytes of its low word
-    uint32_t got[EPL], gotl[sizeof(T) == 8 ? EPL : 1], own[EPL];
-    uint32_t run = 0;
-    const uint32_t o0 = o;
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      // o: where the value's word would start if its leading bytes were stored
-      // too, so that its stored bytes lie in place; shared bytes come from the
-      // word before, whatever follows the stored ones is cleared by `keep`
-      const uint32_t ci = (c >> (2 * (EPL - 1 - i))) & 3u;
-      o = i == 0 ? o - ci : __builtin_amdgcn_sad_u8(nb, ci, o);  // o + nb - ci
-      got[i] = __builtin_bswap32(stage_get(stage, o));
-      if constexpr (sizeof(T) == 8) {
-        if (longer) gotl[i] = stage_get(stage, o + 4u);
-      }
-      own[i] = __builtin_amdgcn_alignbyte(~0u, 0u, ci);  // the top ci bytes: the shared ones
-      run = (run & own[i]) | (got[i] & ~own[i]);
-    }
-    // Leading bytes from the lanes before this one in the block: the lanes'
-    // (smallest code, top three bytes) pairs scanned under lead_compose.
-    // Bytes below the kept ones never reach a kept byte (a code keeps at most
-    // the top min(3, nb) bytes of a live value).
-    uint32_t carry = 0;
-    if constexpr (LPB > 1) {
-      uint32_t pk = (run & 0xFFFFFF00u) | min_code<EPL>(c);
-      uint32_t o2 = lane_up<LPB, 1>(pk);
-      pk = lig >= 1 ? lead_compose(o2, pk) : pk;
-      if constexpr (LPB > 2) {
-        o2 = lane_up<LPB, 2>(pk);
-        pk = lig >= 2 ? lead_compose(o2, pk) : pk;
-      }
-      if constexpr (LPB > 4) {
-        o2 = lane_up<LPB, 4>(pk);
-        pk = lig >= 4 ? lead_compose(o2, pk) : pk;
-      }
-      if constexpr (LPB > 8) {
-        o2 = lane_up<LPB, 8>(pk);
-        pk = lig >= 8 ? lead_compose(o2, pk) : pk;
-      }
-      if constexpr (LPB > 16) {
-        o2 = __shfl_up(pk, 16, LPB);
-        pk = lig >= 16 ? lead_compose(o2, pk) : pk;
-      }
-      if constexpr (LPB > 32) {
-        o2 = __shfl_up(pk, 32, LPB);
-        pk = lig >= 32 ? lead_compose(o2, pk) : pk;
-      }
-      carry = lane_up<LPB, 1>(pk) & 0xFFFFFF00u;
-      carry = lig == 0 ? 0u : carry;
-    }
-    // x' = mu + (q' << s), the words once more with the carried bytes in front
+    // A float64 row of constant blocks has nothing to decode: 2^28 values, two
+    // thirds of the blocks constant, 476 -> 418 us a call. (float32 rows, of
+    // twice the blocks, rarely are: the branch cost them 2-5 %.)
     T v[EPL];
-    run = carry;
-    if constexpr (sizeof(T) == 4) {
-      const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
+    if (sizeof(T) == 8 && __ballot(nc[s]) == 0) {
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        run = (run & own[i]) | (got[i] & ~own[i]);
-        v[i] = mu[s] + from_bits<T>((run << sh) & keep);
-      }
-    } else if (!longer) {
-      const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        run = (run & own[i]) | (got[i] & ~own[i]);
-        v[i] = mu[s] + from_bits<T>((U)((run << sh) & keep) << (sizeof(U) * 8 - 32));
-      }
+      for (int i = 0; i < EPL; ++i) v[i] = mu[s];
     } else {
-      const U keep = (U)(top_bytes_mask<U>((int)nb) << sh);
+      // kept bits K (0: constant, absent or unusable), stored bytes a value
+      uint32_t K = kraw[s];
+      const bool raw = K == kRawK;
+      if (nc[s] && !raw && ((int)K < Traits<T>::KMIN || (int)K > Traits<T>::W)) {
+        bad = true;
+        K = 0;
+      }
+      if (raw) K = 0;
+      uint32_t nb = (K + 7u) >> 3;
+      const uint32_t sh = 8u * nb - K;
+      uint32_t c;  // the lane's codes, first value in the top bits
+      if constexpr (EPL == 8)
+        c = ((craw[s] & 0xFFu) << 8) | (craw[s] >> 8);
+      else
+        c = __builtin_bswap32(craw[s]);
+      // Codes of values past the end are cleared; a code above nb marks the
+      // stream bad and its lane is then read as if all codes were 0, which
+      // keeps every offset within the stage.
+      if (tail) c = valid_codes<EPL>(c, cnt);
+      c = K ? c : 0u;
+      if (__ballot(K && nb < 3u) != 0) {
+        const uint32_t hi = c & 0xAAAAAAAAu, lo = c & 0x55555555u;
+        const bool over = K && ((nb == 1u && hi != 0) || (nb == 2u && (lo & (hi >> 1)) != 0));
+        bad = bad || over;
+        c = over ? 0u : c;
+      }
+      const bool some_raw = __ballot(raw) != 0;
+      if (some_raw) nb = raw ? (uint32_t)BYTES : nb;
+      // stored bytes of the lane, and its first one's place in the stage
+      const uint32_t lb =
+          (uint32_t)__umul24(nb, (uint32_t)cnt) - ((uint32_t)__popc(c) + (uint32_t)__popc(c & 0xAAAAAAAAu));
+      const uint32_t inc = wave_incl_sum_u32(lb);
+      uint32_t o = done + inc - lb;
+      done += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+
+      // Values. Reads of the stage go unguarded: a lane starts at most at the end
+      // of the wave's stored bytes and advances at most a word per value, which
+      // the stage's size allows for. Values past the end of a short block read
+      // whatever lies there and are not stored; being last in their lane and
+      // block, they only reach other such values. (Lanes of constant blocks run
+      // along with nb = 0.)
+      const uint32_t nbh = nb < 4u ? nb : 4u;
+      const bool longer = sizeof(T) == 8 && __ballot(nb > 4u) != 0;  // some value stores bytes of its low word
+      uint32_t got[EPL], gotl[sizeof(T) == 8 ? EPL : 1], own[EPL];
+      uint32_t run = 0;
+      const uint32_t o0 = o;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
+        // o: where the value's word would start if its leading bytes were stored
+        // too, so that its stored bytes lie in place; shared bytes come from the
+        // word before, whatever follows the stored ones is cleared by `keep`
+        const uint32_t ci = (c >> (2 * (EPL - 1 - i))) & 3u;
+        o = i == 0 ? o - ci : __builtin_amdgcn_sad_u8(nb, ci, o);  // o + nb - ci
+        got[i] = __builtin_bswap32(stage_get(stage, o));
+        if constexpr (sizeof(T) == 8) {
+          if (longer) gotl[i] = stage_get(stage, o + 4u);
+        }
+        own[i] = __builtin_amdgcn_alignbyte(~0u, 0u, ci);  // the top ci bytes: the shared ones
         run = (run & own[i]) | (got[i] & ~own[i]);
-        const U q = ((U)run << (sizeof(U) * 8 - 32)) | (U)__builtin_bswap32(gotl[i]);
-        v[i] = mu[s] + from_bits<T>((U)(q << sh) & keep);
       }
-    }
-    if (__ballot(K == 0) != 0) {
-      if (K == 0) {  // constant: mu itself (mu + 0 would lose a zero's sign)
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) v[i] = mu[s];
+      // Leading bytes from the lanes before this one in the block: the lanes'
+      // (smallest code, top three bytes) pairs scanned under lead_compose.
+      // Bytes below the kept ones never reach a kept byte (a code keeps at most
+      // the top min(3, nb) bytes of a live value).
+      uint32_t carry = 0;
+      if constexpr (LPB > 1) {
+        uint32_t pk = (run & 0xFFFFFF00u) | min_code<EPL>(c);
+        uint32_t o2 = lane_up<LPB, 1>(pk);
+        pk = lig >= 1 ? lead_compose(o2, pk) : pk;
+        if constexpr (LPB > 2) {
+          o2 = lane_up<LPB, 2>(pk);
+          pk = lig >= 2 ? lead_compose(o2, pk) : pk;
+        }
+        if constexpr (LPB > 4) {
+          o2 = lane_up<LPB, 4>(pk);
+          pk = lig >= 4 ? lead_compose(o2, pk) : pk;
+        }
+        if constexpr (LPB > 8) {
+          o2 = lane_up<LPB, 8>(pk);
+          pk = lig >= 8 ? lead_compose(o2, pk) : pk;
+        }
+        if constexpr (LPB > 16) {
+          o2 = __shfl_up(pk, 16, LPB);
+          pk = lig >= 16 ? lead_compose(o2, pk) : pk;
+        }
+        if constexpr (LPB > 32) {
+          o2 = __shfl_up(pk, 32, LPB);
+          pk = lig >= 32 ? lead_compose(o2, pk) : pk;
+        }
+        carry = lane_up<LPB, 1>(pk) & 0xFFFFFF00u;
+        carry = lig == 0 ? 0u : carry;
       }
-      if (some_raw && raw) {  // the stored words
+      // x' = mu + (q' << s), the words once more with the carried bytes in front
+      run = carry;
+      if constexpr (sizeof(T) == 4) {
+        const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
-          const uint32_t lo = stage_get(stage, o0 + (uint32_t)(i * BYTES));
-          if constexpr (sizeof(T) == 4)
-            v[i] = from_bits<T>(lo);
-          else
-            v[i] = from_bits<T>((U)lo | ((U)stage_get(stage, o0 + (uint32_t)(i * BYTES) + 4u) << (sizeof(U) * 8 - 32)));
+          run = (run & own[i]) | (got[i] & ~own[i]);
+          v[i] = mu[s] + from_bits<T>((run << sh) & keep);
+        }
+      } else if (!longer) {
+        const uint32_t keep = top_bytes_mask<uint32_t>((int)nbh) << sh;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          run = (run & own[i]) | (got[i] & ~own[i]);
+          v[i] = mu[s] + from_bits<T>((U)((run << sh) & keep) << (sizeof(U) * 8 - 32));
+        }
+      } else {
+        const U keep = (U)(top_bytes_mask<U>((int)nb) << sh);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          run = (run & own[i]) | (got[i] & ~own[i]);
+          const U q = ((U)run << (sizeof(U) * 8 - 32)) | (U)__builtin_bswap32(gotl[i]);
+          v[i] = mu[s] + from_bits<T>((U)(q << sh) & keep);
+        }
+      }
+      if (__ballot(K == 0) != 0) {
+        if (K == 0) {  // constant: mu itself (mu + 0 would lose a zero's sign)
+#pragma unroll
+          for (int i = 0; i < EPL; ++i) v[i] = mu[s];
+        }
+        if (some_raw && raw) {  // the stored words
+#pragma unroll
+          for (int i = 0; i < EPL; ++i) {
+            const uint32_t lo = stage_get(stage, o0 + (uint32_t)(i * BYTES));
+            if constexpr (sizeof(T) == 4)
+              v[i] = from_bits<T>(lo);
+            else
+              v[i] = from_bits<T>((U)lo | ((U)stage_get(stage, o0 + (uint32_t)(i * BYTES) + 4u) << (sizeof(U) * 8 - 32)));
+          }
         }
       }
     }
