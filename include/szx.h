@@ -88,9 +88,10 @@ uint64_t sz_compress_bound(const sz_params* p);
    not trust the slots, and leaves the mark for the next call. Do not write
    into those bytes between calls (overwriting the whole workspace, its first
    bytes included, is fine). sz_decompress keeps two words of its own there
-   (bytes 64-71 and 128-135: a call counter and the token of the last call
-   that cleared its scan status words; every call clears them, in its first
-   kernel) and touches nothing else of them. */
+   (bytes 64-71 and 128-135: a counter of the calls that use scan status words
+   and the token of the last one that cleared them, in its first kernel) and
+   touches nothing else of them. Small calls in either direction use none of
+   the workspace, which has to be there all the same. */
 #define SZ_WS_KEPT_BYTES 16640
 uint64_t sz_workspace_size(const sz_params* p);
 
@@ -198,10 +199,11 @@ sz_status sz_stitch(const sz_params* field, uint32_t nshards, const void* const*
 /* ---- batches (many fields, one launch per pass) ---------------------------
    A batch compresses (or decompresses) many fields of mixed element types,
    sizes and bounds with one launch per pass over all of them: one extrema
-   launch, one range launch, one classification launch, one persistent encode
-   launch (float32 tiles of every field, then float64 tiles), one finalize
-   launch. Each field's stream is byte-identical to what sz_compress writes
-   for it alone (the single call runs the same kernels as a batch of one).
+   launch, one classification launch, one persistent encode launch (float32
+   tiles of every field, then float64 tiles; blocks of 1024 values, and the
+   encoding and decoding of large batches: a launch a type), and one for the fields without values if there are any. Each field's
+   stream is byte-identical to what sz_compress writes for it alone (a large
+   single call runs the same kernels as a batch of one, a small one fewer).
    All fields of a batch share one block size. The batch's descriptor table
    and tile maps live in its workspace: sz_batch_create_* writes them there
    once (a synchronous copy; call it outside graph capture), then every
@@ -242,7 +244,8 @@ sz_status sz_batch_create_decompress(const sz_dfield* fields, uint32_t n, void* 
 /* Launch geometry of the encode pass of a compression batch for the fields of
    one element type: the number of persistent workgroups (the autotuner's
    knob; no effect on the output bytes; values below 8 act as 8, one per
-   ticket class of the encoder). A new batch starts from the
+   ticket class of the encoder; where both types share a launch the larger of
+   their numbers holds). A new batch starts from the
    process-wide table of sz_set_geometry for the size class of that type's
    total input bytes. */
 sz_status sz_batch_set_geometry(sz_batch b, sz_dtype dtype, uint32_t encode_wgs);
@@ -252,7 +255,8 @@ sz_status sz_batch_set_geometry(sz_batch b, sz_dtype dtype, uint32_t encode_wgs)
 uint32_t sz_size_class(uint64_t bytes);
 
 /* Process-wide encode geometry for inputs of one element type and size class,
-   used by sz_compress and as the starting geometry of new batches;
+   used by sz_compress (fields of more than 256 encode tiles or 8192 blocks;
+   smaller ones take a workgroup a tile) and as the starting geometry of new batches;
    encode_wgs = 0 restores the default (4 per compute unit). Thread-safe;
    no effect on the output bytes. */
 sz_status sz_set_geometry(sz_dtype dtype, uint32_t size_class, uint32_t encode_wgs);
