@@ -1398,9 +1398,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<T, B
   encode_pass<T, B, BATCH>(b, s_sh.enc, s_ring, blockIdx.x - 1, gridDim.x - 1);
 }
 
-// Both types of a batch: the float32 tiles and then the float64 tiles, also for
-// workgroup 0, which scans them (a scan workgroup for the float64 tiles alone
-// would wait through all of the others').
+// Both types of a batch: the float32 tiles and then the float64 tiles.
+// Workgroup 0 scans the float32 tiles, workgroup 1 the float64 ones. (One that
+// scanned both in turn would hold the float64 offsets until the last float32
+// tile is encoded: where that tile's workgroup is not dispatched yet, those
+// that wait for a float64 offset never make room for it.)
 template <int B>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<float, B>::WAVES))) void k_encode_both(
     CBatch b) {
@@ -1412,16 +1414,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<floa
     ScanShared scan;
   } s_sh;
   __shared__ __align__(16) uint8_t s_ring[kWavesPerWG * std::max(G4::RING + G4::SLACK, G8::RING + G8::SLACK)];
-  if (blockIdx.x == 0) {
-#pragma unroll 1
-    for (uint32_t dt = 0; dt < 2; ++dt) {
-      const FieldC* f = field_ref<kBatch>(b, *as_constant(b.field_enc[dt]));
-      scan_workgroup(as_global(f->enc_mid), b.tiles_enc[dt], &as_global(f->ctr)->err, 1u, s_sh.scan);
-      __syncthreads();
-    }
+  if (blockIdx.x < 2) {
+    const uint32_t dt = blockIdx.x;
+    const FieldC* f = field_ref<kBatch>(b, *as_constant(b.field_enc[dt]));
+    scan_workgroup(as_global(f->enc_mid), b.tiles_enc[dt], &as_global(f->ctr)->err, 1u, s_sh.scan);
     return;
   }
-  const uint32_t wid = blockIdx.x - 1, wgs = gridDim.x - 1;
+  const uint32_t wid = blockIdx.x - 2, wgs = gridDim.x - 2;
   encode_pass<float, B, kBatch>(b, s_sh.enc, s_ring, wid, wgs);
   __syncthreads();
   encode_pass<double, B, kBatch>(b, s_sh.enc, s_ring, wid, wgs);
@@ -1894,7 +1893,7 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
     if (b.fields && b.tiles_stats[0] && b.tiles_stats[1]) {
       const uint32_t gs = (uint32_t)(b.tiles_stats[0] + b.tiles_stats[1]);
       const uint32_t gc = (uint32_t)(b.tiles_cls[0] + b.tiles_cls[1]);
-      const uint32_t ge = std::max(encoders(0), encoders(1)) + 1;
+      const uint32_t ge = std::max(encoders(0), encoders(1)) + 2;  // two scan workgroups
       run("k_stats", [&] { k_stats_both<B><<<gs, 256, 0, stream>>>(b); });
       run("k_classify", [&] { k_classify_both<B><<<gc, 256, 0, stream>>>(b); });
       encoded = b.tiles_enc[0] + b.tiles_enc[1] <= kOneLaunchTiles;

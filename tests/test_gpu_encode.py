@@ -144,3 +144,32 @@ def test_few_workgroups_above_the_small_calls(block, dtype):
             finally:
                 szx.set_geometry(dt, cls, 0)
             assert size == ref.size and np.array_equal(out[:size].cpu().numpy(), ref), (kind, wgs)
+
+
+@pytest.mark.parametrize("wgs", [0, 2048])
+@pytest.mark.parametrize("n32,n64", [(32, 32), (33, 31), (31, 33), (48, 4)])
+def test_both_types_with_a_workgroup_beyond_the_resident_ones(n32, n64, wgs):
+    """A batch of both types whose float32 tiles number as many as the launch's
+    workgroups or a few more or less (32 fields of 1 MiB are 1024 tiles, four a
+    compute unit), so that workgroups with a tile of their own start only when
+    others have ended; with more workgroups asked for, many of them. Twice over
+    one workspace, and on two streams side by side."""
+    xs = []
+    for i in range(n32 + n64):
+        dt = np.float32 if i < n32 else np.float64
+        xs.append((np.sin(np.arange(1 << 18 if i < n32 else 1 << 17) * 1e-3 * (i + 1)) + 1e-2 * i).astype(dt))
+    refs = [szref.compress(x, 1e-3, "rel", 128) for x in xs]
+    dev = [torch.from_numpy(x).cuda() for x in xs]
+    batches = [szx.compress_batch(dev, 1e-3, "rel", 128) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for use in range(2):
+        for b, s in zip(batches, streams):
+            if wgs:
+                b.set_geometry(wgs)
+            b.run(s)
+        torch.cuda.synchronize()
+        for b in batches:
+            for i, ref in enumerate(refs):
+                m = int(b.sizes[i].cpu().view(torch.int64))
+                assert m == ref.size and np.array_equal(b.outs[i][:m].cpu().numpy(), ref), (i, use)
