@@ -1153,7 +1153,8 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint
   const uint32_t cls = wid % kTicketClasses;
   const bool direct = wgs >= b.tiles_enc[DT];  // a workgroup for every tile
   const FieldC* const one = BATCH == kSingle ? field_ref<BATCH>(b, 0) : nullptr;
-  const uint64_t ntiles = BATCH == kSingle ? as_constant(one->ctr)->n_tiles : b.tiles_enc[DT];
+  const uint64_t ntiles = BATCH == kSingle ? listed_tiles(as_constant(one->ctr)->err, as_constant(one->ctr)->n_tiles)
+                                           : b.tiles_enc[DT];
   const uint32_t* const list = BATCH == kSingle ? as_global(one->enc_list) : nullptr;
   uint32_t* ticket = b.tickets + (DT * kTicketClasses + cls) * 64;
   const uint32_t wave = uniform(threadIdx.x / kWave);
@@ -1389,7 +1390,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EncGeo<T, B
   if (blockIdx.x == 0) {
     // the type's status words lie in one array, its first field's first
     const FieldC* f = field_ref<BATCH>(b, BATCH == kSingle ? 0u : *as_constant(b.field_enc[DT]));
-    const uint64_t total = scan_workgroup(as_global(f->enc_mid), b.tiles_enc[DT], &as_global(f->ctr)->err, 1u, s_sh.scan);
+    // (where a single call's classification gave up, no tile is encoded and none is waited for)
+    const uint64_t ntiles = BATCH == kSingle ? listed_tiles(as_constant(f->ctr)->err, b.tiles_enc[DT]) : b.tiles_enc[DT];
+    const uint64_t total = scan_workgroup(as_global(f->enc_mid), ntiles, &as_global(f->ctr)->err, 1u, s_sh.scan);
     if constexpr (BATCH == kSingle) {
       if (threadIdx.x == 0) finish_stream(field_at<BATCH>(b, 0), total);
     }

@@ -40,6 +40,11 @@ struct Counters {
   uint64_t e_bits;     // bit pattern of the bound e in the element type
 };
 
+// Tiles that the encode pass of a single call takes from the list (and scans).
+// None where the classification gave up: its tiles then count from partial
+// prefixes, and the list has gaps that hold whatever the workspace held before.
+__host__ __device__ inline uint64_t listed_tiles(uint32_t err, uint64_t n_tiles) { return err != 0 ? 0 : n_tiles; }
+
 // The range slots of a field are left all zero by every compression that
 // used them (its last classification tile clears them), which then sets the
 // field's clean word to kCleanWord. A compression that finds another value

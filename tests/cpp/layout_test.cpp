@@ -1,0 +1,25 @@
+// Host-side rules that the kernels share with the layout header.
+#include <stdint.h>
+#include <stdio.h>
+
+#include "../../paper_2201_13020_amd/csrc/szx_layout.hpp"
+
+#define CHECK(c)                                              \
+  do {                                                        \
+    if (!(c)) {                                               \
+      fprintf(stderr, "check failed line %d: %s\n", __LINE__, #c); \
+      return 1;                                               \
+    }                                                         \
+  } while (0)
+
+int main() {
+  // the encoder reads no entry of a list that a failed classification may have
+  // left with gaps
+  CHECK(szx::listed_tiles(0, 191) == 191);
+  CHECK(szx::listed_tiles(0, 0) == 0);
+  CHECK(szx::listed_tiles(1, 191) == 0);
+  CHECK(szx::listed_tiles(0x80000000u, ~0ull) == 0);
+
+  printf("layout ok\n");
+  return 0;
+}
