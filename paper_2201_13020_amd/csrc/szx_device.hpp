@@ -441,7 +441,6 @@ __device__ __forceinline__ void wg_excl_scan_multi(const uint32_t (&v)[S], uint3
 constexpr uint64_t kFlagAgg = 1ull << 62;
 constexpr uint64_t kFlagIncl = 2ull << 62;
 constexpr uint64_t kValueMask = (1ull << 62) - 1;
-constexpr uint32_t kSpinLimit = 1u << 18;
 
 // The flag and the value share one 64-bit word, so a reader never needs any
 // other memory of the writer: relaxed device-scope atomics are enough. (An
@@ -555,13 +554,15 @@ __device__ __noinline__ uint64_t lookback_resolve(uint64_t* status, uint32_t t, 
 // (256 a wave), and publishes every tile's inclusive prefix as soon as all
 // earlier tiles have published, so a tile's own wait is one status word. (A
 // decoupled look-back walks back through every tile still in flight, one
-// window per round and per tile.) It waits only on tiles that running
-// workgroups hold, and its waits are bounded like the others: on exhaustion
-// err is raised and it stops, and the tiles still waiting give up on their own
-// bounds. Returns the sum over all tiles. A round is one trip to the device's coherence point: the loads go
-// out together (none in a branch, where it would wait for the one before it;
-// past the last tile they read the word behind it, which stays unpublished)
-// and the sums take 32-bit DPP steps. (One wave that read 16 words a lane, each
+// window per round and per tile.) The tile that it waits for may be one that no
+// running workgroup holds yet (the launch's later workgroups start as earlier
+// ones, or another launch's, end), so its wait is bounded by far more rounds
+// than a tile's: on exhaustion err is raised and it stops, and the tiles still
+// waiting give up on their own bounds. Returns the sum over all tiles. A round
+// is one trip to the device's coherence point: the loads go out together (none
+// in a branch, where it would wait for the one before it; past the last tile
+// they read the word behind it, which stays unpublished) and the sums take
+// 32-bit DPP steps. (One wave that read 16 words a lane, each
 // load behind a branch and spilled, and summed 64-bit words by lane shuffles
 // took 6.5 us a round of 1024: the encoder of a 2 GiB float64 field, 65536
 // tiles, ran 421 us and waited on it; with this 331 us.)
@@ -626,7 +627,7 @@ __device__ __forceinline__ uint64_t scan_workgroup(uint64_t* status, uint64_t nt
     run += total;
     first += adv;
     if (adv == 0) {
-      if (++spins > kSpinLimit) {
+      if (++spins > kScanSpinLimit) {
         if (threadIdx.x == 0) atomicMax(err, err_code);
         break;
       }

@@ -108,6 +108,13 @@ constexpr uint32_t kClsBlocks = 1024;
 // bits; the chained pass over them takes 38 us in all).
 constexpr uint32_t kDirectTiles = 256;
 
+// Bounds of the kernels' waits, in polls without progress (0.2 us each). A
+// workgroup that waits on what running workgroups do gives up after 50 ms. The
+// scan workgroup of the encode pass waits for tiles of workgroups that may not
+// have started, which lasts as long as another launch holds the device: 13 s.
+constexpr uint32_t kSpinLimit = 1u << 18;
+constexpr uint32_t kScanSpinLimit = 1u << 26;
+
 // Ticket classes of the persistent encode pass (per element type).
 constexpr uint32_t kTicketClasses = 8;
 // Tiles of the extrema pass per chunk; a chunk leaves one finite range.

@@ -20,6 +20,12 @@ int main() {
   CHECK(szx::listed_tiles(1, 191) == 0);
   CHECK(szx::listed_tiles(0x80000000u, ~0ull) == 0);
 
+  // a launch beside the encode pass may hold the device for seconds before the
+  // pass's later workgroups start: the scan workgroup outlasts that, and a
+  // tile's wait, which is for running workgroups, stays short (0.19 us a poll)
+  CHECK(0.19e-6 * szx::kScanSpinLimit >= 10.0);
+  CHECK(0.19e-6 * szx::kSpinLimit < 0.1);
+
   printf("layout ok\n");
   return 0;
 }
