@@ -866,28 +866,7 @@ __device__ __forceinline__ void copy_out(uint8_t* __restrict__ out, uint64_t dst
   for (uint32_t c = l; c < nfull; c += kWave) {
     const uint4 q0 = ring[(at16 + c) & mask16];
     const uint4 q1 = ring[(at16 + c + 1) & mask16];
-    const uint32_t w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-    uint4 u;
-    // k is the same for every lane: a uniform branch picks the words
-    switch (k) {
-      case 0:
-        u = make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], sh), __builtin_amdgcn_alignbyte(w[2], w[1], sh),
-                       __builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh));
-        break;
-      case 1:
-        u = make_uint4(__builtin_amdgcn_alignbyte(w[2], w[1], sh), __builtin_amdgcn_alignbyte(w[3], w[2], sh),
-                       __builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh));
-        break;
-      case 2:
-        u = make_uint4(__builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh),
-                       __builtin_amdgcn_alignbyte(w[5], w[4], sh), __builtin_amdgcn_alignbyte(w[6], w[5], sh));
-        break;
-      default:
-        u = make_uint4(__builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh),
-                       __builtin_amdgcn_alignbyte(w[6], w[5], sh), __builtin_amdgcn_alignbyte(w[7], w[6], sh));
-        break;
-    }
-    *reinterpret_cast<uint4*>(base + h + c * 16u) = u;
+    *reinterpret_cast<uint4*>(base + h + c * 16u) = realign16(q0, q1, k, sh);
   }
 }
 

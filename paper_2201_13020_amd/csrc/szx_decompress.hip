@@ -738,6 +738,22 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
       const int rem = (int)nval_t - (int)(lk * B + lig * EPL);  // values from this lane's first one to the tile's end
       cnt = rem < 0 ? 0 : (rem > EPL ? EPL : rem);
     }
+    T* const y = reinterpret_cast<T*>(a.out) + kb * B;  // of the tile
+    const uint32_t i0 = (wave * G::WBLK + (uint32_t)(s * G::GPW)) * (uint32_t)B;  // the row's first value
+    constexpr uint32_t CH = (uint32_t)(EPL * BYTES) / 16u;  // 16-byte chunks a lane
+    // chunk d of the row, as far as the field goes; streamed past the caches
+    // (the values are not read again here)
+    auto put = [&](uint32_t d, const v4u& w) {
+      const uint32_t first = i0 + d * (16u / BYTES);  // its first value
+      if (!tail || first + 16u / BYTES <= nval_t) {
+        __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(y + first));
+      } else {
+        uint32_t* const yw = reinterpret_cast<uint32_t*>(y + first);
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+          if (first + j * 4u / BYTES < nval_t) yw[j] = w[j];
+      }
+    };
     // A float64 row of constant blocks has nothing to decode: 2^28 values, two
     // thirds of the blocks constant, 476 -> 418 us a call. (float32 rows, of
     // twice the blocks, rarely are: the branch cost them 2-5 %.)
@@ -754,7 +770,7 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
         K = 0;
       }
       if (raw) K = 0;
-      uint32_t nb = (K + 7u) >> 3;
+      const uint32_t nb = (K + 7u) >> 3;
       const uint32_t sh = 8u * nb - K;
       uint32_t c;  // the lane's codes, first value in the top bits
       if constexpr (EPL == 8)
@@ -766,17 +782,36 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
       // keeps every offset within the stage.
       if (tail) c = valid_codes<EPL>(c, cnt);
       c = K ? c : 0u;
-      if (__ballot(K && nb < 3u) != 0) {
+      uint32_t per = nb;  // stored bytes of a value whose code is 0
+      bool some_raw = false;
+      if (__ballot(nc[s] && nb < 3u) != 0) {  // few kept bytes, or raw
         const uint32_t hi = c & 0xAAAAAAAAu, lo = c & 0x55555555u;
         const bool over = K && ((nb == 1u && hi != 0) || (nb == 2u && (lo & (hi >> 1)) != 0));
         bad = bad || over;
         c = over ? 0u : c;
+        per = raw ? (uint32_t)BYTES : nb;
+        some_raw = __ballot(raw) != 0;
+        // A row of raw blocks alone is its stored bytes, realigned. (Lane by lane, as
+        // below, their runs of 64 or 128 bytes would all start in the same four or
+        // two LDS banks. 160 MB of raw blocks: float32, b = 128, 178 us a call so and
+        // 80 this way; float64 171 and 72, b = 1024 329 and 94.)
+        if (__builtin_expect(some_raw, 0) && __ballot(raw || cnt == 0) == ~0ull) {
+          const uint32_t at = uniform(done);
+          const uint4* const q = reinterpret_cast<const uint4*>(stage + (at & ~15u));
+#pragma unroll 1
+          for (uint32_t k = 0; k < CH; ++k) {
+            const uint32_t d = k * kWave + lane;
+            const uint4 u = realign16(q[d], q[d + 1], (at >> 2) & 3u, at & 3u);
+            put(d, v4u{u.x, u.y, u.z, u.w});
+          }
+          done += (tail ? std::min<uint32_t>(nval_t > i0 ? nval_t - i0 : 0u, (uint32_t)G::ROW) : (uint32_t)G::ROW) *
+                  (uint32_t)BYTES;
+          continue;
+        }
       }
-      const bool some_raw = __ballot(raw) != 0;
-      if (some_raw) nb = raw ? (uint32_t)BYTES : nb;
       // stored bytes of the lane, and its first one's place in the stage
-      const uint32_t lb =
-          (uint32_t)__umul24(nb, (uint32_t)cnt) - ((uint32_t)__popc(c) + (uint32_t)__popc(c & 0xAAAAAAAAu));
+      const uint32_t lb = (uint32_t)__umul24(per, (uint32_t)cnt) -
+                          ((uint32_t)__popc(c) + (uint32_t)__popc(c & 0xAAAAAAAAu));
       const uint32_t inc = wave_incl_sum_u32(lb);
       uint32_t o = done + inc - lb;
       done += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
@@ -786,12 +821,13 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
       // the stage's size allows for. Values past the end of a short block read
       // whatever lies there and are not stored; being last in their lane and
       // block, they only reach other such values. (Lanes of constant blocks run
-      // along with nb = 0.)
+      // along with nb = 0, and so do those of raw blocks, all at one address.)
       const uint32_t nbh = nb < 4u ? nb : 4u;
       const bool longer = sizeof(T) == 8 && __ballot(nb > 4u) != 0;  // some value stores bytes of its low word
       uint32_t got[EPL], gotl[sizeof(T) == 8 ? EPL : 1], own[EPL];
       uint32_t run = 0;
       const uint32_t o0 = o;
+      o = raw ? kStageHead : o;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
         // o: where the value's word would start if its leading bytes were stored
@@ -868,26 +904,29 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
 #pragma unroll
           for (int i = 0; i < EPL; ++i) v[i] = mu[s];
         }
-        if (some_raw && raw) {  // the stored words
+        if (__builtin_expect(some_raw, 0) && raw) {  // the stored words
+          const uint32_t* p = reinterpret_cast<const uint32_t*>(stage + (o0 & ~3u));
+          uint32_t at = *p;
+          auto word = [&]() {
+            const uint32_t next = *++p, w = __builtin_amdgcn_alignbyte(next, at, o0);
+            at = next;
+            return w;
+          };
 #pragma unroll
           for (int i = 0; i < EPL; ++i) {
-            const uint32_t lo = stage_get(stage, o0 + (uint32_t)(i * BYTES));
+            const uint32_t lo = word();
             if constexpr (sizeof(T) == 4)
               v[i] = from_bits<T>(lo);
             else
-              v[i] = from_bits<T>((U)lo | ((U)stage_get(stage, o0 + (uint32_t)(i * BYTES) + 4u) << (sizeof(U) * 8 - 32)));
+              v[i] = from_bits<T>((U)lo | ((U)word() << (sizeof(U) * 8 - 32)));
           }
         }
       }
     }
 
-    T* const y = reinterpret_cast<T*>(a.out) + kb * B;  // of the tile
-    const uint32_t i0 = (wave * G::WBLK + (uint32_t)(s * G::GPW)) * (uint32_t)B;  // the row's first value
-    constexpr uint32_t CH = (uint32_t)(EPL * BYTES) / 16u;  // 16-byte chunks a lane
     if constexpr (SUB == 1) {
       // The row passes through the stage (its mid bytes are used up), so that
-      // every store of the wave covers 1 KiB without gaps and can stream past
-      // the caches (the values are not read again here). Chunk c of lane L
+      // every store of the wave covers 1 KiB without gaps. Chunk c of lane L
       // sits at slot L CH + (c ^ (L / (16 / CH)) mod CH): 16 lanes writing one
       // chunk each, or reading 16 consecutive ones, touch all 64 banks.
       v4u* const slots = reinterpret_cast<v4u*>(stage);
@@ -910,16 +949,7 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
       for (uint32_t k = 0; k < CH; ++k) {
         const uint32_t d = k * kWave + lane;  // chunk of the row
         const uint32_t L = d / CH;
-        const v4u w = slots[L * CH + ((d % CH) ^ ((L / PER) % CH))];
-        const uint32_t first = i0 + d * (16u / BYTES);  // its first value
-        if (!tail || first + 16u / BYTES <= nval_t) {
-          __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(y + first));
-        } else {
-          uint32_t* const yw = reinterpret_cast<uint32_t*>(y + first);
-#pragma unroll
-          for (uint32_t j = 0; j < 4; ++j)
-            if (first + j * 4u / BYTES < nval_t) yw[j] = w[j];
-        }
+        put(d, slots[L * CH + ((d % CH) ^ ((L / PER) % CH))]);
       }
     } else {
       T* const yl = y + (i0 + lane * EPL);

@@ -327,6 +327,26 @@ __device__ __forceinline__ double buffer_value<double>(__amdgpu_buffer_rsrc_t rs
   return __longlong_as_double((long long)(((uint64_t)u.y << 32) | u.x));
 }
 
+// The 16 bytes that start 4 k + sh bytes into the 32 of q0 and q1 (k, sh < 4,
+// k the same for every lane: a uniform branch picks the words).
+__device__ __forceinline__ uint4 realign16(const uint4& q0, const uint4& q1, uint32_t k, uint32_t sh) {
+  const uint32_t w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+  switch (k) {
+    case 0:
+      return make_uint4(__builtin_amdgcn_alignbyte(w[1], w[0], sh), __builtin_amdgcn_alignbyte(w[2], w[1], sh),
+                        __builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh));
+    case 1:
+      return make_uint4(__builtin_amdgcn_alignbyte(w[2], w[1], sh), __builtin_amdgcn_alignbyte(w[3], w[2], sh),
+                        __builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh));
+    case 2:
+      return make_uint4(__builtin_amdgcn_alignbyte(w[3], w[2], sh), __builtin_amdgcn_alignbyte(w[4], w[3], sh),
+                        __builtin_amdgcn_alignbyte(w[5], w[4], sh), __builtin_amdgcn_alignbyte(w[6], w[5], sh));
+    default:
+      return make_uint4(__builtin_amdgcn_alignbyte(w[4], w[3], sh), __builtin_amdgcn_alignbyte(w[5], w[4], sh),
+                        __builtin_amdgcn_alignbyte(w[6], w[5], sh), __builtin_amdgcn_alignbyte(w[7], w[6], sh));
+  }
+}
+
 // Inclusive sum over groups of G consecutive lanes (G a power of two <= 64).
 template <int G, typename V>
 __device__ __forceinline__ V group_incl_sum(V v) {

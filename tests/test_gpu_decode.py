@@ -67,3 +67,56 @@ def test_one_launch_and_two_meet(block, dtype):
             bad = s.copy()
             bad[at] ^= 1
             assert gpu_decompress(bad, szx.inspect(s[:96].tobytes()))[1] == 3, (n, at)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [8, 16, 32, 64, 128, 256, 512, 1024])
+def test_rows_of_raw_blocks(block, dtype):
+    """Rows that hold raw blocks alone, which are copied as they lie: all of a
+    field's, runs of them between coded and constant blocks (their stored bytes
+    start at every alignment), and a short last row or block."""
+    r = np.random.default_rng(block)
+    for n in (1, 7, 4096, 8191, 40_003, 140_001):
+        nblk = -(-n // block)
+        for runs in (1, 3, 40):  # blocks a run
+            sort = np.repeat(r.integers(0, 4, nblk // runs + 1), runs)[:nblk]
+            x = np.cumsum(r.standard_normal(n)) * 1e-2
+            x = np.where(np.repeat(sort == 0, block)[:n], 1.0, x).astype(dtype)
+            first = np.flatnonzero(sort >= 2) * block
+            x[np.minimum(first + r.integers(0, block, first.size), n - 1)] = np.nan
+            if runs == 3:
+                x[::block] = np.inf
+            ref = szref.compress(x, 1e-3, "abs", block)
+            y, status = gpu_decompress(ref)
+            assert status == 0 and same_bits(y, szref.decompress(ref)), (n, runs)
+
+
+@pytest.mark.parametrize("dtype,block", [("float32", 128), ("float64", 128), ("float64", 1024)])
+def test_raw_blocks_decode_at_half_the_copy_rate(dtype, block):
+    """A field of raw blocks, whose decompression only moves bytes, takes at most
+    twice the time of a device copy of as many bytes (160 MB each way; lane by
+    lane it took three to five times that)."""
+    dt = getattr(torch, dtype)
+    x = torch.randn((160 << 20) // torch.finfo(dt).bits * 8, device="cuda").to(dt)
+    x[::block] = float("nan")
+    out, size = szx.compress(x, 1e-3, "abs", block)
+    n = int(size.cpu().view(torch.int64))
+    ws = torch.zeros(szx.workspace_size(dt, x.shape, 1e-3, "abs", block), dtype=torch.uint8, device="cuda")
+    y, st = torch.empty_like(x), torch.zeros(1, dtype=torch.uint32, device="cuda")
+    info = dict(dtype=dt, dims=tuple(x.shape), block=block)
+    src, dst = torch.empty_like(x), torch.empty_like(x)
+
+    def median(fn):
+        ts = []
+        for _ in range(15):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            fn()
+            b.record()
+            b.synchronize()
+            ts.append(a.elapsed_time(b))
+        return sorted(ts)[7]
+    copy = median(lambda: dst.copy_(src))
+    took = median(lambda: szx.decompress(out, n, info, out=y, status=st, ws=ws))
+    assert int(st.cpu().view(torch.int32)) == 0 and torch.equal(y.view(torch.uint8), x.view(torch.uint8))
+    assert took <= 2.0 * copy, (took, copy)
