@@ -424,34 +424,39 @@ __device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, ui
       const_cast<uint8_t*>(in + h.sec.kbytes + R0), (short)0, (int)have_nc, 0x00020000);
   const __amdgpu_buffer_rsrc_t rc_ = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(in + h.sec.codes + R0 * (B / 4)), (short)0, (int)(have_nc * (B / 4)), 0x00020000);
-  uint32_t kbv[BPT];
-  BlockCodes<B> cv[AHEAD];
+  uint32_t mid = 0, midb[BPT] = {};
+  // A wave of constant blocks has none to look at: their loads, though of
+  // nothing, cost a constant field of 2^18 float32 values 11.6 us a call at
+  // b = 1024 (9.7 without) and 9.2 at b = 512 (8.1).
+  if (__ballot(ncb != 0) != 0) {
+    uint32_t kbv[BPT];
+    BlockCodes<B> cv[AHEAD];
 #pragma unroll
-  for (int i = 0; i < BPT; ++i) {
-    // this block's rank from the tile's first: rex plus the thread's
-    // non-constant blocks before it (constant blocks read far past the range)
-    const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
-    const bool live = (ncb >> i) & 1u;
-    kbv[i] = __builtin_amdgcn_raw_buffer_load_b8(rk_, live ? (int)rl : 0x40000000, 0, 0);
-    if (i < AHEAD) load_codes<B>(rc_, live ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i]);
-  }
-  uint32_t mid = 0, midb[BPT];
-#pragma unroll
-  for (int i = 0; i < BPT; ++i) {
-    const uint64_t k = k0 + i;
-    midb[i] = mid;  // the thread's mid bytes before its block i
-    if ((ncb >> i) & 1u) {
+    for (int i = 0; i < BPT; ++i) {
+      // this block's rank from the tile's first: rex plus the thread's
+      // non-constant blocks before it (constant blocks read far past the range)
       const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
-      if ((uint64_t)rl < have_nc) {
-        const uint32_t nk = (uint32_t)std::min<uint64_t>((uint64_t)B, a.n - k * B);
-        mid += block_mid_bytes<T, B>(cv[i % AHEAD], kbv[i], nk, bad);
-      } else {
-        bad = true;
-      }
+      const bool live = (ncb >> i) & 1u;
+      kbv[i] = __builtin_amdgcn_raw_buffer_load_b8(rk_, live ? (int)rl : 0x40000000, 0, 0);
+      if (i < AHEAD) load_codes<B>(rc_, live ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i]);
     }
-    if (i + AHEAD < BPT) {
-      const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << (i + AHEAD)) - 1u));
-      load_codes<B>(rc_, (ncb >> (i + AHEAD)) & 1u ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i % AHEAD]);
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const uint64_t k = k0 + i;
+      midb[i] = mid;  // the thread's mid bytes before its block i
+      if ((ncb >> i) & 1u) {
+        const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << i) - 1u));
+        if ((uint64_t)rl < have_nc) {
+          const uint32_t nk = (uint32_t)std::min<uint64_t>((uint64_t)B, a.n - k * B);
+          mid += block_mid_bytes<T, B>(cv[i % AHEAD], kbv[i], nk, bad);
+        } else {
+          bad = true;
+        }
+      }
+      if (i + AHEAD < BPT) {
+        const uint32_t rl = rex + (uint32_t)__popc(ncb & ((1u << (i + AHEAD)) - 1u));
+        load_codes<B>(rc_, (ncb >> (i + AHEAD)) & 1u ? rl * (uint32_t)(B / 4) : 0x40000000u, cv[i % AHEAD]);
+      }
     }
   }
   uint32_t tmid;

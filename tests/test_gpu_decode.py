@@ -120,3 +120,19 @@ def test_raw_blocks_decode_at_half_the_copy_rate(dtype, block):
     took = median(lambda: szx.decompress(out, n, info, out=y, status=st, ws=ws))
     assert int(st.cpu().view(torch.int32)) == 0 and torch.equal(y.view(torch.uint8), x.view(torch.uint8))
     assert took <= 2.0 * copy, (took, copy)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [8, 128, 512, 1024])
+def test_waves_of_constant_blocks(block, dtype):
+    """Runs of 256 constant blocks, which the index pass's waves skip, before,
+    between and after others, in one index tile and in several."""
+    for nblk, const in ((300, [0]), (700, [1]), (1030, [0, 2, 3]), (2600, [0, 1, 2, 3, 5, 8]), (1024, [0, 1, 2, 3])):
+        n = nblk * block - 3
+        x = np.random.default_rng(nblk).standard_normal(n)
+        for k in const:
+            x[k * 256 * block: (k + 1) * 256 * block] = 0.25
+        x = x.astype(dtype)
+        ref = szref.compress(x, 1e-3, "abs", block)
+        y, status = gpu_decompress(ref)
+        assert status == 0 and same_bits(y, szref.decompress(ref)), (nblk, const)
