@@ -8,8 +8,12 @@ covers, so it is measured per (device, block size, element type, size class)
 and cached in a JSON file ($SZX_TUNE_CACHE, default ~/.cache/szx/tune.json).
 apply_cache loads the entries of one device and block size into the
 library's process-wide table (per element type and size class), which
-sz_compress and new batches consult. The other launch parameters (tile bytes
-of the passes) are compile-time constants of the kernels.
+sz_compress and new batches consult. (Single calls of at most 8192 blocks and
+256 encode tiles take a workgroup a tile and ignore the knob.) A batch of both
+element types whose encode pass is one launch for both has one number, the
+larger of the two: its types are tuned together, for that batch alone, and
+nothing of it is stored as one type's. The other launch parameters (tile bytes of
+the passes) are compile-time constants of the kernels.
 """
 import json
 import os
@@ -19,6 +23,20 @@ import torch
 from . import szx
 
 MULTIPLIERS = (1, 2, 3, 4, 6, 8, 12, 16)
+
+# Where the encode pass of a batch of both types is one launch: blocks below
+# 1024 values, at most 16384 tiles of 32 KiB. (A field's last tile may be a short
+# one, so the bytes give the fewest tiles there can be: a batch counted as
+# shared here may yet have two launches, never the other way round.)
+SHARED_BELOW_BLOCK = 1024
+SHARED_BYTES = 16384 * 32768
+
+
+def shares_encode_launch(bytes_per_dtype, block):
+    """Whether a batch of these bytes per element type may encode both types in
+    one launch."""
+    present = [v for v in bytes_per_dtype.values() if v > 0]
+    return len(present) > 1 and int(block) < SHARED_BELOW_BLOCK and sum(present) <= SHARED_BYTES
 
 
 def cache_path():
@@ -93,10 +111,11 @@ def tune_batch(batch, bytes_per_dtype, block=128, reps=5, multipliers=MULTIPLIER
                timer=None, device=None):
     """Time batch.run() over the candidate encode geometries of each element
     type present (bytes_per_dtype: {"float32": bytes, "float64": bytes}), keep
-    the fastest in the batch, the library table and the cache. `block` is the
-    block size of the batch's fields (part of the cache key); `timer(fn,
-    reps)` returns the time of fn in ms (default: the median of reps runs
-    between device events); `device` is a device index or key. Returns
+    the fastest in the batch, the library table and the cache. Types that may
+    share their encode launch are swept together, and what is found stays in the
+    batch. `block` is the block size of the batch's fields (part of the cache
+    key); `timer(fn, reps)` returns the time of fn in ms (default: the median of
+    reps runs between device events); `device` is a device index or key. Returns
     {dtype: (encode_wgs, ms, {candidate: ms})}."""
     dev = device_key(device)
     ncu = _compute_units(dev)
@@ -104,19 +123,23 @@ def tune_batch(batch, bytes_per_dtype, block=128, reps=5, multipliers=MULTIPLIER
     entries = _load() if store else {}
     result = {}
     batch.run()  # warm
-    for dtype, nbytes in bytes_per_dtype.items():
-        if nbytes <= 0:
-            continue
+    present = [dtype for dtype, nbytes in bytes_per_dtype.items() if nbytes > 0]
+    shared = shares_encode_launch(bytes_per_dtype, block)
+    for group in [present] if shared else [[dtype] for dtype in present]:
         times = {}
         for m in multipliers:
-            batch.set_geometry(m * ncu, dtype)
+            for dtype in group:
+                batch.set_geometry(m * ncu, dtype)
             times[m * ncu] = timer(batch.run, reps)
         best = min(times, key=times.get)
-        batch.set_geometry(best, dtype)
-        cls = szx.size_class(nbytes)
-        szx.set_geometry(dtype, cls, best)
-        entries[_key(dev, block, dtype, cls)] = dict(encode_wgs=best, ms=times[best], bytes=int(nbytes))
-        result[dtype] = (best, times[best], times)
-    if store:
+        for dtype in group:
+            batch.set_geometry(best, dtype)
+            result[dtype] = (best, times[best], times)
+            if not shared:
+                cls = szx.size_class(bytes_per_dtype[dtype])
+                szx.set_geometry(dtype, cls, best)
+                entries[_key(dev, block, dtype, cls)] = dict(encode_wgs=best, ms=times[best],
+                                                             bytes=int(bytes_per_dtype[dtype]))
+    if store and not shared:
         _store(entries)
     return result

@@ -120,3 +120,42 @@ def test_apply_cache_tolerates_missing_and_foreign_files(cache):
     assert tune.apply_cache(DEV) == 0
     path.write_text(json.dumps({"odd-key": {"encode_wgs": 1}, f"{DEV}|b128|float32|c2": {"encode_wgs": 999}}))
     assert tune.apply_cache(DEV) == 1 and table == [("float32", 2, 999)]
+
+
+class SharedBatch(FakeBatch):
+    """A batch whose types encode in one launch: the larger number is launched."""
+
+    def launched(self):
+        return max(self.geom.get(dt) or 4 * 256 for dt in ("float32", "float64"))
+
+
+def shared_timer(batch, cost):
+    seen = []
+
+    def timer(fn, reps):
+        fn()
+        seen.append(batch.launched())
+        return cost(batch.launched())
+    return timer, seen
+
+
+@pytest.mark.parametrize("best", [256, 768, 4096])
+def test_types_that_share_a_launch_are_tuned_together(cache, best):
+    """Every candidate is what the launch really has, the fastest is found below
+    the default too, and a time of both types is not stored as one type's."""
+    path, table = cache
+    b = SharedBatch()
+    timer, seen = shared_timer(b, lambda w: 1.0 + abs(w - best) / 1000.0)
+    res = tune.tune_batch(b, {"float32": 300 << 20, "float64": 100 << 20}, block=128, reps=1, timer=timer, device=DEV)
+    assert seen == [m * 256 for m in tune.MULTIPLIERS]
+    assert b.launched() == best and b.geom == {"float32": best, "float64": best}
+    assert all(res[dt][0] == best and res[dt][1] == pytest.approx(1.0) for dt in ("float32", "float64"))
+    assert table == [] and not path.exists()
+
+
+def test_where_types_share_a_launch():
+    assert tune.shares_encode_launch({"float32": 1 << 20, "float64": 1}, 128)
+    assert tune.shares_encode_launch({"float32": 256 << 20, "float64": 256 << 20}, 512)
+    assert not tune.shares_encode_launch({"float32": 256 << 20, "float64": (256 << 20) + 1}, 512)
+    assert not tune.shares_encode_launch({"float32": 1 << 20, "float64": 1 << 20}, 1024)
+    assert not tune.shares_encode_launch({"float32": 1 << 20, "float64": 0}, 128)
