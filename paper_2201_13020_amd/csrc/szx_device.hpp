@@ -249,14 +249,14 @@ __device__ __forceinline__ void wave_sync() {
 // rows 0 and 2 added to rows 1 and 3 (row_bcast:15) and the last lane of row 1
 // to rows 2 and 3 (row_bcast:31). Lanes without a source add 0. No LDS.
 __device__ __forceinline__ uint32_t wave_incl_sum_u32(uint32_t v) {
-  int x = (int)v;
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return (uint32_t)x;
+  // (unsigned: the sums wrap where they overflow)
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
 }
 
 // Lane i - d within each row of 16 lanes (row_shr:d, d in {1, 2, 4, 8});
@@ -455,8 +455,8 @@ __device__ __forceinline__ void wg_excl_scan_multi(const uint32_t (&v)[S], uint3
 
 // A tile's status word: flag in the top two bits (0 = not yet published,
 // 1 = aggregate of the tile alone, 2 = inclusive prefix), value below. An
-// aggregate takes at most 23 bits (the values of 1024 blocks of 1024 doubles),
-// so a window of them adds up in 32 bits, with DPP and no LDS (sums of 64-bit
+// aggregate takes at most 24 bits (the 2^23 bytes of 1024 blocks of 1024
+// doubles), so a window of 256 of them adds up in 32 bits, with DPP and no LDS (sums of 64-bit
 // words by lane shuffles cost 12 LDS permutes a window, one after another).
 constexpr uint64_t kFlagAgg = 1ull << 62;
 constexpr uint64_t kFlagIncl = 2ull << 62;

@@ -105,7 +105,8 @@ constexpr uint32_t kClsBlocks = 1024;
 // gate of the chained index): 100x500x500 float32 (191 tiles) 12.3 -> 8.3 us,
 // one tile 7.5 -> 5.9 us, 256 batched fields 26 -> 17.6 us. Beyond, the counts
 // grow with the square of the tiles (2048 of them would read 270 MB of state
-// bits; the chained pass over them takes 38 us in all).
+// bits; the chained pass over them takes 38 us in all). The sums are 32-bit ones:
+// the totals of 256 tiles reach 2^31 (raw doubles, b = 1024).
 constexpr uint32_t kDirectTiles = 256;
 
 // Bounds of the kernels' waits, in polls without progress (0.2 us each). A

@@ -136,3 +136,22 @@ def test_waves_of_constant_blocks(block, dtype):
         ref = szref.compress(x, 1e-3, "abs", block)
         y, status = gpu_decompress(ref)
         assert status == 0 and same_bits(y, szref.decompress(ref)), (nblk, const)
+
+
+def test_direct_index_at_its_largest_sum():
+    """262144 raw blocks of 1024 doubles, the most that the direct index takes:
+    its totals add up to 2^31 mid bytes. Then a header that states one less."""
+    n, block = 1 << 28, 1024
+    x = torch.randn(n, device="cuda", dtype=torch.float64)
+    x[::block] = float("nan")
+    out, size = szx.compress(x, 1e-3, "abs", block)
+    m = int(size.cpu().view(torch.int64))
+    info = szx.inspect(out[:96].cpu().numpy().tobytes())
+    assert int(out[88:96].cpu().view(torch.int64)) == 1 << 31
+    y, st = szx.decompress(out, m, info)
+    torch.cuda.synchronize()
+    assert int(st.cpu().view(torch.int32)) == 0 and torch.equal(y.view(torch.int64), x.view(torch.int64))
+    out[88:96] = torch.tensor([(1 << 31) - 1], dtype=torch.int64).view(torch.uint8).cuda()
+    _, st = szx.decompress(out, m, info)
+    torch.cuda.synchronize()
+    assert int(st.cpu().view(torch.int32)) == 3
