@@ -142,7 +142,6 @@ szx::FieldC single_field_c(const szx::Job& j, const void* in, void* out, uint64_
   f.stats = ws + W.stats;
   f.plan = ws + W.plan;
   f.enc_r0 = (uint32_t*)(ws + W.enc_r0);
-  f.enc_list = f.enc_r0 + ft.enc + 1;
   f.cls_status = (uint64_t*)(ws + W.cls_status);
   f.enc_mid = (uint64_t*)(ws + W.enc_mid);
   return f;
@@ -160,7 +159,6 @@ szx::FieldD single_field_d(const szx::Job& j, const void* in, uint64_t in_bytes,
   f.index = (uint64_t*)(ws + W.dec_index);
   f.rank_st = (uint64_t*)(ws + W.dec_rank);
   f.mid_st = (uint64_t*)(ws + W.dec_mid);
-  f.totals = (uint32_t*)f.mid_st;
   f.n = j.n;
   f.nblk = j.nblk;
   f.dtype = j.dtype;
@@ -263,11 +261,11 @@ sz_status plan_compress(const sz_cfield* fs, uint32_t n, uint8_t* ws, std::vecto
     cls_off[i] = off;
     off = a256(off + (ft.cls + 1) * 8);
   }
-  // the encode tiles' status words: one array per element type, the fields'
-  // one after another (and the word behind the last, which stays zero)
+  // the encode tiles' status words: one array per element type with tiles, the
+  // fields' one after another (and the word behind the last, which stays zero)
   for (int dt = 0; dt < 2; ++dt) {
     mid_off[dt] = off;
-    off = a256(off + (P.tiles[4 + dt] + 1) * 8);
+    if (P.tiles[4 + dt]) off = a256(off + (P.tiles[4 + dt] + 1) * 8);
   }
   P.zero_end = off;
   std::vector<uint64_t> parts_off(n), stats_off(n), plan_off(n), r0_off(n);
@@ -418,7 +416,6 @@ sz_status plan_decompress(const sz_dfield* fs, uint32_t n, uint8_t* ws, std::vec
     f.index = (uint64_t*)(ws + index_off[i]);
     f.rank_st = (uint64_t*)(ws + rank_off[i]);
     f.mid_st = (uint64_t*)(ws + mid_off[i]);
-    f.totals = (uint32_t*)f.mid_st;
     f.n = j.n;
     f.nblk = j.nblk;
     f.dtype = j.dtype;

@@ -68,7 +68,6 @@ __device__ __forceinline__ FieldC field_at(const CBatch& b, uint32_t fi) {
   f.stats = as_global(f.stats);
   f.plan = as_global(f.plan);
   f.enc_r0 = as_global(f.enc_r0);
-  f.enc_list = as_global(f.enc_list);
   f.cls_status = as_global(f.cls_status);
   f.enc_mid = as_global(f.enc_mid);
   return f;
@@ -571,12 +570,19 @@ __device__ __forceinline__ void finish_stream(const FieldC& f, uint64_t mid_tota
 
 // -------------------------------------------------------------- classify ---
 
+// A single call's list of tiles to encode, behind the first ranks of its tiles.
+template <typename T, int B>
+__device__ __forceinline__ uint32_t* tile_list(const FieldC& f) {
+  return f.enc_r0 + cdiv(f.nblk, (uint64_t)EncGeo<T, B>::TBLK) + 1;
+}
+
 // mu and the constant test of every block, the state bits, and the rank of the
 // first non-constant block of every encode tile (a prefix count over tiles of
-// CLS blocks, four per thread at most). The last tile writes n_nc.
+// CLS blocks, four per thread at most). The last tile writes n_nc. listed: a
+// single call, whose encode pass takes its tiles from a list.
 template <typename T, int B>
-__device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint32_t* s_scan, uint32_t* s_state,
-                                              uint64_t* s_base, uint64_t* s_red) {
+__device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, bool listed, uint32_t* s_scan,
+                                              uint32_t* s_state, uint64_t* s_base, uint64_t* s_red) {
   using U = typename Traits<T>::U;
   constexpr int TBLK = EncGeo<T, B>::TBLK;
   constexpr int CLS = (int)kClsBlocks;
@@ -693,9 +699,9 @@ __device__ __forceinline__ void classify_tile(const FieldC& f, uint32_t t, uint3
   if (starts) {
     const uint32_t et = (uint32_t)(k0 / TBLK);
     f.enc_r0[et] = base + ex;
-    if (f.enc_list) {
+    if (listed) {
       if (used)
-        f.enc_list[tbase + (ex2[1] - total)] = et;
+        tile_list<T, B>(f)[tbase + (ex2[1] - total)] = et;
       else
         status_store(f.enc_mid + et, et == 0 ? kFlagIncl : kFlagAgg);
     }
@@ -725,7 +731,7 @@ __global__ __launch_bounds__(256) void k_classify(CBatch b) {
   __shared__ uint64_t s_red[2 * kWavesPerWG];
   const uint64_t g = blockIdx.x;
   const FieldC f = field_at(b, field_of(b.field_cls[Traits<T>::BYTES / 8], g));
-  classify_tile<T, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+  classify_tile<T, B>(f, (uint32_t)(g - f.base_cls), !b.fields, s_scan, s_state, &s_base, s_red);
 }
 
 template <int B>
@@ -737,11 +743,11 @@ __global__ __launch_bounds__(256) void k_classify_both(CBatch b) {
   uint64_t g = blockIdx.x;
   if (g < b.tiles_cls[0]) {
     const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_cls[0], g));
-    classify_tile<float, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+    classify_tile<float, B>(f, (uint32_t)(g - f.base_cls), false, s_scan, s_state, &s_base, s_red);
   } else {
     g -= b.tiles_cls[0];
     const FieldC f = field_at<kBatch>(b, field_of<kBatch>(b.field_cls[1], g));
-    classify_tile<double, B>(f, (uint32_t)(g - f.base_cls), s_scan, s_state, &s_base, s_red);
+    classify_tile<double, B>(f, (uint32_t)(g - f.base_cls), false, s_scan, s_state, &s_base, s_red);
   }
 }
 
@@ -1134,7 +1140,7 @@ __device__ __forceinline__ void encode_pass(const CBatch& b, EncShared& sh, uint
   const FieldC* const one = BATCH == kSingle ? field_ref<BATCH>(b, 0) : nullptr;
   const uint64_t ntiles = BATCH == kSingle ? listed_tiles(as_constant(one->ctr)->err, as_constant(one->ctr)->n_tiles)
                                            : b.tiles_enc[DT];
-  const uint32_t* const list = BATCH == kSingle ? as_global(one->enc_list) : nullptr;
+  const uint32_t* const list = BATCH == kSingle ? as_global(tile_list<T, B>(*one)) : nullptr;
   uint32_t* ticket = b.tickets + (DT * kTicketClasses + cls) * 64;
   const uint32_t wave = uniform(threadIdx.x / kWave);
   const uint32_t lane = (uint32_t)lane_id(), lig = lane % LPB;

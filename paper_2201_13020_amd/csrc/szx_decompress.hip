@@ -49,7 +49,6 @@ __device__ __forceinline__ FieldD field_at(const DBatch& b, uint32_t fi) {
   f.index = as_global(f.index);
   f.rank_st = as_global(f.rank_st);
   f.mid_st = as_global(f.mid_st);
-  f.totals = as_global(f.totals);
   return f;
 }
 __device__ __forceinline__ uint32_t dfield_of(const uint32_t* map, uint64_t t) { return map ? *as_constant(map + t) : 0u; }
@@ -310,6 +309,8 @@ constexpr uint64_t kIndexMid = (1ull << 48) - 1;
 // bits) and the tile's mid bytes follow it (17 bits).
 __device__ __forceinline__ uint64_t index_direct(uint32_t mid, uint32_t bytes) { return mid | ((uint64_t)bytes << 24); }
 constexpr uint32_t kTotalBad = 0x80000000u;  // in an index tile's total: the stream failed validation there
+// A direct index's totals: each index tile's mid bytes, in place of status words.
+__device__ __forceinline__ uint32_t* direct_totals(const FieldD& a) { return reinterpret_cast<uint32_t*>(a.mid_st); }
 
 // How the index pass finds what lies before a tile: kChained by single-pass
 // prefix sums, kDirect by counting it, kOne where the field is one index tile
@@ -492,7 +493,7 @@ __device__ __forceinline__ bool dindex_tile(const DBatch& b, const FieldD& a, ui
 #pragma unroll
       for (int i = 0; i < kWavesPerWG; ++i) any |= s_scan[kWavesPerWG + i];
       if constexpr (MODE == kDirect)
-        a.totals[t] = tmid | (any ? kTotalBad : 0u);
+        direct_totals(a)[t] = tmid | (any ? kTotalBad : 0u);
       else if (dt == 0)
         *a.status = any ? kStatusCorrupt : 0u;
     }
@@ -602,7 +603,7 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
     e0 = uniform(entry[0]);
     e1 = uniform(entry[1]);
   } else {
-    sums = totals_load(a.totals, direct ? it : 0u);
+    sums = totals_load(direct_totals(a), direct ? it : 0u);
     const uint64_t* e = as_constant(a.index + 2 * (uint64_t)t);
     e0 = e[0];
     e1 = e[1];
@@ -656,7 +657,7 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
     m0_t = (uint64_t)base + rel;
     // once a field: the index tiles' own findings, and the sum of all
     if (!ONE && kb + nblk_t == a.nblk) {
-      const Totals all = totals_load(a.totals, it + 1);
+      const Totals all = totals_load(direct_totals(a), it + 1);
       if (totals_sum(all) != h.mid_total || totals_bad(all)) bad = true;
     }
   }

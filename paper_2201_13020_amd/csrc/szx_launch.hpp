@@ -29,8 +29,7 @@ struct FieldC {
   uint64_t* parts;      // first use only: per chunk, lowest and highest totalOrder key of its finite values
   void* stats;          // two totalOrder keys per block
   uint8_t* plan;        // one plan byte per block (classification -> encode)
-  uint32_t* enc_r0;     // first rank of every encode tile
-  uint32_t* enc_list;   // single calls: the encode tiles with a non-constant block
+  uint32_t* enc_r0;     // first rank of every encode tile; behind them (single calls) the list of tiles to encode
   uint64_t* cls_status; // scan status words, classification tiles
   uint64_t* enc_mid;    // scan status words, encode tiles
   uint64_t base_stats, base_cls, base_enc;  // first chunk / tile of the field in its type's numbering
@@ -70,8 +69,7 @@ struct FieldD {
   uint32_t* status;
   uint64_t* index;    // per decode tile: first rank, first mid byte
   uint64_t* rank_st;  // scan status words of the index pass
-  uint64_t* mid_st;
-  uint32_t* totals;   // direct index: each index tile's mid bytes (in place of mid_st)
+  uint64_t* mid_st;   // (a direct index keeps each index tile's mid bytes there, 32 bits each)
   uint64_t n, nblk;
   uint32_t dtype, ndims;
   uint64_t dims[4];

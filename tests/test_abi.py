@@ -160,3 +160,23 @@ def test_shard_params_and_their_checks():
     for k0, k1 in [(4, 24), (8, 20), (8, 80), (8, 8), (16, 8)]:
         with pytest.raises(szx.SzError):
             szx.shard_params(field, k0, k1)
+
+
+@pytest.mark.parametrize("types,n,block,fields,compress,decompress", [
+    (("float32",), 9000, 512, 1, 23808, 1792),
+    (("float64",), 1 << 20, 8, 1, 2262272, 14080),
+    (("float32",), 1, 128, 2, 42496, 2560),
+    (("float64",), 4096, 16, 2, 50176, 2560),
+    (("float32",), 100_003, 64, 100, 3293952, 126720),
+    (("float32", "float64"), 250_000, 128, 1000, 45335296, 2554624),
+    (("float32", "float64"), 0, 1024, 3, 58112, 3072)])
+def test_batch_workspaces_do_not_grow(types, n, block, fields, compress, decompress):
+    """Workspaces that callers allocated for these batches stay large enough
+    (the sizes the library has asked for before)."""
+    from paper_2201_13020_amd import szx
+    c, d = (szx.SzCField * fields)(), (szx.SzDField * fields)()
+    for i in range(fields):
+        c[i].params = d[i].expected = szx.make_params(types[i % len(types)], (n,), 1e-3, "rel", block)
+    L = szx.lib()
+    assert 0 < L.sz_batch_workspace_size(c, None, fields) <= compress
+    assert 0 < L.sz_batch_workspace_size(None, d, fields) <= decompress
