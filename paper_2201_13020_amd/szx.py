@@ -171,11 +171,17 @@ def workspace_size(dtype, dims, eb=0.0, mode="rel", block=128):
     return int(lib().sz_workspace_size(ctypes.byref(make_params(dtype, dims, eb, mode, block))))
 
 
+# torch's handle of a device's current stream without a Stream object around it
+# (which takes 3 us); not a public name, so other versions may lack it
+_raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream):
     if stream is not None:
         return ctypes.c_void_p(stream.cuda_stream)
-    # the current stream's handle without a Stream object around it (3 us)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_current_stream is not None:
+        return ctypes.c_void_p(_raw_current_stream(torch.cuda.current_device()))
+    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _on(stream, device):

@@ -29,3 +29,29 @@ def test_errors_are_the_same_with_and_without_buffers(given):
         with pytest.raises(szx.SzError) as e:
             szx.compress(x, 1e-3, "rel", 128, out=out[:64], out_size=kw["out_size"], ws=ws)
         assert e.value.code == 2
+
+
+def test_stream_handle_without_the_raw_call(monkeypatch):
+    """Where torch lacks the private call, the current stream's handle comes from
+    the public one; a stream that is handed in is asked itself."""
+    class Stream:
+        cuda_stream = 0x1234
+    monkeypatch.setattr(szx, "_raw_current_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    assert szx._stream_handle(None).value == 0x1234
+    other = Stream()
+    other.cuda_stream = 0x5678
+    assert szx._stream_handle(other).value == 0x5678
+
+
+def test_import_without_the_raw_call():
+    """The binding loads where torch has no such name."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(szx.__file__)))
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2201_13020_amd import szx\n"
+            "assert szx._raw_current_stream is None\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=root, timeout=300)
