@@ -34,6 +34,9 @@ def field(kind, n, dtype, block):
 
 CASES = [  # values, wgs: one tile, ragged tiles, tens of tiles on eight workgroups
     (1, 0), (4097, 0), (8191, 0), (40_000, 0), (600_007, 8), (300_000, 9)]
+# (With blocks of 128, 512 and 1024 values the last two take the two-launch path, which has
+# a workgroup a tile: test_few_workgroups_above_the_small_calls and
+# test_full_rings_follow_partly_filled_ones have the tickets and rings there.)
 
 
 @pytest.mark.parametrize("dtype", ["float32", "float64"])
@@ -173,3 +176,37 @@ def test_both_types_with_a_workgroup_beyond_the_resident_ones(n32, n64, wgs):
             for i, ref in enumerate(refs):
                 m = int(b.sizes[i].cpu().view(torch.int64))
                 assert m == ref.size and np.array_equal(b.outs[i][:m].cpu().numpy(), ref), (i, use)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("block", [128, 256, 512, 1024])
+def test_full_rings_follow_partly_filled_ones(block, dtype):
+    """Rings of the persistent encoder that fill up behind a pending tile of few
+    bytes, and the other way round: runs of smooth blocks between runs that are
+    stored whole (a NaN in every block, or no bound), the runs some fractions of a
+    tile and some tiles long, on eight and nine workgroups and on the default
+    number."""
+    dt = torch.float32 if dtype == "float32" else torch.float64
+    n = 2_200_003
+    r = np.random.default_rng(block)
+    nblk = -(-n // block)
+    tile = max(8, 32768 // (block * (4 if dtype == "float32" else 8)))
+    raw = np.zeros(nblk, bool)
+    at = 0
+    while at < nblk:
+        smooth, full = (int(r.integers(1, 4 * tile)) for _ in range(2))
+        raw[at + smooth: at + smooth + full] = True
+        at += smooth + full
+    x = field("smooth", n, dtype, block)
+    first = np.flatnonzero(raw) * block
+    x[np.minimum(first + r.integers(0, block, first.size), n - 1)] = np.nan
+    for eb in (1e-3, 0.0):
+        ref = szref.compress(x, eb, "rel", block)
+        cls = szx.size_class(x.nbytes)
+        for wgs in (8, 9, 0):
+            try:
+                szx.set_geometry(dt, cls, wgs)
+                out, size = gpu_compress(x, eb, "rel", block)
+            finally:
+                szx.set_geometry(dt, cls, 0)
+            assert size == ref.size and np.array_equal(out[:size].cpu().numpy(), ref), (eb, wgs)
