@@ -257,7 +257,8 @@ uint32_t sz_size_class(uint64_t bytes);
 /* Process-wide encode geometry for inputs of one element type and size class,
    used by sz_compress (fields of more than 256 encode tiles or 8192 blocks;
    smaller ones take a workgroup a tile) and as the starting geometry of new batches;
-   encode_wgs = 0 restores the default (4 per compute unit). Thread-safe;
+   encode_wgs = 0 restores the default (as many as the device holds at once,
+   less two: 4 per compute unit, 2 for float64 blocks of 1024). Thread-safe;
    no effect on the output bytes. */
 sz_status sz_set_geometry(sz_dtype dtype, uint32_t size_class, uint32_t encode_wgs);
 

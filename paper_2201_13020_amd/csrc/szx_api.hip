@@ -177,9 +177,9 @@ uint32_t size_class_of(uint64_t bytes) {
   return c;
 }
 
-uint32_t encode_wgs_for(uint32_t dtype, uint64_t bytes, int ncu) {
+uint32_t encode_wgs_for(uint32_t dtype, uint64_t bytes, uint32_t block, int ncu) {
   const uint32_t v = g_geom[dtype][size_class_of(bytes)].load(std::memory_order_relaxed);
-  return v ? v : (uint32_t)ncu * 4;
+  return v ? v : default_encode_wgs((uint32_t)ncu, block, dtype == SZ_F32 ? 4 : 8);
 }
 
 CLaunchGeom batch_geom(const sz_cfield* fs, uint32_t n, int ncu) {
@@ -189,7 +189,7 @@ CLaunchGeom batch_geom(const sz_cfield* fs, uint32_t n, int ncu) {
     if (make_job(&fs[i].params, j) == SZ_OK) bytes[j.dtype] += j.n * j.w;
   }
   CLaunchGeom g;
-  for (int dt = 0; dt < 2; ++dt) g.encode_wgs[dt] = encode_wgs_for(dt, bytes[dt], ncu);
+  for (int dt = 0; dt < 2; ++dt) g.encode_wgs[dt] = encode_wgs_for(dt, bytes[dt], fs[0].params.block_size, ncu);
   return g;
 }
 
@@ -513,7 +513,7 @@ sz_status compress_single(const Job& j, const void* d_in, void* d_out, uint64_t 
   b.nfields = 1;
   b.any_empty = j.nblk == 0;
   szx::CLaunchGeom g;
-  g.encode_wgs[0] = g.encode_wgs[1] = encode_wgs_for(j.dtype, j.n * j.w, ncu);
+  g.encode_wgs[0] = g.encode_wgs[1] = encode_wgs_for(j.dtype, j.n * j.w, j.b, ncu);
   const hipError_t e = szx::launch_compress(b, j.b, g, stream, current_hook());
   if (e != hipSuccess) return fail(SZ_EDEVICE, std::string("launch failed: ") + hipGetErrorString(e));
   return SZ_OK;

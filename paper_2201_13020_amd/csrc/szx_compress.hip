@@ -173,6 +173,7 @@ struct EncGeo {
   // waves per SIMD, as the rings fit the 160 KiB of LDS: four workgroups of 32
   // KiB, or two of the 64 KiB of 1024-double blocks
   static constexpr int WAVES = RING > 8192u ? 2 : 4;
+  static_assert(WAVES == (int)enc_resident(B, sizeof(T)), "as the default number of workgroups counts them");
 };
 
 // ----------------------------------------------------------------- stats ---

@@ -93,6 +93,20 @@ __host__ __device__ constexpr uint32_t tile_blocks(uint32_t b, uint32_t w, uint3
 __host__ __device__ constexpr uint32_t enc_blocks(uint32_t b, uint32_t w) { return tile_blocks(b, w, kEncodeTileBytes); }
 __host__ __device__ constexpr uint32_t dec_blocks(uint32_t b, uint32_t w) { return tile_blocks(b, w, kDecodeTileBytes); }
 
+// Encode workgroups that a compute unit holds (the LDS rings of a tile), and how
+// many a launch has unless the caller sets another number: as many as the device
+// holds beside the scan workgroup, or the two of a launch for both types. With
+// one more, a launch of as many tiles starts its last tile when another one has
+// ended: 32 float64 fields of 1 MiB, b = 128 (1024 tiles), 37.3 us a call with
+// 1024 workgroups, 35.5 with 1023; b = 1024, of whose 64 KiB tiles a compute unit
+// holds two, 33 such fields 44.8 with 1024, 40.7 with 512.
+__host__ __device__ constexpr uint32_t enc_resident(uint32_t b, uint32_t w) {
+  return enc_blocks(b, w) * b * w > kEncodeTileBytes ? 2 : 4;
+}
+__host__ __device__ constexpr uint32_t default_encode_wgs(uint32_t cus, uint32_t b, uint32_t w) {
+  return cus * enc_resident(b, w) - 2;
+}
+
 // Blocks per tile of the classification and index passes (four a thread, a
 // multiple of every encode tile).
 constexpr uint32_t kClsBlocks = 1024;

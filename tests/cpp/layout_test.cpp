@@ -26,6 +26,18 @@ int main() {
   CHECK(0.19e-6 * szx::kScanSpinLimit >= 10.0);
   CHECK(0.19e-6 * szx::kSpinLimit < 0.1);
 
+  // the encode workgroups of a launch and its two scan workgroups fit the device
+  // at once (160 KiB of LDS a compute unit; a workgroup's rings take its tile)
+  for (uint32_t w : {4u, 8u})
+    for (uint32_t b : {8u, 16u, 32u, 64u, 128u, 256u, 512u, 1024u}) {
+      const uint32_t tile = szx::enc_blocks(b, w) * b * w;
+      for (uint32_t cus : {1u, 64u, 256u}) {
+        const uint32_t n = szx::default_encode_wgs(cus, b, w) + 2;
+        CHECK(n <= cus * ((160u << 10) / (tile + 1024u)) && n <= cus * 4);
+        CHECK(n >= cus * 2);
+      }
+    }
+
   printf("layout ok\n");
   return 0;
 }
