@@ -316,18 +316,25 @@ __global__ __launch_bounds__(256) void k_stats(CBatch b) {
 // A batch of both element types runs each pass as one launch, the float32
 // fields' workgroups first, where the two types' kernels need alike registers
 // and LDS (below b = 1024): a launch for each type has its own start and its
-// own nearly empty end. Fields of 1 MiB on average, b = 128, in a launch a type,
-// and so: 8 of them 40.6 -> 28.2 us a call (graph replays), 256 of them (their
-// encode pass still a launch a type) 359 -> 343; 32 fields of 256 KiB 49.1 -> 33.4.
-// (5 us of each is the pass that ended the batch's streams, which the encode
-// pass does now.)
+// own nearly empty end. b = 128, in a launch a type, and so: 8 fields of a median of
+// 1 MiB 40.6 -> 28.2 us a call (graph replays), 32 of 256 KiB 49.1 -> 33.4. (5 us of
+// each is the pass that ended the batch's streams, which the encode pass does now.)
 template <int B>
 constexpr bool kOneLaunch = B < 1024;
-// The encode pass only up to this many tiles (512 MiB): beyond, what its code
-// for both types costs outweighs a launch. 256 fields of 512 KiB on average, a
-// launch a type and one, 194.3 and 189.8 us a call; of 1 MiB, 349.9 and 355.9; 2048
-// of 1 MiB 2176 and 2218.
-constexpr uint64_t kOneLaunchTiles = 16384;
+// The encode pass up to 4608 tiles in all (144 MiB), and up to 16384 (512 MiB) where
+// at most 2048 of them are float64: a float64 tile costs 2-3 ns more in the kernel of
+// both types, a launch and its end 6 us, and beyond 512 MiB that is nothing. Fields of 1
+// MiB, a launch a type and one, us a call at b = 128 (and 512): 96 MiB, four tenths of
+// it float64, 79.0 and 77.5 (78.9 and 79.4), three quarters 73.4 and 76.7 (73.9 and 76.6),
+// nine tenths 72.5 and 64.6 (73.3 and 65.3); 144 MiB 99.7 and 99.4 (100.4 and 101.2),
+// 96.0 and 97.8 (95.2 and 99.5), 91.9 and 90.5 (91.3 and 91.3); 192 MiB, a tenth 122.5 and
+// 116.9 (125.5 and 119.7), a fifth 124.4 and 123.5 (126.6 and 125.9), nine tenths 112.6
+// and 116.1 (114.0 and 117.0); 512 MiB, a tenth 290.7 and 288.4 (292.5 and 296.6; b = 32
+// 326.9 and 318.7), half 279.0 and 296.6 (280.9 and 301.2).
+inline bool one_encode_launch(uint64_t f32_tiles, uint64_t f64_tiles) {
+  const uint64_t all = f32_tiles + f64_tiles;
+  return all <= 4608 || (all <= 16384 && f64_tiles <= 2048);
+}
 
 template <int B>
 __global__ __launch_bounds__(256) void k_stats_both(CBatch b) {
@@ -1885,7 +1892,7 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
       const uint32_t ge = std::max(encoders(0), encoders(1)) + 2;  // two scan workgroups
       run("k_stats", [&] { k_stats_both<B><<<gs, 256, 0, stream>>>(b); });
       run("k_classify", [&] { k_classify_both<B><<<gc, 256, 0, stream>>>(b); });
-      encoded = b.tiles_enc[0] + b.tiles_enc[1] <= kOneLaunchTiles;
+      encoded = one_encode_launch(b.tiles_enc[0], b.tiles_enc[1]);
       if (encoded) run("k_encode", [&] { k_encode_both<B><<<ge, 256, 0, stream>>>(b); });
       done = true;
     }

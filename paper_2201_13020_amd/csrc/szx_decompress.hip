@@ -522,16 +522,25 @@ __global__ __launch_bounds__(256) void k_dindex(DBatch b) {
 // A batch of both element types runs each pass as one launch, the float32
 // fields' workgroups first, where the two types' kernels need alike registers
 // and LDS (below b = 1024): a launch for each type has its own start and its
-// own nearly empty end. Fields of 1 MiB on average, b = 128, in a launch a type,
+// own nearly empty end. Fields of a median of 1 MiB, b = 128, in a launch a type,
 // and so: 8 of them 23.6 -> 13.5 us a call (graph replays), 256 of them 165 ->
-// 159; 32 fields of 256 KiB 24.2 -> 14.7, at b = 512 40.3 -> 22.9.
+// 159; 32 of 256 KiB 24.2 -> 14.7, at b = 512 40.3 -> 22.9.
 template <int B>
 constexpr bool kOneLaunch = B < 1024;
-// The decode pass only up to this many tiles (768 MiB): beyond, the waves that
-// the float32 kernel's registers cost the float64 tiles outweigh a launch. 256
-// fields of 1 MiB on average, a launch a type and one, 168.6 and 163.2 us a call;
-// 512 of them 375 and 385, 2048 1457 and 1496.
-constexpr uint64_t kOneLaunchTiles = 49152;
+// The decode pass only where few tiles are of the type that loses by it: the
+// kernel of both types has the float32 kernel's registers, which cost the
+// float64 tiles waves, but at b = 512 the float64 kernel's LDS, which costs the
+// float32 tiles theirs. Fields of 1 MiB, a launch a type and one, us a call:
+// b = 128, 96 MiB, nine tenths of it float64, 36.7 and 34.1; 176 MiB, three quarters
+// (8448 tiles) 61.0 and 59.9, nine tenths (10048) 59.0 and 59.1; 192 MiB, nine tenths
+// 62.0 and 63.3; 384 MiB, half (12288) 112.6 and 114.7; 512 MiB, nine tenths 129.7 and
+// 140.5 (b = 32 134.3 and 144.9). b = 512, 160 MiB, four tenths (6144 float32 tiles) 75.1
+// and 75.8, nine tenths 82.2 and 77.2; 192 MiB, a tenth 81.5 and 88.1, half (6144) 88.5
+// and 88.5; 512 MiB, a tenth 172.4 and 196.2, nine tenths 234.4 and 234.7.
+template <int B>
+bool one_decode_launch(const DBatch& b) {
+  return B < 512 ? b.tiles_dec[1] <= 8192 : b.tiles_dec[0] <= 6144;
+}
 
 template <int B, int MODE>
 __global__ __launch_bounds__(256) void k_dindex_both(DBatch b) {
@@ -1070,7 +1079,7 @@ hipError_t launch_decompress_b(const DBatch& b, hipStream_t stream, TimerHook ho
       else
         run("k_dindex", [&] { k_dindex_both<B, kChained><<<gi, 256, 0, stream>>>(b); });
       indexed = true;
-      if (b.tiles_dec[0] + b.tiles_dec[1] <= kOneLaunchTiles) {
+      if (one_decode_launch<B>(b)) {
         run("k_decode", [&] { k_decode_both<B><<<(uint32_t)(b.tiles_dec[0] + b.tiles_dec[1]), 256, 0, stream>>>(b); });
         return hipGetLastError();
       }

@@ -25,18 +25,22 @@ from . import szx
 MULTIPLIERS = (1, 2, 3, 4, 6, 8, 12, 16)
 
 # Where the encode pass of a batch of both types is one launch: blocks below
-# 1024 values, at most 16384 tiles of 32 KiB. (A field's last tile may be a short
-# one, so the bytes give the fewest tiles there can be: a batch counted as
-# shared here may yet have two launches, never the other way round.)
+# 1024 values, at most 4608 tiles of 32 KiB, or 16384 of which at most 2048 float64.
+# (A field's last tile may be a short one, so the bytes give the fewest tiles there
+# can be: a batch counted as shared here may yet have two launches, never the other
+# way round.)
 SHARED_BELOW_BLOCK = 1024
-SHARED_BYTES = 16384 * 32768
+SHARED_BYTES = 4608 * 32768
+SHARED_MOST_BYTES, SHARED_FLOAT64_BYTES = 16384 * 32768, 2048 * 32768
 
 
 def shares_encode_launch(bytes_per_dtype, block):
     """Whether a batch of these bytes per element type may encode both types in
     one launch."""
-    present = [v for v in bytes_per_dtype.values() if v > 0]
-    return len(present) > 1 and int(block) < SHARED_BELOW_BLOCK and sum(present) <= SHARED_BYTES
+    f32, f64 = (bytes_per_dtype.get(dtype, 0) for dtype in ("float32", "float64"))
+    if f32 <= 0 or f64 <= 0 or int(block) >= SHARED_BELOW_BLOCK:
+        return False
+    return f32 + f64 <= SHARED_BYTES or (f32 + f64 <= SHARED_MOST_BYTES and f64 <= SHARED_FLOAT64_BYTES)
 
 
 def cache_path():

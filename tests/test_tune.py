@@ -146,7 +146,7 @@ def test_types_that_share_a_launch_are_tuned_together(cache, best):
     path, table = cache
     b = SharedBatch()
     timer, seen = shared_timer(b, lambda w: 1.0 + abs(w - best) / 1000.0)
-    res = tune.tune_batch(b, {"float32": 300 << 20, "float64": 100 << 20}, block=128, reps=1, timer=timer, device=DEV)
+    res = tune.tune_batch(b, {"float32": 300 << 20, "float64": 60 << 20}, block=128, reps=1, timer=timer, device=DEV)
     assert seen == [m * 256 for m in tune.MULTIPLIERS]
     assert b.launched() == best and b.geom == {"float32": best, "float64": best}
     assert all(res[dt][0] == best and res[dt][1] == pytest.approx(1.0) for dt in ("float32", "float64"))
@@ -155,7 +155,11 @@ def test_types_that_share_a_launch_are_tuned_together(cache, best):
 
 def test_where_types_share_a_launch():
     assert tune.shares_encode_launch({"float32": 1 << 20, "float64": 1}, 128)
-    assert tune.shares_encode_launch({"float32": 256 << 20, "float64": 256 << 20}, 512)
-    assert not tune.shares_encode_launch({"float32": 256 << 20, "float64": (256 << 20) + 1}, 512)
+    assert tune.shares_encode_launch({"float32": 256 << 20, "float64": 64 << 20}, 512)
+    assert not tune.shares_encode_launch({"float32": 256 << 20, "float64": (64 << 20) + 1}, 512)
+    assert tune.shares_encode_launch({"float32": 448 << 20, "float64": 64 << 20}, 512)
+    assert not tune.shares_encode_launch({"float32": (448 << 20) + 1, "float64": 64 << 20}, 512)
+    assert tune.shares_encode_launch({"float32": 44 << 20, "float64": 100 << 20}, 64)
+    assert not tune.shares_encode_launch({"float32": (44 << 20) + 1, "float64": 100 << 20}, 64)
     assert not tune.shares_encode_launch({"float32": 1 << 20, "float64": 1 << 20}, 1024)
     assert not tune.shares_encode_launch({"float32": 1 << 20, "float64": 0}, 128)
