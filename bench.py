@@ -812,7 +812,8 @@ def bench_batch(args):
                                f"{100 * by_dtype['float64'] / total:.0f}% of bytes float64, 1-3 dims, REL "
                                "1e-2/1e-3/1e-4 per field, block 128; one step = batched compress + batched decompress",
                    "fields": len(xs), "bytes": total, "block": BLOCK, "parallelism": "single GPU",
-                   "launch": "hip graph replay, one launch per pass"},
+                   "launch": "hip graph replay, launches a run: "
+                             + ", ".join(f"{k} {v['launches_per_run']}" for k, v in kernels.items())},
         "detail": {
             "ratio": round(total / comp_total, 4),
             "ms": {k: round(v, 4) for k, v in ms.items()},

@@ -200,10 +200,13 @@ sz_status sz_stitch(const sz_params* field, uint32_t nshards, const void* const*
    A batch compresses (or decompresses) many fields of mixed element types,
    sizes and bounds with one launch per pass over all of them: one extrema
    launch, one classification launch, one persistent encode launch (float32
-   tiles of every field, then float64 tiles; blocks of 1024 values, and the
-   encoding and decoding of large batches: a launch a type), and one for the fields without values if there are any. Each field's
-   stream is byte-identical to what sz_compress writes for it alone (a large
-   single call runs the same kernels as a batch of one, a small one fewer).
+   tiles of every field, then float64 tiles), and one for the fields without
+   values if there are any. (A launch a type: every pass where blocks have 1024
+   values; the encode pass above 144 MiB, or above 512 MiB where at most 64 MiB
+   are float64; the decode pass above 128 MiB of float64, or with blocks of 512
+   above 96 MiB of float32.) Each field's stream is byte-identical to what
+   sz_compress writes for it alone (a large single call runs the same kernels,
+   built for one field; a small or middle one has kernels of its own).
    All fields of a batch share one block size. The batch's descriptor table
    and tile maps live in its workspace: sz_batch_create_* writes them there
    once (a synchronous copy; call it outside graph capture), then every

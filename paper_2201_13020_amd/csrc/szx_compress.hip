@@ -1,8 +1,9 @@
 // szx_compress.hip -- compression kernels of the SZx method for gfx950.
 //
-// Pipeline of one sz_compress call, or of one batch of fields (all on the
-// caller's stream; every pass is one launch over all fields of the batch, a
-// single call being a batch of one, so both run the same code):
+// Pipeline of one large sz_compress call, or of one batch of fields (all on the
+// caller's stream; every pass is one launch over all fields of the batch, or one a
+// type where that is faster; a large single call is a batch of one, with its own
+// list of tiles):
 //   k_stats     clears the counters, tickets and tile status words the later
 //               passes use; per-block totalOrder min/max (Alg. 1 needs both
 //               for mu_k); each workgroup folds its finite value range into
@@ -22,10 +23,10 @@
 //               take tiles from interleaved ticket counters (float32 tiles of
 //               all fields, then float64 tiles); each tile's output offset comes
 //               from a single-pass prefix sum over the tiles (Sec. V-B) by
-//               workgroup 0, and while a tile waits for it the next tile is
+//               a scan workgroup, and while a tile waits for it the next tile is
 //               encoded. Bytes are packed in LDS and leave in aligned 16-byte
 //               stores. The stream ends there too (mid-byte total, stream
-//               size): by workgroup 0 in a single call, with its field's last
+//               size): by the scan workgroup in a single call, with its field's last
 //               tile in a batch.
 //   Short single calls take fewer launches: one of one workgroup (k_small), or
 //   k_stats and one more launch that classifies and encodes (k_mid).
@@ -108,18 +109,6 @@ __device__ __forceinline__ int load_run(const T* __restrict__ x, uint64_t i0, ui
     cnt += ok ? 1 : 0;
   }
   return cnt;
-}
-
-// Load the first cnt of EPL consecutive values at x + i0 (aligned to EPL);
-// the others are zero.
-template <typename T, int EPL>
-__device__ __forceinline__ void load_count(const T* __restrict__ x, uint32_t i0, int cnt, T (&v)[EPL]) {
-  if (cnt == EPL) {
-    load_run<T, EPL>(x, i0, (uint64_t)i0 + EPL, v);
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < EPL; ++i) v[i] = i < cnt ? x[i0 + i] : (T)0;
 }
 
 // Inclusive running min (MAX = false) or max over groups of G consecutive
@@ -1128,8 +1117,8 @@ struct EncShared {
 // and, about as long, 18 vector instructions a value plus 250 a tile. Measured
 // there 36 us a launch, and 233 us on 2^28 float64 values at REL 1e-3 (43 and
 // 421 us with a barrier for every row's sums, LDS atomics for every packed
-// dword and tickets for constant tiles); 256 fields of 1 MiB on average, 185 us
-// for the float32 ones and 31 for the float64 ones (239 and 35). Smaller
+// dword and tickets for constant tiles); 256 fields of a median of 1 MiB (599 MiB), 185
+// us for the float32 ones and 31 for the float64 ones (239 and 35). Smaller
 // workgroups without the pending tile, eight a compute unit, took 51 us: every
 // tile then waits 4-5 us for its offset.
 //
@@ -1852,7 +1841,12 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
   // The lines lie where the ways meet (b = 128, us a call): one launch of one
   // workgroup takes 8.5 at 64 KiB of float32 values, 10.9 at 96 KiB, two launches
   // 10.1 and 10.3; float64 8.3 at 64 KiB, 10.5 at 96, 12.1 at 128 and 11.4, 10.6,
-  // 11.3. (A shard's bound comes from elsewhere.)
+  // 11.3. Other block sizes meet there too: 64 KiB of float32 take 10.4, 8.5, 8.9, 9.0
+  // and 9.0 in one and 12.2, 10.9, 11.0, 11.0 and 11.3 in two at b = 8, 32, 256, 512 and
+  // 1024; 96 KiB of float64 10.4, 10.2, 10.8, 10.9 and 12.0, and 12.4, 11.3, 12.3, 12.3 and
+  // 15.1. (Fields of raw blocks alone would meet at 32 and 64 KiB: b = 128, 64 KiB of float32
+  // 13.6 and 12.4, 96 KiB of float64 17.0 and 12.8; three launches took 20. A shard's
+  // bound comes from elsewhere.)
   const bool single = !b.fields && !b.any_empty && b.one.next_range == 0;
   if (single && b.one.n * (b.one.dtype == 0 ? 4 : 8) <= (b.one.dtype == 0 ? kSmallBytes<float> : kSmallBytes<double>)) {
     if (b.one.dtype == 0)
@@ -1866,7 +1860,10 @@ hipError_t launch_compress_b(const CBatch& b, const CLaunchGeom& g, hipStream_t 
   // blocks. float32, b = 128: 8192 blocks in 128 tiles 15.2 us in two, 18.4 in
   // three; 16384 blocks 19.4 and 18.9; b = 256, 256 tiles 16.7 and 19.2, 320
   // tiles 21.6 and 21.0. float64, b = 128: 8192 blocks in 256 tiles 17.5 and
-  // 18.9, 10240 in 320 22.1 and 20.3.
+  // 18.9, 10240 in 320 22.1 and 20.3. Within the lines two are faster at every block
+  // size, for raw blocks too: 8192 blocks or 256 tiles at b = 8, 32, 512 and 1024 take 13.7,
+  // 14.8, 15.8 and 15.2 in two, 19.1, 18.2, 19.1 and 19.7 in three (float64 15.3, 16.4, 15.3 and
+  // 18.8, and 18.4, 18.6, 19.5 and 25.0).
   if (single && b.one.nblk <= kMidBlocks && b.tiles_enc[0] + b.tiles_enc[1] <= kMidTiles) {
     const uint32_t gs = (uint32_t)(b.tiles_stats[0] + b.tiles_stats[1]);
     const uint32_t ge = (uint32_t)(b.tiles_enc[0] + b.tiles_enc[1]);

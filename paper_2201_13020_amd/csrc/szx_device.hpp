@@ -226,7 +226,6 @@ __device__ __forceinline__ U top_bytes_mask(int nb) {
 
 // Leading zero bits of z; any value >= the width for z = 0 (callers cap it).
 __device__ __forceinline__ uint32_t lead_zero_bits(uint32_t z) { return (uint32_t)__clz((int)z); }
-__device__ __forceinline__ uint32_t lead_zero_bits(uint64_t z) { return (uint32_t)__clzll((long long)z); }
 
 __device__ __forceinline__ uint32_t byte_swap(uint32_t v) { return __builtin_bswap32(v); }
 __device__ __forceinline__ uint64_t byte_swap(uint64_t v) { return __builtin_bswap64(v); }
@@ -267,27 +266,6 @@ __device__ __forceinline__ uint32_t dpp_shr(int d, uint32_t v) {
     case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
     case 4: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
     default: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
-  }
-}
-
-// The value of the previous lane within groups of G <= 16 lanes (row_shr:1;
-// the first lane of each row of 16 gets 0, other group starts get their
-// neighbour, which callers replace).
-__device__ __forceinline__ uint32_t lane_before_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
-}
-template <int G, typename U>
-__device__ __forceinline__ U lane_before(U v) {
-  if constexpr (G <= 16) {
-    if constexpr (sizeof(U) == 4) {
-      return (U)lane_before_u32((uint32_t)v);
-    } else {
-      const uint32_t lo = lane_before_u32((uint32_t)v);
-      const uint32_t hi = lane_before_u32((uint32_t)(v >> 32));
-      return ((U)hi << 32) | lo;
-    }
-  } else {
-    return __shfl_up(v, 1, G);
   }
 }
 
@@ -378,13 +356,6 @@ __device__ __forceinline__ U group_max(U v) {
     const U o = __shfl_xor(v, d, G);
     v = o > v ? o : v;
   }
-  return v;
-}
-
-template <int G, typename V>
-__device__ __forceinline__ V group_sum(V v) {
-#pragma unroll
-  for (int d = 1; d < G; d <<= 1) v += __shfl_xor(v, d, G);
   return v;
 }
 

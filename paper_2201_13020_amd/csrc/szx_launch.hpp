@@ -1,7 +1,8 @@
 // szx_launch.hpp -- what the host API hands to the kernels: one descriptor per
 // field, and a batch of descriptors with maps from each pass's global tile
-// numbering to the field. A single call is a batch of one field passed by
-// value (fields == nullptr), so single and batched calls run the same code.
+// numbering to the field. A single call passes its field by value (fields ==
+// nullptr): a large one runs a batch's kernels, built for one field, a small or
+// middle one kernels of its own with fewer launches.
 #pragma once
 
 #include <hip/hip_runtime.h>

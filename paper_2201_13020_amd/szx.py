@@ -396,8 +396,8 @@ def to_host_stream(out, out_size):
 
 class Batch:
     """A planned batch: its descriptor table lives in `ws`; run() enqueues the
-    passes over all fields (one launch per pass). Keeps the tensors it names
-    alive for its own lifetime."""
+    passes over all fields (one launch per pass, or one a type where that is
+    faster). Keeps the tensors it names alive for its own lifetime."""
 
     def __init__(self, handle, ws, keep, outs=None, sizes=None, statuses=None):
         self._h = handle
