@@ -807,10 +807,13 @@ __device__ __forceinline__ void decode_tile(const FieldD& a, uint32_t t, bool di
         per = raw ? (uint32_t)BYTES : nb;
         some_raw = __ballot(raw) != 0;
         // A row of raw blocks alone is its stored bytes, realigned. (Lane by lane, as
-        // below, their runs of 64 or 128 bytes would all start in the same four or
-        // two LDS banks. 160 MB of raw blocks: float32, b = 128, 178 us a call so and
-        // 80 this way; float64 171 and 72, b = 1024 329 and 94.)
-        if (__builtin_expect(some_raw, 0) && __ballot(raw || cnt == 0) == ~0ull) {
+        // below, their runs of 64 or 128 bytes all start in the same four or two LDS
+        // banks. 160 MB of raw blocks, us a call with the general reads of raw lanes
+        // there too, without, and this way: float32, b = 128, 178, 92 and 80; float64
+        // 171, 79 and 72, b = 1024 329, 147 and 94. Smaller blocks do without: there the
+        // path's code costs coded rows 1 %, the 100x500x500 float32 field at REL 1e-3
+        // 32.2 us for 31.8.)
+        if (B >= 512 && __builtin_expect(some_raw, 0) && __ballot(raw || cnt == 0) == ~0ull) {
           const uint32_t at = uniform(done);
           const uint4* const q = reinterpret_cast<const uint4*>(stage + (at & ~15u));
 #pragma unroll 1
